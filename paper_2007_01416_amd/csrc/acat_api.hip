@@ -214,7 +214,12 @@ acat_status do_step(const acat_problem* prob, const double* u_in, double* u_out,
     st.part = reinterpret_cast<double*>(w + L.part);
   }
   hipStream_t s = static_cast<hipStream_t>(stream);
-  hipError_t e = k.dim == 1 ? launch_step_1d(k, st, 0, s) : launch_step_2d(k, st, 0, s);
+  // a 1D step none of whose decisions are recorded leaves nothing to read in
+  // the workspace either, and runs by tiles
+  const bool recorded = dec && (dec->order_x || dec->psi1_x || dec->alpha_x);
+  hipError_t e = k.dim == 2             ? launch_step_2d(k, st, 0, s)
+                 : replay || recorded ? launch_step_1d(k, st, 0, s)
+                                        : launch_tile_1d(k, st, s);
   return e == hipSuccess ? ACAT_OK : ACAT_ERR_DEVICE;
 }
 
@@ -279,10 +284,23 @@ acat_status check_batch(const acat_batch* bt) {
   return ACAT_OK;
 }
 
+// Cells per tile of a batched problem: 4 GPW r - 1 (r rounds of order P for
+// each of a block's four waves, as in a single problem), r as large as leaves
+// the batch some 4096 tiles, four times what the chip holds at once, so that
+// the tiles dealt out last fill its gaps.
+int batch_tile_cells(int P, int64_t ncell) {
+  const int gpw = P == 3 ? 10 : 32 / P, per = 4 * gpw;
+  const int64_t r = ncell / ((int64_t)per * 4096);
+  const int rmax = BLOCK / per;
+  return per * (int)(r < 1 ? 1 : r > rmax ? rmax : r) - 1;
+}
+
 struct BLayout {
-  size_t hdr, coff, ioffs, N, P, bc, dx, pif, pcell, smax, ord, psi, al, wmax, F, hist, offs, list, total;
-  int64_t ncell, nif;
+  size_t hdr, coff, ioffs, N, P, bc, dx, pif, pcell, tiles, tfirst, tcount, smax, ord, psi, al, wmax, tmax, F, hist,
+      offs, list, total;
+  int64_t ncell, nif, ntiles;
   int Pmax;
+  int T[BATCH_PMAX + 1];   // cells per tile of the problems of half-width P
 };
 
 BLayout blayout(const acat_batch* bt) {
@@ -295,6 +313,8 @@ BLayout blayout(const acat_batch* bt) {
     if (bt->P[b] > L.Pmax) L.Pmax = bt->P[b];
   }
   const int64_t tiles = (L.nif + BLOCK - 1) / BLOCK;
+  for (int P = 1; P <= BATCH_PMAX; ++P) L.T[P] = batch_tile_cells(P, L.ncell);
+  for (int b = 0; b < np; ++b) L.ntiles += (bt->n[b] + L.T[bt->P[b]] - 1) / L.T[bt->P[b]];
   size_t o = 0;
   L.hdr = o;   o += align_up(sizeof(int32_t) * MAX_CLASSES);
   L.coff = o;  o += align_up(sizeof(int64_t) * (np + 1));
@@ -305,11 +325,15 @@ BLayout blayout(const acat_batch* bt) {
   L.dx = o;    o += align_up(sizeof(double) * np);
   L.pif = o;   o += align_up(sizeof(int32_t) * L.nif);
   L.pcell = o; o += align_up(sizeof(int32_t) * L.ncell);
+  L.tiles = o; o += align_up(sizeof(int32_t) * 4 * L.ntiles);
+  L.tfirst = o; o += align_up(sizeof(int32_t) * np);
+  L.tcount = o; o += align_up(sizeof(int32_t) * np);
   L.smax = o;  o += align_up(sizeof(double) * np);
   L.ord = o;   o += align_up((size_t)L.nif);
   L.psi = o;   o += align_up(sizeof(double) * L.nif);
   L.al = o;    o += align_up(sizeof(double) * L.nif);
   L.wmax = o;  o += align_up(sizeof(double) * ((L.ncell + 63) / 64));
+  L.tmax = o;  o += align_up(sizeof(double) * L.ntiles);
   L.F = o;     o += align_up(sizeof(double) * bt->nvar * L.nif);
   L.hist = o;  o += align_up(sizeof(int32_t) * MAX_CLASSES * tiles);
   L.offs = o;  o += align_up(sizeof(int32_t) * MAX_CLASSES * (tiles + 1));
@@ -344,7 +368,11 @@ KBatch make_kbatch(const acat_batch* bt, const BLayout& L, char* w) {
     k.waves[p] = bt->launch && bt->launch[2 * (p - 1)] > 0 ? bt->launch[2 * (p - 1)] : 4;
     k.per_cu[p] = bt->launch ? bt->launch[2 * (p - 1) + 1] : 0;
   }
-  k.fused_flux = bt->launch ? 0 : 1;
+  k.by_tiles = bt->launch ? 0 : 1;
+  k.tiles = reinterpret_cast<const int32_t*>(w + L.tiles);
+  k.tfirst = reinterpret_cast<const int32_t*>(w + L.tfirst);
+  k.tcount = reinterpret_cast<const int32_t*>(w + L.tcount);
+  k.ntiles = (int)L.ntiles;
   k.waves[0] = 4;
   k.per_cu[0] = 0;
   return k;
@@ -526,6 +554,22 @@ acat_status acat_batch_init(const acat_batch* batch, void* workspace, size_t wor
     for (int64_t k = ioffs[b]; k < ioffs[b + 1]; ++k) pif[k] = b;
     for (int64_t e = coff[b]; e < coff[b + 1]; ++e) pcell[e] = b;
   }
+  // tiles, the problems of the highest P first
+  int32_t* tile = reinterpret_cast<int32_t*>(host.data() + (L.tiles - L.coff));
+  int32_t* tfirst = reinterpret_cast<int32_t*>(host.data() + (L.tfirst - L.coff));
+  int32_t* tcount = reinterpret_cast<int32_t*>(host.data() + (L.tcount - L.coff));
+  int32_t nt = 0;
+  for (int q = BATCH_PMAX; q >= 1; --q)
+    for (int b = 0; b < np; ++b) {
+      if (P[b] != q) continue;
+      tfirst[b] = nt;
+      for (int64_t c0 = 0; c0 < batch->n[b]; c0 += L.T[q], ++nt) {
+        tile[4 * (int64_t)nt] = b;
+        tile[4 * (int64_t)nt + 1] = (int32_t)c0;
+        tile[4 * (int64_t)nt + 2] = L.T[q];
+      }
+      tcount[b] = nt - tfirst[b];
+    }
   char* w = static_cast<char*>(workspace);
   if (hipMemcpy(w + L.coff, host.data(), host.size(), hipMemcpyHostToDevice) != hipSuccess) return ACAT_ERR_DEVICE;
   return ACAT_OK;
@@ -561,6 +605,7 @@ acat_status step_batched(const acat_batch* batch, const double* u_in, double* u_
   if (fused_cfl) {
     st.smax = reinterpret_cast<unsigned long long*>(w + L.smax);
     st.wmax = reinterpret_cast<double*>(w + L.wmax);
+    st.tmax = reinterpret_cast<double*>(w + L.tmax);
     st.dt_next = dt_dev;
     st.cfl = cfl;
   }

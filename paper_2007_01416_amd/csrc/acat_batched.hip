@@ -3,17 +3,21 @@
 // together.  The interfaces of all problems are classified in one launch,
 // grouped into per-order work lists shared by all problems, and each order
 // class is one persistent launch over every problem, so the small problems
-// of a batch fill the GPU together.  Per interface the arithmetic is that of
-// the single-problem kernels (same rounding), so a batched step equals the
-// per-problem steps bit for bit.
+// of a batch fill the GPU together.  That is the path of a batch with a launch
+// table; without one the whole step is one launch over tiles of the problems
+// (tile1d.hpp).  Per interface the arithmetic is that of the single-problem
+// kernels (same rounding), so a batched step equals the per-problem steps bit
+// for bit.
 //
 // Layout: states are SoA over the concatenated cells, u[var][coff_b + i];
 // interface arrays are concatenated the same way with offsets ioff_b.
 #include <hip/hip_runtime.h>
 
 #include "acat_internal.hpp"
+#include "cat1d.hpp"
 #include "coeffs.hpp"
 #include "step_common.hpp"
+#include "tile1d.hpp"
 
 namespace acat {
 
@@ -40,16 +44,7 @@ __global__ __launch_bounds__(BLOCK) void k_classify_b(KBatch bt, KBStep st) {
     }
     ps = SelectRT<NV, GW, BATCH_PMAX>::run(v, bt.P[b], bt.eps, bt.theta);
     double psi1 = -1.0, al = -1.0;
-    if (ps == 1) {
-      psi1 = limiter<NV, GW>(v);
-      double uL[NV], uR[NV];
-#pragma unroll
-      for (int c = 0; c < NV; ++c) {
-        uL[c] = v[c][GW - 1];
-        uR[c] = v[c][GW];
-      }
-      al = fmax(spectral_radius<FLUX, 1, NV>(bt.ph, uL, 0), spectral_radius<FLUX, 1, NV>(bt.ph, uR, 0));
-    }
+    if (ps == 1) low_order_weights<FLUX, NV, GW>(bt.ph, 0, v, psi1, al);
     st.ord[kg] = (int8_t)ps;
     st.psi[kg] = psi1;
     st.al[kg] = al;
@@ -58,200 +53,45 @@ __global__ __launch_bounds__(BLOCK) void k_classify_b(KBatch bt, KBStep st) {
   block_hist(sh, valid, ps - 1, st.hist);
 }
 
-// LDS doubles of the exchange buffers of order p at BS threads per block
-template <int NV, int p, int BS>
-constexpr int flux_b_lds() {
-  return 2 * NV * Groups<2 * p, BS>::TOTAL * (2 * p + 1);
-}
-
-// Interfaces of order p of every problem (same arithmetic as k_flux1d), BS
-// threads per block: BS / 2p interfaces per round; the block's share of the
-// class list is `sl`; xsmem: the block's LDS exchange buffers
-// (flux_b_lds<NV, p, BS>() doubles).
+// Interfaces of order p of every problem, BS threads per block.
 template <int FLUX, int NV, int p, int BS>
-__device__ __forceinline__ void flux_b_body(const KBatch& bt, const KBStep& st, const Slice& sl, double* xsmem) {
-  constexpr int L = 2 * p;
-  using Grp = Groups<L, BS>;
-  constexpr int GPB = Grp::PER_BLOCK;
-  constexpr int SL = L + 1;
-  constexpr int NS = Grp::TOTAL * SL;
-  auto& xs = *reinterpret_cast<double (*)[2][NV][NS]>(xsmem);
-
-  const Grp grp(threadIdx.x);
-  const int g = grp.g;
-  const int a = grp.node;
-  const int slot = g * SL + a;
-  const bool inblk = grp.in;
-
-  double g1[L];
-#pragma unroll
-  for (int l = 0; l < L; ++l) g1[l] = TB.G1[p][a][l];
-
-  int buf = 0;
-  for (int64_t base = sl.lo; base < sl.hi; base += GPB) {
-    const bool valid = inblk && base + g < sl.hi;
-    const int64_t kg = valid ? sl.items[base + g] : 0;
+__global__ __launch_bounds__(BS) void k_flux_b(KBatch bt, KBStep st) {
+  using Cat = Cat1D<FLUX, NV, p, BS>;
+  __shared__ double xs[Cat::LDS_DOUBLES];
+  const Cat cat(threadIdx.x);
+  const Slice sl(st.counts, st.list, p - 1);
+  for (int64_t base = sl.lo; base < sl.hi; base += Cat::PER_ROUND) {
+    const bool valid = cat.in && base + cat.g < sl.hi;
+    const int64_t kg = valid ? sl.items[base + cat.g] : 0;
     const int b = bt.pif[kg];
     const int n = bt.N[b], bc = bt.bc[b];
     const int i = (int)(kg - bt.ioffs[b]) - (bc == PERIODIC ? 0 : 1);
     const double* ub = st.u + bt.coff[b];
     const double lam = st.dt[b] / bt.dx[b];
-    const int node = bc_index32(i + (a - p + 1), n, bc);
+    const int node = bc_index32(i + (cat.a - p + 1), n, bc);
     double u[NV];
 #pragma unroll
     for (int c = 0; c < NV; ++c) u[c] = valid ? ub[c * bt.ncell + node] : 1.0;
-
-    double fh0[NV], cur[NV], S[NV];
-    flux1d<FLUX, NV>(bt.ph, u, fh0);
+    double Fc[2];
+    cat.flux(bt.ph, u, lam, xs, Fc[0], Fc[1]);
+    if (!valid) continue;
 #pragma unroll
-    for (int c = 0; c < NV; ++c) {
-      cur[c] = fh0[c];
-      S[c] = fma(TB.INVFACT[1], fh0[c], 0.0);
-    }
-    double W[L][NV];   // Taylor predictions at the time nodes r != 0, one term per level
+    for (int task = 0; task < (NV > Cat::L ? 2 : 1); ++task) {
+      const int c = cat.a + task * Cat::L;
+      if (c >= NV) continue;
+      double F = Fc[task];
+      if constexpr (p == 1) {
+        const int nl = bc_index32(i, n, bc), nr = bc_index32(i + 1, n, bc);
+        double uL[NV], uR[NV];
 #pragma unroll
-    for (int ri = 0; ri < L; ++ri)
-#pragma unroll
-      for (int c = 0; c < NV; ++c) W[ri][c] = u[c];
-#pragma unroll
-    for (int kk = 2; kk <= 2 * p; ++kk) {
-#pragma unroll
-      for (int c = 0; c < NV; ++c) xs[buf][c][slot] = cur[c];
-      Grp::sync();
-      double Uk[NV];
-#pragma unroll
-      for (int c = 0; c < NV; ++c) {
-        double sacc = 0.0;
-#pragma unroll
-        for (int l = 0; l < L; ++l) sacc = fma(g1[l], xs[buf][c][g * SL + l], sacc);
-        Uk[c] = -lam * sacc;
-      }
-      buf ^= 1;
-#pragma unroll
-      for (int ri = 0; ri < L; ++ri) {
-        const int r = ri - p + 1;
-        if (r == 0) continue;
-#pragma unroll
-        for (int c = 0; c < NV; ++c) W[ri][c] = fma(TB.TAYLOR[r + PMAX - 1][kk - 1], Uk[c], W[ri][c]);
-      }
-      double nxt[NV];
-#pragma unroll
-      for (int c = 0; c < NV; ++c) nxt[c] = 0.0;
-#pragma unroll
-      for (int ri = 0; ri < L; ++ri) {
-        const int r = ri - p + 1;
-        if (TB.GT[p][kk - 1][ri] == 0.0) continue;   // zero weight: nothing to add
-        double ph[NV];
-        if (r == 0) {
-#pragma unroll
-          for (int c = 0; c < NV; ++c) ph[c] = fh0[c];
-        } else {
-          flux1d<FLUX, NV>(bt.ph, W[ri], ph);
+        for (int cc = 0; cc < NV; ++cc) {
+          uL[cc] = ub[cc * bt.ncell + nl];
+          uR[cc] = ub[cc * bt.ncell + nr];
         }
-#pragma unroll
-        for (int c = 0; c < NV; ++c) nxt[c] = fma(TB.GT[p][kk - 1][ri], ph[c], nxt[c]);
+        F = fl_cat2<FLUX, NV>(bt.ph, 0, uL, uR, c, F, st.psi[kg], st.al[kg], 0.0);
       }
-#pragma unroll
-      for (int c = 0; c < NV; ++c) {
-        cur[c] = nxt[c];
-        S[c] = fma(TB.INVFACT[kk], nxt[c], S[c]);
-      }
+      st.F[c * bt.nif + kg] = F;
     }
-#pragma unroll
-    for (int c = 0; c < NV; ++c) xs[buf][c][slot] = S[c];
-    Grp::sync();
-    if (valid && a < NV) {
-      for (int task = 0; task < 2; ++task) {
-        const int c = a + task * L;
-        if (c >= NV) break;
-        double F = 0.0;
-#pragma unroll
-        for (int l = 0; l < L; ++l) F = fma(TB.ETA[p][l], xs[buf][c % NV][g * SL + l], F);
-        if constexpr (p == 1) {
-          const double psi = st.psi[kg], al = st.al[kg];
-          const int nl = bc_index32(i, n, bc), nr = bc_index32(i + 1, n, bc);
-          double uL[NV], uR[NV], fL[NV], fR[NV];
-#pragma unroll
-          for (int cc = 0; cc < NV; ++cc) {
-            uL[cc] = ub[cc * bt.ncell + nl];
-            uR[cc] = ub[cc * bt.ncell + nr];
-          }
-          flux1d<FLUX, NV>(bt.ph, uL, fL);
-          flux1d<FLUX, NV>(bt.ph, uR, fR);
-          double ul = 0.0, ur = 0.0, fl = 0.0, fr = 0.0;
-#pragma unroll
-          for (int cc = 0; cc < NV; ++cc)
-            if (cc == c) {
-              ul = uL[cc];
-              ur = uR[cc];
-              fl = fL[cc];
-              fr = fR[cc];
-            }
-          const double flo = 0.5 * (fl + fr) - (0.5 * al) * (ur - ul);
-          F = psi * F + (1.0 - psi) * flo;
-        }
-        st.F[c * bt.nif + kg] = F;
-      }
-    }
-    buf ^= 1;
-  }
-}
-
-template <int FLUX, int NV, int p, int BS>
-__global__ __launch_bounds__(BS) void k_flux_b(KBatch bt, KBStep st) {
-  __shared__ double xsmem[flux_b_lds<NV, p, BS>()];
-  flux_b_body<FLUX, NV, p, BS>(bt, st, Slice(st.counts, st.list, p - 1), xsmem);
-}
-
-// Every order class in one persistent launch (256 threads per block): the
-// grid is cut into runs of whole XCD groups of blocks, one run per class
-// with interfaces, sized by the class's work (interfaces times the flops of
-// one interface of that order); each block runs the kernel body of its
-// class over its share of that class's list.  Same arithmetic per interface
-// as the per-class launches.
-template <int NV>
-constexpr int flux_b_all_lds() {
-  constexpr int a = flux_b_lds<NV, 1, BLOCK>(), b = flux_b_lds<NV, 2, BLOCK>();
-  constexpr int c = flux_b_lds<NV, 3, BLOCK>(), d = flux_b_lds<NV, 4, BLOCK>();
-  constexpr int ab = a > b ? a : b, cd = c > d ? c : d;
-  return ab > cd ? ab : cd;
-}
-
-template <int FLUX, int NV>
-__global__ __launch_bounds__(BLOCK) void k_flux_b_all(KBatch bt, KBStep st) {
-  __shared__ double xsmem[flux_b_all_lds<NV>()];
-  // relative cost of one interface of order p (1D Euler flops of the recursion)
-  constexpr int64_t cost[BATCH_PMAX + 1] = {0, 172, 1212, 4482, 11192};
-  const int units = (int)gridDim.x / NXCD;
-  int64_t work[BATCH_PMAX + 1], total = 0;
-  int nz = 0;
-#pragma unroll
-  for (int p = 1; p <= BATCH_PMAX; ++p) {
-    work[p] = p <= bt.Pmax ? (int64_t)st.counts[p - 1] * cost[p] : 0;
-    total += work[p];
-    nz += work[p] > 0;
-  }
-  if (total == 0) return;
-  // units per class: one each for classes with work, the rest in proportion to the work
-  int u[BATCH_PMAX + 1], used = 0;
-#pragma unroll
-  for (int p = 1; p <= BATCH_PMAX; ++p) {
-    u[p] = work[p] > 0 ? 1 + (int)((int64_t)(units - nz) * work[p] / total) : 0;
-    used += u[p];
-  }
-  const int unit = (int)blockIdx.x / NXCD;
-  if (unit >= used) return;
-  int p = 1, first = 0;
-  while (unit >= first + u[p]) {
-    first += u[p];
-    ++p;
-  }
-  const int blk = (int)blockIdx.x - first * NXCD, nblk = u[p] * NXCD;
-  switch (p) {
-    case 1: flux_b_body<FLUX, NV, 1, BLOCK>(bt, st, Slice(st.counts, st.list, 0, blk, nblk), xsmem); break;
-    case 2: flux_b_body<FLUX, NV, 2, BLOCK>(bt, st, Slice(st.counts, st.list, 1, blk, nblk), xsmem); break;
-    case 3: flux_b_body<FLUX, NV, 3, BLOCK>(bt, st, Slice(st.counts, st.list, 2, blk, nblk), xsmem); break;
-    default: flux_b_body<FLUX, NV, 4, BLOCK>(bt, st, Slice(st.counts, st.list, 3, blk, nblk), xsmem); break;
   }
 }
 
@@ -307,6 +147,38 @@ __global__ __launch_bounds__(BLOCK) void k_update_b(KBatch bt, KBStep st) {
       else atomicMax(&st.smax[key], (unsigned long long)__double_as_longlong(m));
     }
   }
+}
+
+// The whole step of one tile of one problem per block; CFL: and the largest
+// spectral radius of its new cells (NaN and -0 count as +0).  The tiles of
+// the highest orders come first, so that the launch ends on short ones.
+template <int FLUX, int NV, bool CFL>
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void k_tile_b(KBatch bt, KBStep st) {
+  __shared__ TileMem<FLUX, NV, BATCH_PMAX> m;
+  const int32_t* tl = bt.tiles + 4 * (int64_t)blockIdx.x;
+  const int b = tl[0];
+  const int64_t off = bt.coff[b];
+  const Tile t{st.u + off, st.uout + off, bt.ncell, bt.N[b], tl[1], tl[2], bt.P[b], bt.bc[b], bt.dx[b]};
+  const double dt = st.dt[b];
+  tile_load<FLUX, NV, BATCH_PMAX>(m, t);
+  __syncthreads();
+  double w[NV];
+  const bool has = tile_step<FLUX, NV, BATCH_PMAX, true>(m, t, bt.ph, 0, bt.eps, bt.theta, dt, st.status, w);
+  if constexpr (CFL) {
+    const double s = block_max(has ? speed_floor(spectral_radius<FLUX, 1, NV>(bt.ph, w, 0)) : 0.0, m.red);
+    if (threadIdx.x == 0) st.tmax[blockIdx.x] = s;
+  }
+}
+
+// dt[b] = cfl dx[b] / (the largest of problem b's tiles), one wave per problem.
+__global__ __launch_bounds__(64) void k_dt_tiles_b(KBatch bt, const double* tmax, double cfl, double* dt) {
+  const int b = blockIdx.x;
+  const double* mine = tmax + bt.tfirst[b];
+  double m = 0.0;
+  for (int i = threadIdx.x; i < bt.tcount[b]; i += 64) m = fmax(m, mine[i]);
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) m = fmax(m, __shfl_xor(m, off));
+  if (threadIdx.x == 0) dt[b] = cfl * bt.dx[b] / m;
 }
 
 // smax[b] = max spectral radius over problem b: one 1024-thread block per
@@ -393,7 +265,23 @@ hipError_t launch_flux_b(const KBatch& bt, const KBStep& st, hipStream_t s) {
 }
 
 template <int FLUX, int NV>
+hipError_t tiles_b_impl(const KBatch& bt, const KBStep& st, hipStream_t s) {
+  {
+    ProfScope ps("step_b", s);
+    if (st.smax) k_tile_b<FLUX, NV, true><<<bt.ntiles, BLOCK, 0, s>>>(bt, st);
+    else k_tile_b<FLUX, NV, false><<<bt.ntiles, BLOCK, 0, s>>>(bt, st);
+  }
+  ACAT_CHECK_LAUNCH();
+  if (st.smax) {
+    k_dt_tiles_b<<<bt.nprob, 64, 0, s>>>(bt, st.tmax, st.cfl, st.dt_next);
+    ACAT_CHECK_LAUNCH();
+  }
+  return hipSuccess;
+}
+
+template <int FLUX, int NV>
 hipError_t step_b_impl(const KBatch& bt, const KBStep& st, hipStream_t s) {
+  if (bt.by_tiles) return tiles_b_impl<FLUX, NV>(bt, st, s);
   const int cblocks = (int)((bt.nif + BLOCK - 1) / BLOCK);
   {
     ProfScope ps("classify_b", s);
@@ -406,22 +294,10 @@ hipError_t step_b_impl(const KBatch& bt, const KBStep& st, hipStream_t s) {
                                                          st.list);
   ACAT_CHECK_LAUNCH();
   hipError_t e;
-  if (bt.fused_flux) {
-    // one persistent launch for every order class
-    auto kern = k_flux_b_all<FLUX, NV>;
-    int grid = persistent_grid(kern, bt.nif, 0);
-    if (grid < NXCD * BATCH_PMAX) grid = NXCD * BATCH_PMAX;   // at least one XCD group per class
-    {
-      ProfScope ps("flux_b_all", s);
-      kern<<<grid, BLOCK, 0, s>>>(bt, st);
-    }
-    ACAT_CHECK_LAUNCH();
-  } else {
-    if ((e = launch_flux_b<FLUX, NV, 1>(bt, st, s)) != hipSuccess) return e;
-    if ((e = launch_flux_b<FLUX, NV, 2>(bt, st, s)) != hipSuccess) return e;
-    if ((e = launch_flux_b<FLUX, NV, 3>(bt, st, s)) != hipSuccess) return e;
-    if ((e = launch_flux_b<FLUX, NV, 4>(bt, st, s)) != hipSuccess) return e;
-  }
+  if ((e = launch_flux_b<FLUX, NV, 1>(bt, st, s)) != hipSuccess) return e;
+  if ((e = launch_flux_b<FLUX, NV, 2>(bt, st, s)) != hipSuccess) return e;
+  if ((e = launch_flux_b<FLUX, NV, 3>(bt, st, s)) != hipSuccess) return e;
+  if ((e = launch_flux_b<FLUX, NV, 4>(bt, st, s)) != hipSuccess) return e;
   {
     ProfScope ps("update_b", s);
     const unsigned grid = (unsigned)((bt.ncell + BLOCK - 1) / BLOCK);

@@ -87,6 +87,8 @@ struct ProfScope {
 
 // Launchers (return the first HIP error).
 hipError_t launch_step_1d(const KProb& pb, const KStep& st, int grid_blocks, hipStream_t stream);
+// the 1D step by tiles (no decisions recorded, no class lists kept)
+hipError_t launch_tile_1d(const KProb& pb, const KStep& st, hipStream_t stream);
 hipError_t launch_step_2d(const KProb& pb, const KStep& st, int grid_blocks, hipStream_t stream);
 hipError_t launch_max_speed(const KProb& pb, const double* u, double* smax, hipStream_t stream);
 // classification (replay: recorded orders) and per-class item lists only
@@ -113,7 +115,11 @@ struct KBatch {
   const int32_t* pcell;     // [ncell] problem of each cell
   int waves[BATCH_PMAX + 1];    // per order class p: waves per block of the flux kernel (1, 2 or 4)
   int per_cu[BATCH_PMAX + 1];   // per order class p: persistent blocks per CU (0: occupancy limit)
-  int fused_flux;               // every order class in one launch (k_flux_b_all) instead of one per class
+  int by_tiles;                 // the whole step in one launch over the tiles, instead of one pass after another
+  const int32_t* tiles;         // [ntiles][4] problem, first cell, cells, 0; the highest P first
+  const int32_t* tfirst;        // [nprob] first tile of each problem
+  const int32_t* tcount;        // [nprob] its number of tiles
+  int ntiles;
 };
 
 struct KBStep {
@@ -129,13 +135,14 @@ struct KBStep {
   int32_t* counts;
   int32_t* list;
   uint32_t* status;
-  // with smax set: the update also reduces the spectral radius of the new
+  // with smax set (passes; by tiles: tmax): the update also reduces the spectral radius of the new
   // state, one maximum per wave that lies whole inside one problem into
   // wmax[wave] and the rest into smax[problem] (bit patterns of non-negative
   // doubles, atomic maxima; zero on entry); a last kernel folds both into
   // the next time steps dt_next[b] = cfl dx[b] / max and clears smax
   unsigned long long* smax;
   double* wmax;             // [ceil(ncell / 64)]
+  double* tmax;             // [ntiles] by tiles: the maximum of each tile
   double* dt_next;
   double cfl;
 };

@@ -29,6 +29,7 @@
 #include <utility>
 
 #include "acat_internal.hpp"
+#include "cat1d.hpp"
 #include "coeffs.hpp"
 #include "step_common.hpp"
 
@@ -72,19 +73,7 @@ __global__ __launch_bounds__(BLOCK) void k_classify1d(KProb pb, KStep st) {
       }
       ps = Select<NV, G, P>::run(v, pb.eps, pb.theta, (pb.flags & FLAG_PSI2_MODIFIED) != 0);
       double psi1 = -1.0, al = -1.0;
-      if (ps == 1) {
-        psi1 = limiter<NV, G>(v);
-        if constexpr (NV == 1) {
-          if (pb.flags & FLAG_PSI1_ROE) psi1 = limiter_roe<FLUX, G>(pb.ph, v, 0);
-        }
-        double uL[NV], uR[NV];
-#pragma unroll
-        for (int c = 0; c < NV; ++c) {
-          uL[c] = v[c][G - 1];
-          uR[c] = v[c][G];
-        }
-        al = fmax(spectral_radius<FLUX, 1, NV>(pb.ph, uL, 0), spectral_radius<FLUX, 1, NV>(pb.ph, uR, 0));
-      }
+      if (ps == 1) low_order_weights<FLUX, NV, G>(pb.ph, pb.flags, v, psi1, al);
       st.ordx[k] = (int8_t)ps;
       st.psix[k] = psi1;
       st.alx[k] = al;
@@ -101,149 +90,43 @@ __global__ __launch_bounds__(BLOCK) void k_classify1d(KProb pb, KStep st) {
 }
 
 // CAT2p flux of the interfaces of order p (p = 1: FL-CAT2 blend).
-// Rounding follows one fixed order: every weighted sum of the recursion is a
-// chain of fused multiply-adds in index order, nothing else is contracted
-// (the library is built with -ffp-contract=off).
 template <int FLUX, int NV, int p>
 __global__ __launch_bounds__(BLOCK) void k_flux1d(KProb pb, KStep st) {
-  constexpr int L = 2 * p;            // lanes per interface = stencil nodes
-  using Grp = Groups<L>;
-  constexpr int GPB = Grp::PER_BLOCK; // interfaces per round
-  constexpr int SL = L + 1;           // LDS slots per interface (one pad slot against bank conflicts)
-  constexpr int NS = Grp::TOTAL * SL; // slots per component, idle lanes included
-  __shared__ double xs[2][NV][NS];
+  using Cat = Cat1D<FLUX, NV, p, BLOCK>;
+  __shared__ double xs[Cat::LDS_DOUBLES];
 
-  const Grp grp(threadIdx.x);
-  const int g = grp.g;
-  const int a = grp.node;             // node index, offset j = a - p + 1
-  const int slot = g * SL + a;
-  const bool inblk = grp.in;
+  const Cat cat(threadIdx.x);
   const double lam = step_dt(st) / pb.dx;
   const int64_t nx = pb.nx, nI = pb.nIx;
-
-  double g1[L];
-#pragma unroll
-  for (int l = 0; l < L; ++l) g1[l] = TB.G1[p][a][l];
-
-  int buf = 0;
   const Slice sl(st.counts, st.list, p - 1);
-  for (int64_t base = sl.lo; base < sl.hi; base += GPB) {
-    {
-      const bool valid = inblk && base + g < sl.hi;
-      const int32_t k = valid ? sl.items[base + g] : 0;
-      const int i = k + (int)pb.ioff;
-      const int node = bc_index32(i + (a - p + 1), (int)nx, pb.bc);
-      double u[NV];
+  for (int64_t base = sl.lo; base < sl.hi; base += Cat::PER_ROUND) {
+    const bool valid = cat.in && base + cat.g < sl.hi;
+    const int32_t k = valid ? sl.items[base + cat.g] : 0;
+    const int i = k + (int)pb.ioff;
+    const int node = bc_index32(i + (cat.a - p + 1), (int)nx, pb.bc);
+    double u[NV];
 #pragma unroll
-      for (int c = 0; c < NV; ++c) u[c] = valid ? st.u[c * nx + node] : 1.0;
-
-      double fh0[NV], cur[NV], S[NV];
-      flux1d<FLUX, NV>(pb.ph, u, fh0);
-      // S = sum_k Fh^{k-1} / k! at this node (the CAT flux, Sec. 2.2, summed node by node)
+    for (int c = 0; c < NV; ++c) u[c] = valid ? st.u[c * nx + node] : 1.0;
+    double Fc[2];
+    cat.flux(pb.ph, u, lam, xs, Fc[0], Fc[1]);
+    if (!valid) continue;
 #pragma unroll
-      for (int c = 0; c < NV; ++c) {
-        cur[c] = fh0[c];
-        S[c] = fma(TB.INVFACT[1], fh0[c], 0.0);
+    for (int task = 0; task < (NV > Cat::L ? 2 : 1); ++task) {
+      const int c = cat.a + task * Cat::L;
+      if (c >= NV) continue;
+      double F = Fc[task];
+      if constexpr (p == 1) {
+        const int64_t nl = bc_index32(i, (int)nx, pb.bc), nr = bc_index32(i + 1, (int)nx, pb.bc);
+        double uL[NV], uR[NV];
+#pragma unroll
+        for (int cc = 0; cc < NV; ++cc) {
+          uL[cc] = st.u[cc * nx + nl];
+          uR[cc] = st.u[cc * nx + nr];
+        }
+        F = fl_cat2<FLUX, NV>(pb.ph, pb.flags, uL, uR, c, F, st.psix[k], st.alx[k],
+                              pb.dx / ((double)pb.dim * step_dt(st)));
       }
-      // Taylor predictions W_r = u + sum_{l<kk} r^l/l! U^l, U^l = dt^l u~^(l), at the
-      // time nodes r != 0, one term added per level (same fma chain as summing from u)
-      double W[L][NV];
-#pragma unroll
-      for (int ri = 0; ri < L; ++ri)
-#pragma unroll
-        for (int c = 0; c < NV; ++c) W[ri][c] = u[c];
-#pragma unroll
-      for (int kk = 2; kk <= 2 * p; ++kk) {
-        // share Fh^{kk-2} of every node of the stencil
-#pragma unroll
-        for (int c = 0; c < NV; ++c) xs[buf][c][slot] = cur[c];
-        Grp::sync();
-        // U^{kk-1} = -lambda * (spatial derivative of Fh^{kk-2} at this node)
-        double Uk[NV];
-#pragma unroll
-        for (int c = 0; c < NV; ++c) {
-          double sacc = 0.0;
-#pragma unroll
-          for (int l = 0; l < L; ++l) sacc = fma(g1[l], xs[buf][c][g * SL + l], sacc);
-          Uk[c] = -lam * sacc;
-        }
-        buf ^= 1;
-#pragma unroll
-        for (int ri = 0; ri < L; ++ri) {
-          const int r = ri - p + 1;
-          if (r == 0) continue;
-#pragma unroll
-          for (int c = 0; c < NV; ++c) W[ri][c] = fma(TB.TAYLOR[r + PMAX - 1][kk - 1], Uk[c], W[ri][c]);
-        }
-        // flux at the Taylor-predicted states of the time nodes r, and its
-        // (kk-1)-th time derivative at r = 0
-        double nxt[NV];
-#pragma unroll
-        for (int c = 0; c < NV; ++c) nxt[c] = 0.0;
-#pragma unroll
-        for (int ri = 0; ri < L; ++ri) {
-          const int r = ri - p + 1;
-          // a time node whose weight is exactly zero adds nothing: its flux
-          // is not evaluated (the same sum for finite values)
-          if (TB.GT[p][kk - 1][ri] == 0.0) continue;
-          double ph[NV];
-          if (r == 0) {
-#pragma unroll
-            for (int c = 0; c < NV; ++c) ph[c] = fh0[c];
-          } else {
-            flux1d<FLUX, NV>(pb.ph, W[ri], ph);
-          }
-#pragma unroll
-          for (int c = 0; c < NV; ++c) nxt[c] = fma(TB.GT[p][kk - 1][ri], ph[c], nxt[c]);
-        }
-#pragma unroll
-        for (int c = 0; c < NV; ++c) {
-          cur[c] = nxt[c];
-          S[c] = fma(TB.INVFACT[kk], nxt[c], S[c]);
-        }
-      }
-      // F_c = sum_j eta_j S_j,c on lane a = c (and a + L when NV > L)
-#pragma unroll
-      for (int c = 0; c < NV; ++c) xs[buf][c][slot] = S[c];
-      Grp::sync();
-      double F0 = 0.0, F1 = 0.0;
-      if (valid && a < NV) {
-#pragma unroll
-        for (int l = 0; l < L; ++l) F0 = fma(TB.ETA[p][l], xs[buf][a][g * SL + l], F0);
-        if (NV > L && a + L < NV) {
-#pragma unroll
-          for (int l = 0; l < L; ++l) F1 = fma(TB.ETA[p][l], xs[buf][(a + L) % NV][g * SL + l], F1);
-        }
-      }
-      buf ^= 1;   // the assembly above may still read this buffer
-      if (valid && a < NV) {
-        for (int task = 0; task < 2; ++task) {
-          const int c = a + task * L;
-          if (c >= NV) break;
-          double F = task == 0 ? F0 : F1;
-          if constexpr (p == 1) {
-            // FL-CAT2 (Sec. 3.1): psi^1 CAT2 + (1 - psi^1) Rusanov
-            const double psi = st.psix[k], al = st.alx[k];
-            const int64_t nl = bc_index32(i, (int)nx, pb.bc), nr = bc_index32(i + 1, (int)nx, pb.bc);
-            double uL[NV], uR[NV], fL[NV], fR[NV];
-#pragma unroll
-            for (int cc = 0; cc < NV; ++cc) {
-              uL[cc] = st.u[cc * nx + nl];
-              uR[cc] = st.u[cc * nx + nr];
-            }
-            flux1d<FLUX, NV>(pb.ph, uL, fL);
-            flux1d<FLUX, NV>(pb.ph, uR, fR);
-            double ul = 0.0, ur = 0.0, fl = 0.0, fr = 0.0;
-#pragma unroll
-            for (int cc = 0; cc < NV; ++cc)
-              if (cc == c) { ul = uL[cc]; ur = uR[cc]; fl = fL[cc]; fr = fR[cc]; }
-            const double alf = pb.dx / ((double)pb.dim * step_dt(st));
-            const double flo = lo_flux<FLUX, 1, NV>(pb.ph, pb.flags, 0, uL, uR, fl, fr, ul, ur, al, alf);
-            F = psi * F + (1.0 - psi) * flo;
-          }
-          st.Fx[c * nI + k] = F;
-        }
-      }
+      st.Fx[c * nI + k] = F;
     }
   }
 }

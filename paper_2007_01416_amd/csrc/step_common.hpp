@@ -186,14 +186,19 @@ __device__ __forceinline__ void block_hist(int* sh, bool valid, int cls, int32_t
   if (threadIdx.x < MAX_CLASSES) out[(int64_t)blockIdx.x * MAX_CLASSES + threadIdx.x] = sh[threadIdx.x];
 }
 
+// dt clipped so that t does not pass t_final
+__device__ __forceinline__ double clip_dt(double dt, double t, double t_final) {
+  if (t >= t_final) return 0.0;
+  return t + dt > t_final ? t_final - t : dt;
+}
+
 // CFL rule: 1D cfl dx / s; 2D (Sec. 5.5) cfl/2 min(dx/s_x, dy/s_y); clipped at t_final
 __device__ __forceinline__ void cfl_rule(int dim, double dx, double dy, double s0, double s1, double cfl,
                                          double t_final, double* t_dev, double* dt_dev) {
   double dt = dim == 1 ? cfl * dx / s0 : 0.5 * cfl * fmin(dx / s0, dy / s1);
   if (t_dev) {
     const double t = *t_dev;
-    if (t >= t_final) dt = 0.0;
-    else if (t + dt > t_final) dt = t_final - t;
+    dt = clip_dt(dt, t, t_final);
     *t_dev = t + dt;
   }
   *dt_dev = dt;
