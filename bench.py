@@ -119,9 +119,9 @@ def bench_batched(acat, workloads, steps_batched=500, steps_single=10):
     bs.replay(steps_batched // 2)
     torch.cuda.synchronize()
     tb = time.perf_counter() - t0
-    # the same graph-replayed steps with the default launch (every order class
-    # in one flux launch: 6 launches per step) and with one flux launch per
-    # order class at the default shape (9 launches per step)
+    # the same graph-replayed steps with the default launch (the step in one
+    # launch over tiles, one more for the time steps) and with one flux launch
+    # per order class at the default shape (9 launches per step)
     def graph_ms(table):
         batch.set_launch(table)
         bd = acat.BatchSolver(batch, u0, w["cfl"])
@@ -182,18 +182,29 @@ def bench_batched(acat, workloads, steps_batched=500, steps_single=10):
     nprof = 20
     hist = torch.zeros((nprof, 4), dtype=torch.int32, device="cuda")
     torch.cuda.synchronize()
+    by_tiles = all(v[0] == 0 for v in best.values())
     acat.profile(True)
     for k in range(nprof):
         batch.cfl_dt(ue, w["cfl"], dte)
         batch.step(ue, dte, out=uo)
-        hist[k].copy_(counts)
+        if not by_tiles:
+            hist[k].copy_(counts)
         ue, uo = uo, ue
     prof = acat.profile_read()
     acat.profile(False)
+    if by_tiles:        # the tiles keep no counts: the same steps again, a launch per order class
+        batch.set_launch({p: (4, 0) for p in batch.orders})
+        ue.copy_(torch.from_numpy(u0))
+        for k in range(nprof):
+            batch.cfl_dt(ue, w["cfl"], dte)
+            batch.step(ue, dte, out=uo)
+            hist[k].copy_(counts)
+            ue, uo = uo, ue
+        batch.set_launch(None)
     per_p = hist.cpu().numpy().astype(np.int64).sum(0)
     cf = F.C_F[("euler", 1)]
-    if "flux_b_all" in prof:             # the default: every order class in one launch
-        dom_name = "flux_b_all"
+    if "step_b" in prof:                 # the default: the whole step in one launch over tiles
+        dom_name = "step_b"
         dom_launches, dom_ms = prof[dom_name]
         dom_flops = sum(int(per_p[p - 1]) * F.interface_flops_1d(p, 3, cf) for p in batch.orders)
     else:
@@ -216,7 +227,7 @@ def bench_batched(acat, workloads, steps_batched=500, steps_single=10):
             "speedup_vs_per_instance_graph": vb / (cells * steps_single_graph / tsg),
             "per_instance_eager_value": vs, "per_instance_eager_steps": steps_single,
             "per_instance_eager_ms_per_step": 1e3 * ts / steps_single, "speedup_vs_per_instance_eager": vb / vs,
-            "autotuned_launch": ("default: every order class in one launch (kept: per-class shapes not "
+            "autotuned_launch": ("default: the step in one launch over tiles (kept: per-class shapes not "
                                  "2 % faster, graph-replayed)" if all(v[0] == 0 for v in best.values()) else
                                  {f"p{p}": {"waves_per_block": v[0], "blocks_per_cu": v[1],
                                             "kernel_us": round(1e3 * v[2], 2)} for p, v in best.items()}),
@@ -476,6 +487,8 @@ def _class_profile(acat, s, nclass, steps, warmup):
     import torch
     for _ in range(warmup):
         s.step()
+    one_d = s.prob.dim == 1
+    start = acat.Solver(s.prob, s.u, s.cfl) if one_d else None
     counts = s.ws[:64].view(torch.int32)
     hist = torch.zeros((steps, 16), dtype=torch.int32, device="cuda")
     torch.cuda.synchronize()
@@ -483,11 +496,17 @@ def _class_profile(acat, s, nclass, steps, warmup):
     t0 = time.perf_counter()
     for k in range(steps):
         s.step()
-        hist[k].copy_(counts)
+        if not one_d:
+            hist[k].copy_(counts)
     torch.cuda.synchronize()
     el = time.perf_counter() - t0
     prof = acat.profile_read()
     acat.profile(False)
+    if one_d:       # a 1D step by tiles keeps no class counts: the same steps again, their orders recorded
+        dec = acat.Decisions(s.prob)
+        for k in range(steps):
+            start.step(dec=dec)
+            hist[k, :nclass].copy_(torch.bincount(dec.order_x.to(torch.int64), minlength=nclass + 1)[1:])
     return el, hist.cpu().numpy().astype(np.int64)[:, :nclass].sum(0), prof
 
 
@@ -504,14 +523,11 @@ def bench_high_order(acat, workloads, F, steps=20, warmup=3, n1d=1 << 22, n2d=20
                             gamma=w["gamma"])
         s = acat.Solver(prob, w["u"], w["cfl"])
         el, per, prof = _class_profile(acat, s, P, steps, warmup)
-        kern = {}
-        for p in range(1, P + 1):
-            name = f"flux1d_p{p}"
-            if name in prof and per[p - 1] > 0:
-                c, ms = prof[name]
-                fl = per[p - 1] * F.interface_flops_1d(p, 3, F.C_F[("euler", 1)])
-                kern[name] = {"avg_us": round(1e3 * ms / c, 2), "items": int(per[p - 1]),
-                              "frac": round(fl / (ms * 1e-3) / 1e12 / PEAK_FP64_TFLOPS, 4)}
+        # one kernel runs every order (and the classification and update): the fluxes' flops alone
+        c, ms = prof["step1d"]
+        fl = sum(int(per[p - 1]) * F.interface_flops_1d(p, 3, F.C_F[("euler", 1)]) for p in range(1, P + 1))
+        kern = {"step1d": {"avg_us": round(1e3 * ms / c, 2), "items": {f"p{p}": int(per[p - 1]) for p in range(1, P + 1)},
+                           "frac": round(fl / (ms * 1e-3) / 1e12 / PEAK_FP64_TFLOPS, 4)}}
         out[f"euler1d_P{P}_n{n1d}"] = {"value": n1d * steps / el, "unit": "cell-updates/s",
                                        "ms_per_step": 1e3 * el / steps, "kernels": kern,
                                        "device_status": acat.device_status()}

@@ -124,7 +124,9 @@ acat_status acat_workspace_size(const acat_problem* prob, size_t* bytes /* host 
 
 /* u_out = one ACAT step of u_in.  The time step is *dt_dev when dt_dev is
  * not NULL (device scalar, e.g. from acat_cfl_dt), else `dt` (> 0 or 0).
- * `dec` (nullable, host struct of device pointers) records the decisions. */
+ * `dec` (nullable, host struct of device pointers) records the decisions.  A 1D
+ * step that records none runs by tiles, with nothing but the wave-speed
+ * maxima in the workspace. */
 acat_status acat_step(const acat_problem* prob, const double* u_in, double* u_out, double dt,
                       const double* dt_dev, void* workspace, size_t workspace_bytes,
                       const acat_decisions* dec, void* stream);
@@ -224,9 +226,9 @@ acat_status acat_cfl_dt(const acat_problem* prob, const double* smax_dev, double
 /* ---------------------------------------------------------------------
  * Batched step: nprob independent 1D problems with one flux, each with its
  * own cell count n[b], largest half-width P[b], boundary bc[b], spacing
- * dx[b] and time step dt[b], advanced together (one classification launch,
- * one persistent flux launch over all problems and order classes, or one
- * per order class with a launch table below).  Per problem
+ * dx[b] and time step dt[b], advanced together (one launch over tiles of all
+ * problems, or, with a launch table below, one classification launch and one
+ * persistent flux launch per order class).  Per problem
  * the result equals acat_step bit for bit.
  *   States: SoA over the concatenated cells, u[var][coff_b + i] with
  *   coff_b = n[0] + ... + n[b-1] (total C cells: arrays of nvar * C).
@@ -245,12 +247,12 @@ typedef struct {
   const int32_t* P;     /* host [nprob] 1..4                                   */
   const int32_t* bc;    /* host [nprob] ACAT_BC_*                              */
   const double* dx;     /* host [nprob] > 0                                    */
-  /* host [8] or NULL.  NULL: every order class in one persistent launch of
-   * 256-thread blocks, the grid shared among the classes by their work.  A
-   * table: one launch per order class p = 1..4 with the shape of entries
-   * 2(p-1) and 2(p-1)+1 = waves per block (1, 2 or 4; 0 = 4) and persistent
-   * blocks per CU (0 = the occupancy limit, else 1..32).  Every choice gives
-   * the same results bit for bit; the autotuner chooses by timing. */
+  /* host [8] or NULL.  NULL: the whole step in one launch of 256-thread
+   * blocks, one per tile of a problem.  A table: one launch per order class
+   * p = 1..4 with the shape of entries 2(p-1) and 2(p-1)+1 = waves per block
+   * (1, 2 or 4; 0 = 4) and persistent blocks per CU (0 = the occupancy limit,
+   * else 1..32).  Every choice gives the same results bit for bit; the
+   * autotuner chooses by timing. */
   const int32_t* launch;
 } acat_batch;
 

@@ -1,6 +1,6 @@
 """Autotuner of the batched step's launch shapes.
 
-By default the batched step runs every order class in one launch.  The
+By default the batched step is one launch over tiles of its problems.  The
 alternative is one launch per order class p, whose flux kernel's shape is a
 number of waves per block (1, 2 or 4: 64, 128 or 256 threads, i.e. 32p ...
 128/p interfaces per block round) and a number of persistent blocks per CU
@@ -37,7 +37,7 @@ def _time_classes(batch, u, dt, out, reps):
 def tune(batch, u: torch.Tensor, dt: torch.Tensor, reps: int = 5, waves=WAVES, per_cu=PER_CU,
          cache: str | None = None, verbose: bool = False) -> dict:
     """Choose and set the fastest launch: one launch per order class with the
-    fastest shape of each, or the default single launch of every class.
+    fastest shape of each, or the default single launch over tiles.
     Returns {p: (waves, blocks_per_cu, ms)}: ms the class kernel's time, or
     (0, 0, ms per step) for every p when the default launch is kept.  With
     `cache` (a JSON file) a choice stored for the same batch signature is
@@ -73,7 +73,7 @@ def tune(batch, u: torch.Tensor, dt: torch.Tensor, reps: int = 5, waves=WAVES, p
         print(f"[tune] graph-replayed step: tuned {t_tuned * 1e3:.1f} us, default {t_default * 1e3:.1f} us",
               flush=True)
     if not t_tuned < 0.98 * t_default:      # within 2 %: timing noise, keep the default
-        best = {p: (0, 0, t_default) for p in best}   # waves 0: the default single launch of every class
+        best = {p: (0, 0, t_default) for p in best}   # waves 0: the default single launch over tiles
         tuned = None
     batch.set_launch(tuned)
     if cache:

@@ -41,8 +41,10 @@ __global__ __launch_bounds__(BLOCK) void k_speed1d(KProb pb, const double* __res
 
 // Tiles of T cells.  CFL mode: from nparts partial maxima, or, with nparts =
 // 0, from the one tile that holds the whole problem.
+// Four waves per SIMD up to P = 5 (bounded to 128 registers there, 137
+// unbounded: 3e5 cells 218 -> 206 us per step), three at P = 6 (159).
 template <int FLUX, int NV, int P>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(P <= 4 ? 4 : 3))) void k_tile1d(
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(P <= 5 ? 4 : 3))) void k_tile1d(
     KProb pb, KStep st, int T, int nparts) {
   __shared__ TileMem<FLUX, NV, P> m;
   constexpr int G = TileMem<FLUX, NV, P>::G;
@@ -81,9 +83,13 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(P <= 4 ? 
 
 // Cells per tile: 4 GPW r - 1, whose interfaces are r rounds for each of the
 // block's four waves (GPW interfaces of order P per round).  A tile costs its
-// r rounds and about one more for staging, classification and update; with
-// fewer tiles than the chip holds at once one round each is the shortest,
-// with more the r whose last pass over the chip wastes least.
+// r rounds and 0.55 of one for staging, classification and update; the nb
+// tiles pass over the chip (`resident` blocks at once) nb / resident times
+// and half a pass more until the last ones end.  The r of the least
+// (nb / resident + 0.5) (r + 0.55) is within 2 % of the fastest measured r
+// (1, 2, 3, 4, 6, 8, 12) at orders 4 to 12 and 4e3 to 1e6 cells; e.g. P = 4:
+// 4096 cells r = 1 (15.8 us per step; r = 2 20.9), 65536 cells r = 2 (36.7;
+// r = 1 39.1, r = 4 47.3), P = 6, 1e6 cells r = 8 (961; r = 1 1449).
 template <int P>
 int tile_cells(int64_t n, int64_t resident) {
   constexpr int per = NWAVE * Groups<2 * P, 64>::PER_BLOCK, rmax = BLOCK / per;
@@ -91,7 +97,7 @@ int tile_cells(int64_t n, int64_t resident) {
   double cost = 1e300;
   for (int r = 1; r <= rmax; ++r) {
     const int64_t nb = (n + per * r - 2) / (per * r - 1);
-    const double c = (double)((nb + resident - 1) / resident) * (r + 1.0);
+    const double c = ((double)nb / (double)resident + 0.5) * (r + 0.55);
     if (c < cost) {
       cost = c;
       best = r;
