@@ -149,7 +149,7 @@ acat_status acat_step_cfl(const acat_problem* prob, const double* u_in, double* 
  * ACAT_NOALLOC_SCRATCH_BYTES in the library's static device memory, one per
  * GPU, held until the process ends.  The caller still owns u_in, u_out, the
  * optional decision maps and dt_dev; the call allocates and frees nothing.
- *   - ACAT_ERR_WORKSPACE when acat_workspace_size(prob) exceeds
+ *   - ACAT_ERR_WORKSPACE when acat_workspace_size(prob), 8 KiB of counters aside, exceeds
  *     ACAT_NOALLOC_SCRATCH_BYTES (64 MiB: e.g. 2D Euler up to about 800^2
  *     cells, 1D Euler up to about 1.4 million cells); other errors as
  *     acat_step.

@@ -86,8 +86,11 @@ KProb make_kprob(const acat_problem* p) {
 //   offs          int32[MAX_CLASSES][tiles + 1]
 //   list          int32[items]
 //   part          double[tiles][dim] partial wave-speed maxima (acat_step_cfl)
+//   tickets       int32[MAX_CLASSES][NXCD][TICKET_STRIDE]
+constexpr size_t TICKET_BYTES = sizeof(int32_t) * MAX_CLASSES * NXCD * TICKET_STRIDE;
+static_assert(TICKET_BYTES % ALIGN == 0, "the last part keeps the total aligned");
 struct Layout {
-  size_t hdr, ordx, ordy, psix, psiy, alx, aly, Fx, Gy, cls, hist, offs, list, part, total;
+  size_t hdr, ordx, ordy, psix, psiy, alx, aly, Fx, Gy, cls, hist, offs, list, part, tickets, total;
   int64_t nItems;
 };
 
@@ -113,6 +116,7 @@ Layout layout(const KProb& k) {
   // a corner with q1 != q2 has two entries under the square-stencil variant
   L.list = o;  o += align_up(sizeof(int32_t) * (size_t)L.nItems * ((k.flags & FLAG_SQUARE_2D) ? 2 : 1));
   L.part = o;  o += align_up(sizeof(double) * 2 * (size_t)cblocks);
+  L.tickets = o;  o += TICKET_BYTES;
   L.total = o;
   return L;
 }
@@ -135,7 +139,10 @@ uint32_t* status_ptr() {
 // Workspace of acat_step_noalloc: one fixed array per device, in the
 // library's own static memory, held until the process ends.  Host code uses
 // the device address obtained from the runtime, never the array's name.
-__device__ __align__(256) unsigned char scratch[ACAT_NOALLOC_SCRATCH_BYTES];
+// The ticket counters lie beyond the documented size: they do not count
+// against it.
+constexpr size_t SCRATCH_BYTES = ACAT_NOALLOC_SCRATCH_BYTES + TICKET_BYTES;
+__device__ __align__(256) unsigned char scratch[SCRATCH_BYTES];
 
 void* noalloc_scratch_ptr() {
   static std::atomic<void*> ptrs[64] = {};
@@ -201,6 +208,7 @@ acat_status do_step(const acat_problem* prob, const double* u_in, double* u_out,
   st.hist = reinterpret_cast<int32_t*>(w + L.hist);
   st.offs = reinterpret_cast<int32_t*>(w + L.offs);
   st.list = reinterpret_cast<int32_t*>(w + L.list);
+  st.tickets = reinterpret_cast<int32_t*>(w + L.tickets);
   st.status = status_ptr();
   if (!st.status) return ACAT_ERR_DEVICE;
   st.replay = replay ? 1 : 0;
@@ -403,10 +411,10 @@ acat_status acat_step_noalloc(const acat_problem* prob, const double* u_in, doub
                               const double* dt_dev, const acat_decisions* dec, void* stream) {
   acat_status rc = check_problem(prob);
   if (rc != ACAT_OK) return rc;
-  if (layout(make_kprob(prob)).total > ACAT_NOALLOC_SCRATCH_BYTES) return ACAT_ERR_WORKSPACE;
+  if (layout(make_kprob(prob)).total > SCRATCH_BYTES) return ACAT_ERR_WORKSPACE;
   void* ws = noalloc_scratch_ptr();
   if (!ws) return ACAT_ERR_DEVICE;
-  return do_step(prob, u_in, u_out, dt, dt_dev, ws, ACAT_NOALLOC_SCRATCH_BYTES, dec, false, stream);
+  return do_step(prob, u_in, u_out, dt, dt_dev, ws, SCRATCH_BYTES, dec, false, stream);
 }
 
 acat_status acat_step_cfl(const acat_problem* prob, const double* u_in, double* u_out, double cfl, double t_final,

@@ -13,6 +13,8 @@ namespace acat {
 
 constexpr int BLOCK = 256;        // threads per block of every step kernel
 constexpr int MAX_CLASSES = 16;   // order classes: P in 1D, P*P in 2D
+constexpr int NXCD = 8;           // MI355X: 8 accelerator complex dies, each with its own L2
+constexpr int TICKET_STRIDE = 16; // int32 from one ticket counter to the next (64 bytes)
 constexpr int BATCH_PMAX = 4;     // largest half-width of a batched problem
 
 // Problem geometry and parameters as the kernels see them.
@@ -61,6 +63,7 @@ struct KStep {
   int32_t* offs;          // per-class exclusive prefix of hist over tiles [MAX_CLASSES][tiles + 1]
   int32_t* counts;        // [MAX_CLASSES] items per order class
   int32_t* list;          // item ids grouped by class, tile order within a class [items]
+  int32_t* tickets;       // [MAX_CLASSES][NXCD][TICKET_STRIDE] chunk counters of the flux kernels (one used of each 16)
   uint32_t* status;       // device status bits
   int replay;             // decisions given in ord/psi/al
   // CFL mode: the classification also reduces the cells' spectral radii into

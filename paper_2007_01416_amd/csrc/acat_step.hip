@@ -424,23 +424,28 @@ constexpr int corner_stride() {
   return Groups<L>::TOTAL * corner_group_stride<L>();
 }
 
+// The classes (2, 3), (3, 2) and those of order 4 run two blocks per CU, the
+// others three.
+template <int Q1, int Q2>
+using CornerChunks = Chunks<Groups<4 * Q1 * Q2>::PER_BLOCK, (Q1 == 4 || Q2 == 4 || Q1 + Q2 == 5)>;
+
 // Fluxes of the corners of order class (Q1, Q2) (Sec. 4; rectangle J_Q1 x J_Q2)
-// in the block's share `sl` of the class list; every class but (1,1), which
+// in the chunks `ck` of the class list; every class but (1,1), which
 // runs one lane per corner (k_flux2d_q11).  SQUARE: list entries carry
 // the square-stencil variant's tags (square classes only).  xsm: the two
 // exchange buffers (2 Xch<NV>::NP corner_stride<L>() double2), g1s: the
 // derivative weights ((2 Q1)^2 + (2 Q2)^2 doubles), both in LDS.
 template <int FLUX, int NV, int Q1, int Q2, bool SQUARE>
-__device__ __forceinline__ void flux2d_body(const KProb& pb, const KStep& st, const Slice& sl, double2* xsm,
-                                            double* g1s) {
+__device__ __forceinline__ void flux2d_body(const KProb& pb, const KStep& st, CornerChunks<Q1, Q2> ck,
+                                            double2* xsm, double* g1s) {
   static_assert(Q1 > 1 || Q2 > 1, "class (1,1) runs in k_flux2d_q11");
   constexpr int N1 = 2 * Q1, N2 = 2 * Q2, L = N1 * N2;
   using Grp = Groups<L>;
-  constexpr int CPB = Grp::PER_BLOCK;
   constexpr int NP = Xch<NV>::NP;
   constexpr int STRIDE = corner_stride<L>();
   constexpr int GS = corner_group_stride<L>();
   double2* const xs[2] = {xsm, xsm + NP * STRIDE};
+  __shared__ int32_t sh_ticket[2];
 
   const int tid = threadIdx.x;
   const Grp grp(tid);
@@ -465,10 +470,10 @@ __device__ __forceinline__ void flux2d_body(const KProb& pb, const KStep& st, co
   const double* g1y = g1s + N1 * N1 + a2 * N2;
 
   int buf = 0;
-  for (int64_t base = sl.lo; base < sl.hi; base += CPB) {
+  for (; ck.base < ck.end; ck.advance(sh_ticket)) {
     {
-      const bool valid = inblk && base + g < sl.hi;
-      const int32_t raw = valid ? sl.items[base + g] : 0;
+      const bool valid = inblk && ck.base + g < ck.end;
+      const int32_t raw = valid ? ck.items[ck.base + g] : 0;
       // square-stencil variant: entries carry which flux to store (1 F, 2 G, 0 both)
       const int32_t e = SQUARE ? (raw & ((1 << LIST_TAG_SHIFT) - 1)) : raw;
       const int tag = SQUARE ? (raw >> LIST_TAG_SHIFT) : 0;
@@ -567,11 +572,13 @@ __device__ __forceinline__ void flux2d_body(const KProb& pb, const KStep& st, co
 
 
 template <int FLUX, int NV, int Q1, int Q2, bool SQUARE = false>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(2))) void k_flux2d(KProb pb, KStep st) {
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(Q1 <= 3 ? 3 : 2))) void k_flux2d(
+    KProb pb, KStep st) {
   constexpr int L = (2 * Q1) * (2 * Q2);
   __shared__ double2 xsm[2 * Xch<NV>::NP * corner_stride<L>()];
   __shared__ double g1s[(2 * Q1) * (2 * Q1) + (2 * Q2) * (2 * Q2)];
-  flux2d_body<FLUX, NV, Q1, Q2, SQUARE>(pb, st, Slice(st.counts, st.list, (Q1 - 1) * pb.P + (Q2 - 1)), xsm, g1s);
+  flux2d_body<FLUX, NV, Q1, Q2, SQUARE>(
+      pb, st, CornerChunks<Q1, Q2>(st, (Q1 - 1) * pb.P + (Q2 - 1), blockIdx.x, gridDim.x), xsm, g1s);
 }
 
 // Order class (1,1) with ONE LANE PER CORNER.  The corner's four nodes
@@ -693,7 +700,7 @@ __global__ __launch_bounds__(BLOCK) void k_flux2d_q11(KProb pb, KStep st) {
 // list.  Both classes have the same corner size and the same work per
 // corner; per corner the arithmetic is that of the one-class launch.
 template <int FLUX, int NV, int QA, int QB>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(2))) void k_flux2d_pair(KProb pb, KStep st) {
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(QA == 1 && QB == 3 ? 3 : 2))) void k_flux2d_pair(KProb pb, KStep st) {
   constexpr int L = (2 * QA) * (2 * QB);
   __shared__ double2 xsm[2 * Xch<NV>::NP * corner_stride<L>()];
   __shared__ double g1s[(2 * QA) * (2 * QA) + (2 * QB) * (2 * QB)];
@@ -703,13 +710,11 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(2))) void
   const int units = (int)gridDim.x / NXCD;
   const int ua = na == 0 ? 0 : (nb == 0 ? units : 1 + (int)((int64_t)(units - 2) * na / (na + nb)));
   const int unit = (int)blockIdx.x / NXCD;
-  if (unit < ua) {
-    flux2d_body<FLUX, NV, QA, QB, false>(pb, st, Slice(st.counts, st.list, ca, blockIdx.x, ua * NXCD), xsm, g1s);
-  } else {
-    const int ub = units - ua;
-    flux2d_body<FLUX, NV, QB, QA, false>(pb, st, Slice(st.counts, st.list, cb, blockIdx.x - ua * NXCD, ub * NXCD),
-                                         xsm, g1s);
-  }
+  if (unit < ua)
+    flux2d_body<FLUX, NV, QA, QB, false>(pb, st, CornerChunks<QA, QB>(st, ca, blockIdx.x, ua * NXCD), xsm, g1s);
+  else
+    flux2d_body<FLUX, NV, QB, QA, false>(
+        pb, st, CornerChunks<QB, QA>(st, cb, blockIdx.x - ua * NXCD, (units - ua) * NXCD), xsm, g1s);
 }
 
 template <int FLUX, int NV>
@@ -917,7 +922,7 @@ hipError_t lists2d_impl(const KProb& pb, const KStep& st, hipStream_t s) {
   {
     ProfScope ps("class_lists", s);
     k_scan_hist<<<P * P + (st.cfl_mode ? 1 : 0), SCAN_T, 0, s>>>(st.hist, cblocks, st.offs, st.counts, P * P,
-                                                                cfl_reduce(pb, st, cblocks));
+                                                                cfl_reduce(pb, st, cblocks), st.tickets);
     if (pb.flags & FLAG_SQUARE_2D)
       k_scatter<P * P, true, true><<<cblocks, BLOCK, 0, s>>>(st.cls, 0, pb.n1, pb.n2, cblocks, st.offs, st.counts,
                                                               st.list, P);

@@ -11,7 +11,6 @@ namespace acat {
 namespace {
 
 constexpr CoeffTables TB = make_tables();
-constexpr int NXCD = 8;   // MI355X: 8 accelerator complex dies, each with its own L2
 
 // ---------------------------------------------------------------- helpers
 // Quotients below use div_rn (physics.hpp): the indicator's operands are sums
@@ -217,10 +216,11 @@ constexpr int SCAN_T = 1024;   // threads of the class-list prefix kernel
 
 // offs[c][t] = items of class c in tiles < t, counts[c] = total: one block per
 // class, each thread summing a contiguous chunk of tiles, then a block-wide
-// exclusive scan of the chunk sums.  With cr.part, block ncls reduces the
+// exclusive scan of the chunk sums; and the class's tickets cleared.  With cr.part, block ncls reduces the
 // partial maxima and writes the CFL time step.
 __global__ __launch_bounds__(SCAN_T) void k_scan_hist(const int32_t* hist, int ntiles, int32_t* offs,
-                                                      int32_t* counts, int ncls, CflReduce cr) {
+                                                      int32_t* counts, int ncls, CflReduce cr,
+                                                      int32_t* tickets = nullptr) {
   __shared__ int wsum[SCAN_T / 64];
   __shared__ double wmax[2][SCAN_T / 64];
   const int c = blockIdx.x, tid = threadIdx.x, lane = __lane_id(), wid = tid >> 6;
@@ -249,6 +249,7 @@ __global__ __launch_bounds__(SCAN_T) void k_scan_hist(const int32_t* hist, int n
     }
     return;
   }
+  if (tickets && tid < NXCD) tickets[(c * NXCD + tid) * TICKET_STRIDE] = 0;
   const int per = (ntiles + SCAN_T - 1) / SCAN_T;
   const int t0 = tid * per;
   const int t1 = min(t0 + per, ntiles);
@@ -436,6 +437,78 @@ struct Groups {
     } else {
       __syncthreads();
     }
+  }
+};
+
+// v, the same in every lane of the wave, in a scalar register
+template <class T>
+__device__ __forceinline__ T wave_uniform(T v) {
+  return __builtin_amdgcn_readfirstlane(v);
+}
+
+// A persistent block's share of one class list, in rounds of PER_ROUND items.
+// The list is cut into one contiguous region per XCD (neighbouring items share
+// that XCD's L2), and a region into chunks of an eighth of a block's mean share
+// (1 to 8 rounds): block j takes the j-th, and draws further ones from the
+// region's ticket (drawn when a chunk starts, read when it ends).
+// With equal shares alone the oldest block of a CU, which wins every issue slot
+// it asks for, ended after half the kernel's time, and the CU drained to two
+// blocks, then to one: 2D Euler 2048^2, class (3, 3) 7370 us per launch, with
+// tickets 6570; class (4, 4) of 1021 x 777 corners 3410 and 3200.  Kernels of
+// two blocks per CU (PAIRED) drain less, and with 2 to 11 rounds per block take
+// equal shares: class (3, 4), 8 rounds, 222 us and 231 by tickets, class (1, 4)
+// 75 and 79; with three per CU tickets win there too (class (1, 3), 6 rounds,
+// 82 us in equal shares and 78, class (2, 2) of 400^2 corners 42 and 40.5).
+// One ticket per wave instead of per block made that class (2, 2) 65 us: draws
+// from one counter take about 20 ns each.
+template <int PER_ROUND, bool PAIRED>
+struct Chunks {
+  const int32_t* items;     // of the region
+  int base, end, len;       // the current chunk; the region's items
+  int step, nb, drawn, phase;
+  int32_t* ticket;
+  bool more;                // chunks are left beyond the blocks' first ones
+  // block `blk` of `nblk` (a multiple of NXCD) on class c
+  __device__ __forceinline__ Chunks(const KStep& st, int c, int blk, int nblk) {
+    int64_t first = 0;
+    for (int k = 0; k < c; ++k) first += st.counts[k];
+    const int64_t n = st.counts[c];
+    const int x = blk % NXCD, j = blk / NXCD;
+    nb = nblk / NXCD;
+    const int64_t lo = n * x / NXCD;
+    items = st.list + first + lo;
+    len = (int)(n * (x + 1) / NXCD - lo);
+    ticket = st.tickets + (c * NXCD + x) * TICKET_STRIDE;
+    phase = 0;
+    const int rounds = len / (PER_ROUND * nb);
+    if (PAIRED && rounds >= 2 && rounds < 12) {
+      base = (int)((int64_t)len * j / nb);
+      end = (int)((int64_t)len * (j + 1) / nb);
+      more = false;
+      step = drawn = 0;
+      return;
+    }
+    step = PER_ROUND * (rounds < 16 ? 1 : rounds >= 64 ? 8 : rounds / 8);
+    more = nb * step < len;
+    start(j);
+  }
+  __device__ __forceinline__ void start(int chunk) {
+    const int64_t at = (int64_t)chunk * step;
+    base = at < len ? (int)at : len;
+    end = len - base < step ? len : base + step;
+    drawn = 0;
+    if (more && base < end && threadIdx.x == 0) drawn = atomicAdd(ticket, 1);
+  }
+  // after a round: the next one, of the next chunk where this one is done.
+  // sh: two ints of LDS, used in turn so that one barrier per chunk suffices.
+  __device__ __forceinline__ void advance(int32_t* sh) {
+    base += PER_ROUND;
+    if (base < end || !more) return;
+    if (threadIdx.x == 0) sh[phase] = drawn;
+    __syncthreads();
+    const int t = wave_uniform(sh[phase]);
+    phase ^= 1;
+    start(nb + t);
   }
 };
 
