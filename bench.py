@@ -526,7 +526,8 @@ def bench_high_order(acat, workloads, F, steps=20, warmup=3, n1d=1 << 22, n2d=20
         # one kernel runs every order (and the classification and update): the fluxes' flops alone
         c, ms = prof["step1d"]
         fl = sum(int(per[p - 1]) * F.interface_flops_1d(p, 3, F.C_F[("euler", 1)]) for p in range(1, P + 1))
-        kern = {"step1d": {"avg_us": round(1e3 * ms / c, 2), "items": {f"p{p}": int(per[p - 1]) for p in range(1, P + 1)},
+        kern = {"step1d": {"avg_us": round(1e3 * ms / c, 2),
+                           "items": {f"p{p}": int(per[p - 1]) for p in range(1, P + 1)},
                            "frac": round(fl / (ms * 1e-3) / 1e12 / PEAK_FP64_TFLOPS, 4)}}
         out[f"euler1d_P{P}_n{n1d}"] = {"value": n1d * steps / el, "unit": "cell-updates/s",
                                        "ms_per_step": 1e3 * el / steps, "kernels": kern,

@@ -13,10 +13,10 @@
 //                  per-block maxima)
 //   k_scatter      the item lists: every class's items in tile order
 //                  (wave ballots, no global atomics)
-//   k_flux*<class> persistent kernels, one per order class (2D: one per
-//                  square class and one per mirror pair (q1,q2) + (q2,q1)).
-//                  A block takes a contiguous slice of its class's list and
-//                  processes it in rounds with one LANE PER STENCIL NODE: a
+//   k_flux1d<p>    persistent kernels, 1D: one per order class, each block a
+//   k_flux2d       contiguous slice of its class's list; 2D: one or two for
+//                  all classes, whose blocks draw chunks of the class lists.
+//                  A list is processed in rounds, one LANE PER STENCIL NODE: a
 //                  1D interface of order p occupies 2p lanes, a 2D corner of
 //                  orders (q1, q2) 2q1 x 2q2 lanes.  Each lane keeps its
 //                  node's state and Taylor predictions in registers and
@@ -26,6 +26,7 @@
 //   k_update*      conservative flux-difference update + status bits
 #include <hip/hip_runtime.h>
 
+#include <string>
 #include <utility>
 
 #include "acat_internal.hpp"
@@ -424,56 +425,48 @@ constexpr int corner_stride() {
   return Groups<L>::TOTAL * corner_group_stride<L>();
 }
 
-// The classes (2, 3), (3, 2) and those of order 4 run two blocks per CU, the
-// others three.
-template <int Q1, int Q2>
-using CornerChunks = Chunks<Groups<4 * Q1 * Q2>::PER_BLOCK, (Q1 == 4 || Q2 == 4 || Q1 + Q2 == 5)>;
+// First-derivative weights of every half-width up to 4 times -lamx (rows) and
+// -lamy (columns), in LDS: node a, weight l of half-width q at first(q) + 2 q a + l.
+struct EdgeWeights {
+  static constexpr int first(int q) { return 4 * ((q - 1) * q * (2 * q - 1) / 6); }   // 4 sum_{k<q} k^2
+};
 
-// Fluxes of the corners of order class (Q1, Q2) (Sec. 4; rectangle J_Q1 x J_Q2)
-// in the chunks `ck` of the class list; every class but (1,1), which
-// runs one lane per corner (k_flux2d_q11).  SQUARE: list entries carry
-// the square-stencil variant's tags (square classes only).  xsm: the two
-// exchange buffers (2 Xch<NV>::NP corner_stride<L>() double2), g1s: the
-// derivative weights ((2 Q1)^2 + (2 Q2)^2 doubles), both in LDS.
+// Fluxes of the corners of order class (Q1, Q2) (Sec. 4; rectangle J_Q1 x J_Q2),
+// items [base, end) of the list; every class but (1,1), which runs one lane
+// per corner (flux2d_q11).  SQUARE: list entries carry the square-stencil
+// variant's tags (square classes only).  xsm: the two exchange buffers
+// (2 Xch<NV>::NP corner_stride<L>() double2), gxs, gys: the derivative weights
+// (EdgeWeights), in LDS.
 template <int FLUX, int NV, int Q1, int Q2, bool SQUARE>
-__device__ __forceinline__ void flux2d_body(const KProb& pb, const KStep& st, CornerChunks<Q1, Q2> ck,
-                                            double2* xsm, double* g1s) {
-  static_assert(Q1 > 1 || Q2 > 1, "class (1,1) runs in k_flux2d_q11");
+__device__ __forceinline__ void flux2d_body(const KProb& pb, const KStep& st, int tid, double dt,
+                                            const int32_t* items, int base, int end, double2* xsm, const double* gxs,
+                                            const double* gys) {
+  static_assert(Q1 > 1 || Q2 > 1, "class (1,1) runs in flux2d_q11");
   constexpr int N1 = 2 * Q1, N2 = 2 * Q2, L = N1 * N2;
   using Grp = Groups<L>;
   constexpr int NP = Xch<NV>::NP;
   constexpr int STRIDE = corner_stride<L>();
   constexpr int GS = corner_group_stride<L>();
   double2* const xs[2] = {xsm, xsm + NP * STRIDE};
-  __shared__ int32_t sh_ticket[2];
 
-  const int tid = threadIdx.x;
   const Grp grp(tid);
   const int g = grp.g;
   const int nd = grp.node;
   const int a1 = nd % N1, a2 = nd / N1;     // node (j1, j2) = (a1 - Q1 + 1, a2 - Q2 + 1)
   const bool inblk = grp.in;
-  const double dt = step_dt(st);
-  const double lamx = dt / pb.dx, lamy = dt / pb.dy;
   const int64_t nx = pb.nx, ny = pb.ny, plane = pb.nx * pb.ny;
   const int nx32 = (int)pb.nx, ny32 = (int)pb.ny, ioff = (int)pb.ioff;
   const uint32_t n1u = (uint32_t)pb.n1;
-
-  // derivative weights times -lamx (rows) and -lamy (columns), in LDS (the
-  // corner pass holds a node's row weights in registers and reads its column
-  // weights at each use)
-  for (int i = tid; i < N1 * N1 + N2 * N2; i += BLOCK)
-    g1s[i] = i < N1 * N1 ? -lamx * TB.G1[Q1][i / N1][i % N1]
-                         : -lamy * TB.G1[Q2][(i - N1 * N1) / N2][(i - N1 * N1) % N2];
-  __syncthreads();
-  const double* g1x = g1s + a1 * N1;
-  const double* g1y = g1s + N1 * N1 + a2 * N2;
+  // the corner pass holds a node's row weights in registers and reads its
+  // column weights at each use
+  const double* g1x = gxs + EdgeWeights::first(Q1) + a1 * N1;
+  const double* g1y = gys + EdgeWeights::first(Q2) + a2 * N2;
 
   int buf = 0;
-  for (; ck.base < ck.end; ck.advance(sh_ticket)) {
+  for (; base < end; base += Grp::PER_BLOCK) {
     {
-      const bool valid = inblk && ck.base + g < ck.end;
-      const int32_t raw = valid ? ck.items[ck.base + g] : 0;
+      const bool valid = inblk && base + g < end;
+      const int32_t raw = valid ? items[base + g] : 0;
       // square-stencil variant: entries carry which flux to store (1 F, 2 G, 0 both)
       const int32_t e = SQUARE ? (raw & ((1 << LIST_TAG_SHIFT) - 1)) : raw;
       const int tag = SQUARE ? (raw >> LIST_TAG_SHIFT) : 0;
@@ -571,16 +564,6 @@ __device__ __forceinline__ void flux2d_body(const KProb& pb, const KStep& st, Co
 }
 
 
-template <int FLUX, int NV, int Q1, int Q2, bool SQUARE = false>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(Q1 <= 3 ? 3 : 2))) void k_flux2d(
-    KProb pb, KStep st) {
-  constexpr int L = (2 * Q1) * (2 * Q2);
-  __shared__ double2 xsm[2 * Xch<NV>::NP * corner_stride<L>()];
-  __shared__ double g1s[(2 * Q1) * (2 * Q1) + (2 * Q2) * (2 * Q2)];
-  flux2d_body<FLUX, NV, Q1, Q2, SQUARE>(
-      pb, st, CornerChunks<Q1, Q2>(st, (Q1 - 1) * pb.P + (Q2 - 1), blockIdx.x, gridDim.x), xsm, g1s);
-}
-
 // Order class (1,1) with ONE LANE PER CORNER.  The corner's four nodes
 // (j1, j2) in {0,1}^2 (cells (i1 + j1, i2 + j2)) live in one lane, which
 // computes, with the same operations in the same order as the node-per-lane
@@ -590,9 +573,9 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(Q1 <= 3 ?
 // Taylor predictions, the series of F on the row and of G on the column,
 // the eta-weighted sums and the FL-CAT2 blends.  No LDS exchange and no
 // barrier; a wavefront holds 64 independent corners.
-template <int FLUX, int NV, bool SQUARE = false>
-__global__ __launch_bounds__(BLOCK) void k_flux2d_q11(KProb pb, KStep st) {
-  const double dt = step_dt(st);
+template <int FLUX, int NV, bool SQUARE>
+__device__ __forceinline__ void flux2d_q11(const KProb& pb, const KStep& st, int tid, double dt, const int32_t* items,
+                                           int base, int end) {
   const double lamx = dt / pb.dx, lamy = dt / pb.dy;
   // derivative weights times -lamx (x) and -lamy (y): gx[a][l], gy[a][l]
   double gx[2][2], gy[2][2];
@@ -608,9 +591,8 @@ __global__ __launch_bounds__(BLOCK) void k_flux2d_q11(KProb pb, KStep st) {
   const int64_t nx = pb.nx, ny = pb.ny, plane = pb.nx * pb.ny;
   const int nx32 = (int)pb.nx, ny32 = (int)pb.ny, ioff = (int)pb.ioff;
   const uint32_t n1u = (uint32_t)pb.n1;
-  const Slice sl(st.counts, st.list, 0);
-  for (int64_t it = sl.lo + threadIdx.x; it < sl.hi; it += BLOCK) {
-    const int32_t raw = sl.items[it];
+  for (int it = base + tid; it < end; it += BLOCK) {
+    const int32_t raw = items[it];
     const int32_t e = SQUARE ? (raw & ((1 << LIST_TAG_SHIFT) - 1)) : raw;
     const int tag = SQUARE ? (raw >> LIST_TAG_SHIFT) : 0;
     const uint32_t eq = (uint32_t)e / n1u;
@@ -693,28 +675,135 @@ __global__ __launch_bounds__(BLOCK) void k_flux2d_q11(KProb pb, KStep st) {
   }
 }
 
-// The mirror classes (QA, QB) and (QB, QA), QA < QB, in one launch: the grid
-// is cut into two runs of whole XCD groups of blocks, sized by the two
-// classes' corner counts (at least one group for a class with corners),
-// each block running its class's kernel body over its share of that class's
-// list.  Both classes have the same corner size and the same work per
-// corner; per corner the arithmetic is that of the one-class launch.
-template <int FLUX, int NV, int QA, int QB>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(QA == 1 && QB == 3 ? 3 : 2))) void k_flux2d_pair(KProb pb, KStep st) {
-  constexpr int L = (2 * QA) * (2 * QB);
-  __shared__ double2 xsm[2 * Xch<NV>::NP * corner_stride<L>()];
-  __shared__ double g1s[(2 * QA) * (2 * QA) + (2 * QB) * (2 * QB)];
-  const int ca = (QA - 1) * pb.P + (QB - 1), cb = (QB - 1) * pb.P + (QA - 1);
-  const int64_t na = st.counts[ca], nb = st.counts[cb];
-  if (na + nb == 0) return;
-  const int units = (int)gridDim.x / NXCD;
-  const int ua = na == 0 ? 0 : (nb == 0 ? units : 1 + (int)((int64_t)(units - 2) * na / (na + nb)));
-  const int unit = (int)blockIdx.x / NXCD;
-  if (unit < ua)
-    flux2d_body<FLUX, NV, QA, QB, false>(pb, st, CornerChunks<QA, QB>(st, ca, blockIdx.x, ua * NXCD), xsm, g1s);
-  else
-    flux2d_body<FLUX, NV, QB, QA, false>(
-        pb, st, CornerChunks<QB, QA>(st, cb, blockIdx.x - ua * NXCD, (units - ua) * NXCD), xsm, g1s);
+// The order classes of a 2D step in one or two launches, by the blocks that
+// fit a CU at their register need: three (FEW false: orders up to 3 but (2, 3)
+// and (3, 2); up to 168 registers per lane), or two (those two and the classes
+// with an order 4; up to 256).  All the classes of a launch share its blocks
+// (Chunks), so that a small grid's classes run side by side and a large one's
+// leave no tails.  The costliest class comes first.  Against one launch per
+// class or mirror pair, a step of 64^2 corners at P = 3 34.3 -> 27.7 us, 192^2
+// 74.6 -> 59.0, 400^2 at P = 2 79.7 -> 71.7, 1000^2 at P = 3 1213 -> 1180, 2048^2
+// 6401 -> 6407 (the gain of the tails is spent on registers: 12 spilled of the
+// 168 that three blocks per CU allow), 1021 x 777 at P = 4 3222 -> 3169.
+struct Cls {
+  int q1, q2;
+};
+template <int P, bool FEW, bool SQUARE>
+struct ClassSet {
+  static constexpr Cls ALL[MAX_CLASSES] = {{4, 4}, {3, 4}, {4, 3}, {2, 4}, {4, 2}, {1, 4}, {4, 1}, {2, 3},
+                                           {3, 2}, {3, 3}, {1, 3}, {3, 1}, {2, 2}, {1, 2}, {2, 1}, {1, 1}};
+  static constexpr bool few(Cls c) { return c.q1 == 4 || c.q2 == 4 || c.q1 + c.q2 == 5; }
+  static constexpr bool has(Cls c) {
+    return c.q1 <= P && c.q2 <= P && few(c) == FEW && (!SQUARE || c.q1 == c.q2);
+  }
+  static constexpr int count() {
+    int n = 0;
+    for (Cls c : ALL) n += has(c);
+    return n;
+  }
+  static constexpr int N = count();
+  static constexpr Cls at(int k) {
+    for (Cls c : ALL)
+      if (has(c) && k-- == 0) return c;
+    return {1, 1};
+  }
+  static constexpr int per_round(Cls c) {
+    switch (4 * c.q1 * c.q2) {
+      case 4: return BLOCK;
+      case 8: return Groups<8>::PER_BLOCK;
+      case 12: return Groups<12>::PER_BLOCK;
+      case 16: return Groups<16>::PER_BLOCK;
+      case 24: return Groups<24>::PER_BLOCK;
+      case 32: return Groups<32>::PER_BLOCK;
+      case 36: return Groups<36>::PER_BLOCK;
+      case 48: return Groups<48>::PER_BLOCK;
+      default: return Groups<64>::PER_BLOCK;
+    }
+  }
+  static constexpr int stride(Cls c) {
+    switch (4 * c.q1 * c.q2) {
+      case 4: return 0;
+      case 8: return corner_stride<8>();
+      case 12: return corner_stride<12>();
+      case 16: return corner_stride<16>();
+      case 24: return corner_stride<24>();
+      case 32: return corner_stride<32>();
+      case 36: return corner_stride<36>();
+      case 48: return corner_stride<48>();
+      default: return corner_stride<64>();
+    }
+  }
+  static constexpr int max_stride() {
+    int m = 1;
+    for (int k = 0; k < N; ++k) m = stride(at(k)) > m ? stride(at(k)) : m;
+    return m;
+  }
+  static constexpr int min_per_round() {
+    int m = BLOCK;
+    for (int k = 0; k < N; ++k) m = per_round(at(k)) < m ? per_round(at(k)) : m;
+    return m;
+  }
+};
+
+template <int FLUX, int NV, int P, bool FEW, bool SQUARE>
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(FEW ? 2 : 3))) void k_flux2d(KProb pb,
+                                                                                                  KStep st) {
+  using Set = ClassSet<P, FEW, SQUARE>;
+  __shared__ double2 xsm[2 * Xch<NV>::NP * Set::max_stride()];
+  __shared__ double gxs[EdgeWeights::first(P + 1)], gys[EdgeWeights::first(P + 1)];
+  __shared__ ChunkTable tab;
+  const double dt = step_dt(st);
+  for (int q = 1; q <= P; ++q) {
+    const double lamx = dt / pb.dx, lamy = dt / pb.dy;
+    for (int i = threadIdx.x; i < 4 * q * q; i += BLOCK) {
+      const double w = TB.G1[q][i / (2 * q)][i % (2 * q)];
+      gxs[EdgeWeights::first(q) + i] = -lamx * w;
+      gys[EdgeWeights::first(q) + i] = -lamy * w;
+    }
+  }
+  constexpr auto sets = [] {
+    struct {
+      int cls[MAX_CLASSES], per_round[MAX_CLASSES];
+    } t{};
+    for (int k = 0; k < Set::N; ++k) {
+      t.cls[k] = (Set::at(k).q1 - 1) * P + Set::at(k).q2 - 1;
+      t.per_round[k] = Set::per_round(Set::at(k));
+    }
+    return t;
+  }();
+  Chunks<Set::N> ck(st, tab, FEW ? 1 : 0, blockIdx.x, gridDim.x, [&](int k, int& c, int& per_round) {
+    c = sets.cls[k];
+    per_round = sets.per_round[k];
+  });
+  auto run = [&](auto kc) {
+    constexpr int k = decltype(kc)::value;
+    if constexpr (k < Set::N) {
+      constexpr Cls c = Set::at(k);
+      // what a class derives from its lane's number and the time step is
+      // computed at each chunk: kept for all classes at once it would spill
+      int tid = threadIdx.x;
+      double h = dt;
+      asm volatile("" : "+v"(tid), "+v"(h));
+      if constexpr (c.q1 == 1 && c.q2 == 1)
+        flux2d_q11<FLUX, NV, SQUARE>(pb, st, tid, h, ck.items, ck.base, ck.end);
+      else
+        flux2d_body<FLUX, NV, c.q1, c.q2, SQUARE>(pb, st, tid, h, ck.items, ck.base, ck.end, xsm, gxs, gys);
+    }
+  };
+  while (ck.start(st, tab)) {
+    switch (ck.cls) {
+      case 0: run(std::integral_constant<int, 0>{}); break;
+      case 1: run(std::integral_constant<int, 1>{}); break;
+      case 2: run(std::integral_constant<int, 2>{}); break;
+      case 3: run(std::integral_constant<int, 3>{}); break;
+      case 4: run(std::integral_constant<int, 4>{}); break;
+      case 5: run(std::integral_constant<int, 5>{}); break;
+      case 6: run(std::integral_constant<int, 6>{}); break;
+      case 7: run(std::integral_constant<int, 7>{}); break;
+      default: run(std::integral_constant<int, 8>{}); break;
+    }
+    ck.advance(tab);
+  }
 }
 
 template <int FLUX, int NV>
@@ -862,48 +951,26 @@ hipError_t step1d_impl(const KProb& pb, const KStep& st, int cap, hipStream_t s)
   return hipSuccess;
 }
 
-// A square class (Q, Q); the other classes run as mirror pairs (launch_pair2d).
-template <int FLUX, int NV, int P, int Q>
-hipError_t launch_class2d(const KProb& pb, const KStep& st, int cap, hipStream_t s) {
-  if constexpr (Q <= P) {
-    static const char* names[5] = {"", "flux2d_q11", "flux2d_q22", "flux2d_q33", "flux2d_q44"};
-    // under the square-stencil variant only the square classes have items,
-    // tagged with the flux they store
-    // (1,1): one lane per corner (k_flux2d_q11); the others one lane per node
-    const bool sq = (pb.flags & FLAG_SQUARE_2D) != 0;
-    void (*kern)(KProb, KStep);
-    int grid;
-    if constexpr (Q == 1) {
-      kern = sq ? k_flux2d_q11<FLUX, NV, true> : k_flux2d_q11<FLUX, NV>;
-      grid = persistent_grid(kern, pb.n1 * pb.n2, cap);
-    } else {
-      kern = sq ? k_flux2d<FLUX, NV, Q, Q, true> : k_flux2d<FLUX, NV, Q, Q>;
-      grid = group_grid<(2 * Q) * (2 * Q)>(kern, pb.n1 * pb.n2, cap);
-    }
+// The classes of one launch (ClassSet).
+template <int FLUX, int NV, int P, bool FEW, bool SQUARE>
+hipError_t launch_flux2d(const KProb& pb, const KStep& st, int cap, hipStream_t s) {
+  using Set = ClassSet<P, FEW, SQUARE>;
+  if constexpr (Set::N > 0) {
+    static const std::string name = [] {
+      std::string n = "flux2d_";
+      for (int k = 0; k < Set::N; ++k) n += "q" + std::to_string(10 * Set::at(k).q1 + Set::at(k).q2);
+      return n;
+    }();
+    auto kern = k_flux2d<FLUX, NV, P, FEW, SQUARE>;
+    static const int per_cu = [&] {
+      int b = 0;
+      return hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, kern, BLOCK, 0) == hipSuccess && b > 0 ? b : 1;
+    }();
+    // no more blocks than rounds, with one cut short per class and XCD
+    const int64_t rounds = pb.n1 * pb.n2 / Set::min_per_round() + NXCD * Set::N;
+    const int grid = persistent_grid(kern, rounds * BLOCK, cap, BLOCK, per_cu);
     {
-      ProfScope ps(names[Q], s);
-      kern<<<grid, BLOCK, 0, s>>>(pb, st);
-    }
-    ACAT_CHECK_LAUNCH();
-  }
-  return hipSuccess;
-}
-
-// The mirror classes (QA, QB) and (QB, QA), QA < QB, in one launch.
-template <int FLUX, int NV, int P, int QA, int QB>
-hipError_t launch_pair2d(const KProb& pb, const KStep& st, int cap, hipStream_t s) {
-  static_assert(QA < QB, "pairs are named by their lower-left class");
-  if constexpr (QB <= P) {
-    static const char* names[5][5] = {{"", "", "", "", ""},
-                                      {"", "", "flux2d_q12q21", "flux2d_q13q31", "flux2d_q14q41"},
-                                      {"", "", "", "flux2d_q23q32", "flux2d_q24q42"},
-                                      {"", "", "", "", "flux2d_q34q43"},
-                                      {"", "", "", "", ""}};
-    auto kern = k_flux2d_pair<FLUX, NV, QA, QB>;
-    // two runs of XCD groups: at least one per class
-    const int grid = std::max(group_grid<(2 * QA) * (2 * QB)>(kern, pb.n1 * pb.n2, cap), 2 * NXCD);
-    {
-      ProfScope ps(names[QA][QB], s);
+      ProfScope ps(name.c_str(), s);
       kern<<<grid, BLOCK, 0, s>>>(pb, st);
     }
     ACAT_CHECK_LAUNCH();
@@ -938,16 +1005,13 @@ template <int FLUX, int NV, int P>
 hipError_t step2d_impl(const KProb& pb, const KStep& st, int cap, hipStream_t s) {
   hipError_t e;
   if ((e = lists2d_impl<FLUX, NV, P>(pb, st, s)) != hipSuccess) return e;
-  if ((e = launch_class2d<FLUX, NV, P, 1>(pb, st, cap, s)) != hipSuccess) return e;
-  if ((e = launch_pair2d<FLUX, NV, P, 1, 2>(pb, st, cap, s)) != hipSuccess) return e;
-  if ((e = launch_class2d<FLUX, NV, P, 2>(pb, st, cap, s)) != hipSuccess) return e;
-  if ((e = launch_pair2d<FLUX, NV, P, 1, 3>(pb, st, cap, s)) != hipSuccess) return e;
-  if ((e = launch_pair2d<FLUX, NV, P, 2, 3>(pb, st, cap, s)) != hipSuccess) return e;
-  if ((e = launch_class2d<FLUX, NV, P, 3>(pb, st, cap, s)) != hipSuccess) return e;
-  if ((e = launch_pair2d<FLUX, NV, P, 1, 4>(pb, st, cap, s)) != hipSuccess) return e;
-  if ((e = launch_pair2d<FLUX, NV, P, 2, 4>(pb, st, cap, s)) != hipSuccess) return e;
-  if ((e = launch_pair2d<FLUX, NV, P, 3, 4>(pb, st, cap, s)) != hipSuccess) return e;
-  if ((e = launch_class2d<FLUX, NV, P, 4>(pb, st, cap, s)) != hipSuccess) return e;
+  if (pb.flags & FLAG_SQUARE_2D) {
+    if ((e = launch_flux2d<FLUX, NV, P, false, true>(pb, st, cap, s)) != hipSuccess) return e;
+    if ((e = launch_flux2d<FLUX, NV, P, true, true>(pb, st, cap, s)) != hipSuccess) return e;
+  } else {
+    if ((e = launch_flux2d<FLUX, NV, P, false, false>(pb, st, cap, s)) != hipSuccess) return e;
+    if ((e = launch_flux2d<FLUX, NV, P, true, false>(pb, st, cap, s)) != hipSuccess) return e;
+  }
   {
     ProfScope ps("update2d", s);
     k_update2d<FLUX, NV><<<(unsigned)((pb.nx * pb.ny + BLOCK - 1) / BLOCK), BLOCK, 0, s>>>(pb, st);

@@ -446,69 +446,90 @@ __device__ __forceinline__ T wave_uniform(T v) {
   return __builtin_amdgcn_readfirstlane(v);
 }
 
-// A persistent block's share of one class list, in rounds of PER_ROUND items.
-// The list is cut into one contiguous region per XCD (neighbouring items share
-// that XCD's L2), and a region into chunks of an eighth of a block's mean share
-// (1 to 8 rounds): block j takes the j-th, and draws further ones from the
-// region's ticket (drawn when a chunk starts, read when it ends).
-// With equal shares alone the oldest block of a CU, which wins every issue slot
-// it asks for, ended after half the kernel's time, and the CU drained to two
-// blocks, then to one: 2D Euler 2048^2, class (3, 3) 7370 us per launch, with
-// tickets 6570; class (4, 4) of 1021 x 777 corners 3410 and 3200.  Kernels of
-// two blocks per CU (PAIRED) drain less, and with 2 to 11 rounds per block take
-// equal shares: class (3, 4), 8 rounds, 222 us and 231 by tickets, class (1, 4)
-// 75 and 79; with three per CU tickets win there too (class (1, 3), 6 rounds,
-// 82 us in equal shares and 78, class (2, 2) of 400^2 corners 42 and 40.5).
-// One ticket per wave instead of per block made that class (2, 2) 65 us: draws
-// from one counter take about 20 ns each.
-template <int PER_ROUND, bool PAIRED>
+// The shares of the persistent blocks of a launch that runs NCLS order classes.
+// Every class list is cut into one contiguous region per XCD (neighbouring items
+// share that XCD's L2) and a region into chunks of whole rounds, an eighth of a
+// block's mean share of the class, 1 to 8 rounds.  The chunks of an XCD's
+// regions, class after class (the costliest first), are one sequence: block j
+// takes the j-th, and draws further ones from the XCD's ticket (drawn when a
+// chunk starts, read when it ends).
+// Why not equal shares: the oldest block of a CU wins every issue slot it asks
+// for and ended after half the kernel's time; the CU drained to two blocks,
+// then to one (2D Euler 2048^2, class (3, 3): 7370 us per launch, with tickets
+// 6570; class (4, 4) of 1021 x 777 corners 3410 and 3200).  One ticket per wave
+// instead of per block made class (2, 2) of 400^2 corners 65 us instead of 40:
+// draws from one counter take about 20 ns each.
+struct ChunkTable {
+  int32_t cum[MAX_CLASSES + 1];     // first chunk of each class in the sequence, and their number
+  int32_t len[MAX_CLASSES];         // items of the class's region
+  int32_t step[MAX_CLASSES];        // items per chunk
+  int64_t lo[MAX_CLASSES];          // first list position of the region
+  int32_t next[2];                  // ticket broadcast, used in turn (one barrier per chunk)
+};
+
+template <int NCLS>
 struct Chunks {
-  const int32_t* items;     // of the region
-  int base, end, len;       // the current chunk; the region's items
-  int step, nb, drawn, phase;
+  int cls, base, end;               // the current chunk: items [base, end) of class number cls
+  const int32_t* items;             // of that class's region
+  int id, nb, total, drawn, phase;
   int32_t* ticket;
-  bool more;                // chunks are left beyond the blocks' first ones
-  // block `blk` of `nblk` (a multiple of NXCD) on class c
-  __device__ __forceinline__ Chunks(const KStep& st, int c, int blk, int nblk) {
-    int64_t first = 0;
-    for (int k = 0; k < c; ++k) first += st.counts[k];
-    const int64_t n = st.counts[c];
-    const int x = blk % NXCD, j = blk / NXCD;
+  // cls[k], per_round[k]: class and items per round of the launch's class
+  // number k; row: the launch's row of tickets.  Ends with a barrier.
+  template <class F>
+  __device__ __forceinline__ Chunks(const KStep& st, ChunkTable& tab, int row, int blk, int nblk, F&& classes) {
+    static_assert(NCLS <= MAX_CLASSES, "one table entry per class");
+    const int x = blk % NXCD;
     nb = nblk / NXCD;
-    const int64_t lo = n * x / NXCD;
-    items = st.list + first + lo;
-    len = (int)(n * (x + 1) / NXCD - lo);
-    ticket = st.tickets + (c * NXCD + x) * TICKET_STRIDE;
+    id = blk / NXCD;
     phase = 0;
-    const int rounds = len / (PER_ROUND * nb);
-    if (PAIRED && rounds >= 2 && rounds < 12) {
-      base = (int)((int64_t)len * j / nb);
-      end = (int)((int64_t)len * (j + 1) / nb);
-      more = false;
-      step = drawn = 0;
+    drawn = 0;
+    ticket = st.tickets + (row * NXCD + x) * TICKET_STRIDE;
+    if (threadIdx.x == 0) {
+      int cum = 0;
+      for (int k = 0; k < NCLS; ++k) {
+        int c, per_round;
+        classes(k, c, per_round);
+        int64_t first = 0;
+        for (int q = 0; q < c; ++q) first += st.counts[q];
+        const int64_t n = st.counts[c], lo = n * x / NXCD;
+        const int len = (int)(n * (x + 1) / NXCD - lo);
+        const int share = len / (per_round * nb * 8);
+        const int step = per_round * (share < 1 ? 1 : share > 8 ? 8 : share);
+        tab.cum[k] = cum;
+        tab.len[k] = len;
+        tab.step[k] = step;
+        tab.lo[k] = first + lo;
+        cum += (len + step - 1) / step;
+      }
+      tab.cum[NCLS] = cum;
+    }
+    __syncthreads();
+    total = wave_uniform(tab.cum[NCLS]);
+  }
+  // The chunk `id` (false: none left); draws the next ticket.
+  __device__ __forceinline__ bool start(const KStep& st, const ChunkTable& tab) {
+    if (id >= total) return false;
+    int k = 0;
+#pragma unroll
+    for (int q = 1; q < NCLS; ++q) k += id >= tab.cum[q];
+    cls = wave_uniform(k);
+    const int step = wave_uniform(tab.step[cls]), len = wave_uniform(tab.len[cls]);
+    base = (id - wave_uniform(tab.cum[cls])) * step;
+    end = len - base < step ? len : base + step;
+    items = st.list + tab.lo[cls];
+    if (threadIdx.x == 0 && nb < total) drawn = atomicAdd(ticket, 1);
+    return true;
+  }
+  // After a chunk: its successor's id, in every thread.
+  __device__ __forceinline__ void advance(ChunkTable& tab) {
+    if (nb >= total) {
+      id = total;
       return;
     }
-    step = PER_ROUND * (rounds < 16 ? 1 : rounds >= 64 ? 8 : rounds / 8);
-    more = nb * step < len;
-    start(j);
-  }
-  __device__ __forceinline__ void start(int chunk) {
-    const int64_t at = (int64_t)chunk * step;
-    base = at < len ? (int)at : len;
-    end = len - base < step ? len : base + step;
-    drawn = 0;
-    if (more && base < end && threadIdx.x == 0) drawn = atomicAdd(ticket, 1);
-  }
-  // after a round: the next one, of the next chunk where this one is done.
-  // sh: two ints of LDS, used in turn so that one barrier per chunk suffices.
-  __device__ __forceinline__ void advance(int32_t* sh) {
-    base += PER_ROUND;
-    if (base < end || !more) return;
-    if (threadIdx.x == 0) sh[phase] = drawn;
+    if (threadIdx.x == 0) tab.next[phase] = drawn;
     __syncthreads();
-    const int t = wave_uniform(sh[phase]);
+    id = nb + wave_uniform(tab.next[phase]);
     phase ^= 1;
-    start(nb + t);
   }
 };
 

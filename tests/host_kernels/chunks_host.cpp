@@ -21,37 +21,61 @@ static int atomicAdd(int32_t* p, int v) {
 
 using namespace acat;
 
-template <int PER_ROUND, bool PAIRED>
-long bad_items(int n, int nblk, std::mt19937& rng) {
-  const int cls = 2, before = 5;
-  std::vector<int32_t> counts(MAX_CLASSES, 0), list(before + n), taken(before + n, 0);
+// a launch of three classes (numbers 4, 0 and 2 of the lists, 7, 256 and 16
+// items per round) with the given list lengths
+long bad_items(const int (&n)[3], int nblk, std::mt19937& rng) {
+  constexpr int cls[3] = {4, 0, 2}, per[3] = {7, 256, 16};
+  std::vector<int32_t> counts(MAX_CLASSES, 0);
+  for (int k = 0; k < 3; ++k) counts[cls[k]] = n[k];
+  counts[1] = 5;   // a class of another launch
+  int total = 0, first[MAX_CLASSES];
+  for (int c = 0; c < MAX_CLASSES; ++c) {
+    first[c] = total;
+    total += counts[c];
+  }
+  std::vector<int32_t> list(total), taken(total, 0);
   std::vector<int32_t> tickets(MAX_CLASSES * NXCD * TICKET_STRIDE, 0);
-  counts[0] = before;
-  counts[cls] = n;
-  for (int i = 0; i < before + n; ++i) list[i] = i;
+  for (int i = 0; i < total; ++i) list[i] = i;
   KStep st{};
   st.counts = counts.data();
   st.list = list.data();
   st.tickets = tickets.data();
-  std::vector<Chunks<PER_ROUND, PAIRED>> blk;
-  std::vector<int32_t> sh(2 * nblk, 0);
-  for (int b = 0; b < nblk; ++b) blk.emplace_back(st, cls, b, nblk);
-  std::vector<int> live(nblk);
+  std::vector<ChunkTable> tab(nblk);
+  std::vector<Chunks<3>> blk;
+  blk.reserve(nblk);
+  for (int b = 0; b < nblk; ++b)
+    blk.emplace_back(st, tab[b], 1, b, nblk, [&](int k, int& c, int& p) {
+      c = cls[k];
+      p = per[k];
+    });
+  long bad = 0;
+  std::vector<int> live(nblk), at(nblk, -1);   // at: item the block's chunk has come to (-1: no chunk)
   for (int b = 0; b < nblk; ++b) live[b] = b;
   while (!live.empty()) {
-    const size_t k = rng() % live.size();
-    auto& c = blk[live[k]];
-    if (c.base >= c.end) {
-      live[k] = live.back();
-      live.pop_back();
-      continue;
+    const size_t i = rng() % live.size();
+    const int b = live[i];
+    auto& c = blk[b];
+    if (at[b] < 0) {
+      if (!c.start(st, tab[b])) {
+        live[i] = live.back();
+        live.pop_back();
+        continue;
+      }
+      at[b] = c.base;
     }
-    for (int g = 0; g < PER_ROUND; ++g)
-      if (c.base + g < c.end) ++taken[c.items[c.base + g]];
-    c.advance(&sh[2 * live[k]]);
+    for (int g = 0; g < per[c.cls]; ++g)
+      if (at[b] + g < c.end) {
+        const int item = c.items[at[b] + g];
+        ++taken[item];
+        bad += item < first[cls[c.cls]] || item >= first[cls[c.cls]] + n[c.cls];
+      }
+    at[b] += per[c.cls];
+    if (at[b] >= c.end) {
+      c.advance(tab[b]);
+      at[b] = -1;
+    }
   }
-  long bad = 0;
-  for (int i = 0; i < before + n; ++i) bad += taken[i] != (i >= before);
+  for (int i = 0; i < total; ++i) bad += taken[i] != (i < first[1] || i >= first[1] + 5);
   return bad;
 }
 
@@ -60,16 +84,14 @@ int main() {
   threadIdx = {0, 0, 0};
   long bad = 0, cases = 0;
   for (int nblk : {8, 16, 72, 768})
-    for (int rounds : {0, 1, 2, 11, 12, 15, 16, 63, 64, 200}) {
-      if ((long)rounds * nblk > 20000) continue;
+    for (int rounds : {0, 1, 2, 9, 15, 16, 63, 64, 130})
       for (int d : {-9, -1, 0, 1, 2, 13}) {
-        const int n7 = rounds * 7 * nblk + d, n16 = rounds * 16 * nblk + d;
-        if (n7 < 0) continue;
-        bad += bad_items<7, false>(n7, nblk, rng) + bad_items<7, true>(n7, nblk, rng);
-        bad += bad_items<16, false>(n16, nblk, rng) + bad_items<16, true>(n16, nblk, rng);
+        const int a = rounds * 7 * nblk + d, b = (int)(rng() % 3) * 256 * nblk + d, c = (int)(rng() % (16 * nblk));
+        if (a < 0 || b < 0 || (long)rounds * nblk > 20000) continue;
+        const int lens[4][3] = {{a, b, c}, {a, 0, 0}, {0, b, 0}, {a, 1, c}};
+        for (const auto& n : lens) bad += bad_items(n, nblk, rng);
         cases += 4;
       }
-    }
   std::printf("%ld %ld\n", bad, cases);
   return 0;
 }
