@@ -82,7 +82,7 @@ KProb make_kprob(const acat_problem* p) {
 //   alx, aly      double
 //   Fx, Gy        double interface fluxes
 //   cls           int8 order class of every item (1D interface, 2D corner)
-//   hist          int32[tiles][MAX_CLASSES]
+//   hist          int32[MAX_CLASSES][tiles]
 //   offs          int32[MAX_CLASSES][tiles + 1]
 //   list          int32[items]
 //   part          double[tiles][dim] partial wave-speed maxima (acat_step_cfl)
@@ -222,12 +222,13 @@ acat_status do_step(const acat_problem* prob, const double* u_in, double* u_out,
     st.part = reinterpret_cast<double*>(w + L.part);
   }
   hipStream_t s = static_cast<hipStream_t>(stream);
+  st.recorded = dec && (dec->order_x || dec->psi1_x || dec->alpha_x ||
+                        (k.dim == 2 && (dec->order_y || dec->psi1_y || dec->alpha_y)));
   // a 1D step none of whose decisions are recorded leaves nothing to read in
   // the workspace either, and runs by tiles
-  const bool recorded = dec && (dec->order_x || dec->psi1_x || dec->alpha_x);
-  hipError_t e = k.dim == 2             ? launch_step_2d(k, st, 0, s)
-                 : replay || recorded ? launch_step_1d(k, st, 0, s)
-                                        : launch_tile_1d(k, st, s);
+  hipError_t e = k.dim == 2               ? launch_step_2d(k, st, 0, s)
+                 : replay || st.recorded ? launch_step_1d(k, st, 0, s)
+                                          : launch_tile_1d(k, st, s);
   return e == hipSuccess ? ACAT_OK : ACAT_ERR_DEVICE;
 }
 

@@ -59,13 +59,14 @@ struct KStep {
   double* Fx;             // x-interface fluxes [nvar][ny][nIx] (1D: [nvar][nI])
   double* Gy;             // y-interface fluxes [nvar][nIy][nx]
   int8_t* cls;            // order class of every item: 1D p-1 per interface; 2D (q1-1)*P + (q2-1) per corner [n2][n1]
-  int32_t* hist;          // per-tile class histograms of the classification kernel [tiles][MAX_CLASSES]
+  int32_t* hist;          // per-tile class histograms of the classification kernel [MAX_CLASSES][tiles]
   int32_t* offs;          // per-class exclusive prefix of hist over tiles [MAX_CLASSES][tiles + 1]
   int32_t* counts;        // [MAX_CLASSES] items per order class
   int32_t* list;          // item ids grouped by class, tile order within a class [items]
   int32_t* tickets;       // [MAX_CLASSES][NXCD][TICKET_STRIDE] chunk counters of the flux kernels (one used of each 16)
   uint32_t* status;       // device status bits
   int replay;             // decisions given in ord/psi/al
+  int recorded;           // the caller reads ord/psi/al (else only psi/al of order 1 are needed, by the flux kernels)
   // CFL mode: the classification also reduces the cells' spectral radii into
   // per-block partial maxima `part`, from which one block computes the time
   // step into dt_out (and advances t_dev) before the flux kernels read it

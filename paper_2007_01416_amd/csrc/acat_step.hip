@@ -233,9 +233,11 @@ __global__ __launch_bounds__(BLOCK) void k_classify2d(KProb pb, KStep st) {
           al = fmax(spectral_radius<FLUX, 2, NV>(pb.ph, uL, 0), spectral_radius<FLUX, 2, NV>(pb.ph, uR, 0));
         }
         const int64_t ex = i2 * pb.nIx + (i1 - pb.ioff);
-        st.ordx[ex] = (int8_t)q1;
-        st.psix[ex] = psi1;
-        st.alx[ex] = al;
+        if (st.recorded) st.ordx[ex] = (int8_t)q1;
+        if (st.recorded || q1 == 1) {
+          st.psix[ex] = psi1;
+          st.alx[ex] = al;
+        }
       }
       // y-interface (i1, i2 + 1/2): cells (i2 - G + 1 .. i2 + G, i1)
 #pragma unroll
@@ -259,9 +261,11 @@ __global__ __launch_bounds__(BLOCK) void k_classify2d(KProb pb, KStep st) {
           al = fmax(spectral_radius<FLUX, 2, NV>(pb.ph, uL, 1), spectral_radius<FLUX, 2, NV>(pb.ph, uR, 1));
         }
         const int64_t ey = (i2 - pb.ioff) * nx + i1;
-        st.ordy[ey] = (int8_t)q2;
-        st.psiy[ey] = psi1;
-        st.aly[ey] = al;
+        if (st.recorded) st.ordy[ey] = (int8_t)q2;
+        if (st.recorded || q2 == 1) {
+          st.psiy[ey] = psi1;
+          st.aly[ey] = al;
+        }
       }
     }
   }
@@ -676,9 +680,10 @@ __device__ __forceinline__ void flux2d_q11(const KProb& pb, const KStep& st, int
 }
 
 // The order classes of a 2D step in one or two launches, by the blocks that
-// fit a CU at their register need: three (FEW false: orders up to 3 but (2, 3)
-// and (3, 2); up to 168 registers per lane), or two (those two and the classes
-// with an order 4; up to 256).  All the classes of a launch share its blocks
+// fit a CU at their register need: three (THREE: orders up to 3 but (2, 3)
+// and (3, 2); up to 168 registers per lane), two (TWO: those two and the
+// classes with an order 4; up to 256), or all of them at two (ALL).  All the
+// classes of a launch share its blocks
 // (Chunks), so that a small grid's classes run side by side and a large one's
 // leave no tails.  The costliest class comes first.  Against one launch per
 // class or mirror pair, a step of 64^2 corners at P = 3 34.3 -> 27.7 us, 192^2
@@ -688,22 +693,23 @@ __device__ __forceinline__ void flux2d_q11(const KProb& pb, const KStep& st, int
 struct Cls {
   int q1, q2;
 };
-template <int P, bool FEW, bool SQUARE>
+enum Blocks { THREE, TWO, ALL };
+template <int P, Blocks B, bool SQUARE>
 struct ClassSet {
-  static constexpr Cls ALL[MAX_CLASSES] = {{4, 4}, {3, 4}, {4, 3}, {2, 4}, {4, 2}, {1, 4}, {4, 1}, {2, 3},
-                                           {3, 2}, {3, 3}, {1, 3}, {3, 1}, {2, 2}, {1, 2}, {2, 1}, {1, 1}};
+  static constexpr Cls EVERY[MAX_CLASSES] = {{4, 4}, {3, 4}, {4, 3}, {2, 4}, {4, 2}, {1, 4}, {4, 1}, {2, 3},
+                                             {3, 2}, {3, 3}, {1, 3}, {3, 1}, {2, 2}, {1, 2}, {2, 1}, {1, 1}};
   static constexpr bool few(Cls c) { return c.q1 == 4 || c.q2 == 4 || c.q1 + c.q2 == 5; }
   static constexpr bool has(Cls c) {
-    return c.q1 <= P && c.q2 <= P && few(c) == FEW && (!SQUARE || c.q1 == c.q2);
+    return c.q1 <= P && c.q2 <= P && (B == ALL || few(c) == (B == TWO)) && (!SQUARE || c.q1 == c.q2);
   }
   static constexpr int count() {
     int n = 0;
-    for (Cls c : ALL) n += has(c);
+    for (Cls c : EVERY) n += has(c);
     return n;
   }
   static constexpr int N = count();
   static constexpr Cls at(int k) {
-    for (Cls c : ALL)
+    for (Cls c : EVERY)
       if (has(c) && k-- == 0) return c;
     return {1, 1};
   }
@@ -745,10 +751,11 @@ struct ClassSet {
   }
 };
 
-template <int FLUX, int NV, int P, bool FEW, bool SQUARE>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(FEW ? 2 : 3))) void k_flux2d(KProb pb,
-                                                                                                  KStep st) {
-  using Set = ClassSet<P, FEW, SQUARE>;
+template <int FLUX, int NV, int P, Blocks B, bool SQUARE>
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(B == THREE ? 3 : 2))) void k_flux2d(KProb pb,
+                                                                                                         KStep st) {
+  using Set = ClassSet<P, B, SQUARE>;
+  static_assert(Set::N <= 9, "one case of the switch per class");
   __shared__ double2 xsm[2 * Xch<NV>::NP * Set::max_stride()];
   __shared__ double gxs[EdgeWeights::first(P + 1)], gys[EdgeWeights::first(P + 1)];
   __shared__ ChunkTable tab;
@@ -771,7 +778,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(FEW ? 2 :
     }
     return t;
   }();
-  Chunks<Set::N> ck(st, tab, FEW ? 1 : 0, blockIdx.x, gridDim.x, [&](int k, int& c, int& per_round) {
+  Chunks<Set::N> ck(st, tab, B == TWO ? 1 : 0, blockIdx.x, gridDim.x, [&](int k, int& c, int& per_round) {
     c = sets.cls[k];
     per_round = sets.per_round[k];
   });
@@ -952,16 +959,16 @@ hipError_t step1d_impl(const KProb& pb, const KStep& st, int cap, hipStream_t s)
 }
 
 // The classes of one launch (ClassSet).
-template <int FLUX, int NV, int P, bool FEW, bool SQUARE>
+template <int FLUX, int NV, int P, Blocks B, bool SQUARE>
 hipError_t launch_flux2d(const KProb& pb, const KStep& st, int cap, hipStream_t s) {
-  using Set = ClassSet<P, FEW, SQUARE>;
+  using Set = ClassSet<P, B, SQUARE>;
   if constexpr (Set::N > 0) {
     static const std::string name = [] {
       std::string n = "flux2d_";
       for (int k = 0; k < Set::N; ++k) n += "q" + std::to_string(10 * Set::at(k).q1 + Set::at(k).q2);
       return n;
     }();
-    auto kern = k_flux2d<FLUX, NV, P, FEW, SQUARE>;
+    auto kern = k_flux2d<FLUX, NV, P, B, SQUARE>;
     static const int per_cu = [&] {
       int b = 0;
       return hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, kern, BLOCK, 0) == hipSuccess && b > 0 ? b : 1;
@@ -976,6 +983,22 @@ hipError_t launch_flux2d(const KProb& pb, const KStep& st, int cap, hipStream_t 
     ACAT_CHECK_LAUNCH();
   }
   return hipSuccess;
+}
+
+// Up to P = 2 every class fits three blocks per CU.  Above, those that do not
+// are a launch of their own, but on grids so small that the launch costs more
+// than the third block gives: at P = 3 a step of 64^2 corners takes 25.2 us in
+// one launch and 28.0 in two, 192^2 51.5 and 59.7, 256^2 90.7 and 97.9, 320^2
+// 149 and 149, 512^2 358 and 343.  (At P = 4 two are as fast or faster: 100^2
+// 37.2 and 34.9, 300^2 193.8 and 195.6, 1021 x 777 3391 and 3397.)
+constexpr int64_t ONE_LAUNCH = 90000;
+template <int FLUX, int NV, int P, bool SQUARE>
+hipError_t launch_classes2d(const KProb& pb, const KStep& st, int cap, hipStream_t s) {
+  if constexpr (P == 3) {
+    if (pb.n1 * pb.n2 <= ONE_LAUNCH) return launch_flux2d<FLUX, NV, P, ALL, SQUARE>(pb, st, cap, s);
+  }
+  const hipError_t e = launch_flux2d<FLUX, NV, P, THREE, SQUARE>(pb, st, cap, s);
+  return e != hipSuccess ? e : launch_flux2d<FLUX, NV, P, TWO, SQUARE>(pb, st, cap, s);
 }
 
 template <int FLUX, int NV, int P>
@@ -1005,13 +1028,9 @@ template <int FLUX, int NV, int P>
 hipError_t step2d_impl(const KProb& pb, const KStep& st, int cap, hipStream_t s) {
   hipError_t e;
   if ((e = lists2d_impl<FLUX, NV, P>(pb, st, s)) != hipSuccess) return e;
-  if (pb.flags & FLAG_SQUARE_2D) {
-    if ((e = launch_flux2d<FLUX, NV, P, false, true>(pb, st, cap, s)) != hipSuccess) return e;
-    if ((e = launch_flux2d<FLUX, NV, P, true, true>(pb, st, cap, s)) != hipSuccess) return e;
-  } else {
-    if ((e = launch_flux2d<FLUX, NV, P, false, false>(pb, st, cap, s)) != hipSuccess) return e;
-    if ((e = launch_flux2d<FLUX, NV, P, true, false>(pb, st, cap, s)) != hipSuccess) return e;
-  }
+  e = pb.flags & FLAG_SQUARE_2D ? launch_classes2d<FLUX, NV, P, true>(pb, st, cap, s)
+                                : launch_classes2d<FLUX, NV, P, false>(pb, st, cap, s);
+  if (e != hipSuccess) return e;
   {
     ProfScope ps("update2d", s);
     k_update2d<FLUX, NV><<<(unsigned)((pb.nx * pb.ny + BLOCK - 1) / BLOCK), BLOCK, 0, s>>>(pb, st);

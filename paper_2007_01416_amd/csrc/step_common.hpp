@@ -182,7 +182,7 @@ __device__ __forceinline__ void block_hist(int* sh, bool valid, int cls, int32_t
   if (valid) atomicAdd(&sh[cls], 1);
   if (valid && cls2 >= 0) atomicAdd(&sh[cls2], 1);
   __syncthreads();
-  if (threadIdx.x < MAX_CLASSES) out[(int64_t)blockIdx.x * MAX_CLASSES + threadIdx.x] = sh[threadIdx.x];
+  if (threadIdx.x < MAX_CLASSES) out[(int64_t)threadIdx.x * gridDim.x + blockIdx.x] = sh[threadIdx.x];
 }
 
 // dt clipped so that t does not pass t_final
@@ -254,7 +254,8 @@ __global__ __launch_bounds__(SCAN_T) void k_scan_hist(const int32_t* hist, int n
   const int t0 = tid * per;
   const int t1 = min(t0 + per, ntiles);
   int acc = 0;
-  for (int t = t0; t < t1; ++t) acc += hist[(int64_t)t * MAX_CLASSES + c];
+  const int32_t* mine = hist + (int64_t)c * ntiles;
+  for (int t = t0; t < t1; ++t) acc += mine[t];
   // block-wide exclusive scan of acc: wave inclusive scan, then the wave totals
   int inc = acc;
 #pragma unroll
@@ -278,7 +279,7 @@ __global__ __launch_bounds__(SCAN_T) void k_scan_hist(const int32_t* hist, int n
   int run = wsum[wid] + inc - acc;
   for (int t = t0; t < t1; ++t) {
     offs[(int64_t)c * (ntiles + 1) + t] = run;
-    run += hist[(int64_t)t * MAX_CLASSES + c];
+    run += mine[t];
   }
 }
 
