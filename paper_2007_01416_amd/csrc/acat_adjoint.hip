@@ -14,6 +14,9 @@
 // fixed order (deterministic, no atomics).
 #include <hip/hip_runtime.h>
 
+#include <string>
+#include <utility>
+
 #include "acat_internal.hpp"
 #include "coeffs.hpp"
 #include "step_common.hpp"
@@ -54,7 +57,7 @@ __global__ __launch_bounds__(BLOCK) void k_adj1d(KProb pb, KStep st, const doubl
   const double eta = TB.ETA[p][a];
 
   int buf = 0;
-  const Slice sl(st.counts, st.list, p - 1);
+  const Slice sl(st.counts, st.list, p - 1, GPB);
   for (int64_t base = sl.lo; base < sl.hi; base += GPB) {
     const bool valid = inblk && base + g < sl.hi;
     const int32_t k = valid ? sl.items[base + g] : 0;
@@ -360,6 +363,19 @@ __device__ __forceinline__ void corner_adjoint(const Phys& ph, const double (&u)
     for (int c = 0; c < NV; ++c) Ub[l][c] = 0.0;
 #pragma unroll
   for (int kk = T; kk >= 2; --kk) {
+    // The predicted states below recompute the forward sweep's with the same
+    // operations; made opaque, U keeps the compiler from holding those of all
+    // levels from there to here instead (up to 4 T^2 doubles; q44: 1112 bytes of
+    // scratch per lane, with this 472; P = 3 rectangles with an order 3 in one
+    // kernel: 266 spills, then 175; Euler 192^2: 126 us, then 113; the whole P = 4
+    // adjoint step of 256^2: 1998 us, then 1377).  At T = 4
+    // they fit, and recomputing them costs more: 512^2 P = 2 100.5 us, 104 so.
+    if constexpr (T > 4) {
+#pragma unroll
+      for (int l = 1; l <= kk - 1; ++l)
+#pragma unroll
+        for (int c = 0; c < NV; ++c) asm volatile("" : "+v"(U[l][c]));
+    }
 #pragma unroll
     for (int ri = 0; ri < T; ++ri) {
       const int r = ri - QT + 1;
@@ -425,18 +441,20 @@ __device__ __forceinline__ void corner_adjoint(const Phys& ph, const double (&u)
 // consecutive corners)
 // PASSES (corners with q1 != q2): 1 = the F recursion only, 2 = the G recursion
 // only, added to the contributions the first launch wrote, 3 = both.
-// The body runs the block's share `sl` of the class list; xsm: the two LDS
-// exchange buffers (2 Xch<NV>::NP adj_stride<L>() double2), g1s: LDS for the
-// derivative weights ((2 Q1)^2 + (2 Q2)^2 doubles).
+// The body runs the items [base, end) of the class's list; xsm: the two LDS
+// exchange buffers (2 Xch<NV>::NP adj_stride<L>() double2), gx, gy: LDS, the
+// derivative weights times -lamx and -lamy ((2 Q1)^2 and (2 Q2)^2 doubles,
+// row-major: rows for the recursion, columns for its transpose).
 template <int L>
 constexpr int adj_stride() {
   return Groups<L>::WAVE_LOCAL ? Groups<L>::TOTAL * L : BLOCK + L;
 }
 
 template <int FLUX, int NV, int Q1, int Q2, int PASSES>
-__device__ __forceinline__ void adj2d_body(const KProb& pb, const KStep& st, const Slice& sl,
+__device__ __forceinline__ void adj2d_body(const KProb& pb, const KStep& st, int tid, double dt,
+                                           const int32_t* items, int64_t base, int64_t end,
                                            const double* __restrict__ ubo, double* __restrict__ C, int LMAX,
-                                           double2* xsm, double* g1s) {
+                                           double2* xsm, const double* gx, const double* gy) {
   constexpr int N1 = 2 * Q1, N2 = 2 * Q2, L = N1 * N2;
   using Grp = Groups<L>;
   constexpr int CPB = Grp::PER_BLOCK;
@@ -444,13 +462,11 @@ __device__ __forceinline__ void adj2d_body(const KProb& pb, const KStep& st, con
   constexpr int STRIDE = adj_stride<L>();
   double2* const xs[2] = {xsm, xsm + NP * STRIDE};
 
-  const int tid = threadIdx.x;
   const Grp grp(tid);
   const int g = grp.g;
   const int nd = grp.node;
   const int a1 = nd % N1, a2 = nd / N1;
   const bool inblk = grp.in;
-  const double dt = step_dt(st);
   const double lamx = dt / pb.dx, lamy = dt / pb.dy;
   const int64_t nx = pb.nx, plane = pb.nx * pb.ny;
   const int nx32 = (int)pb.nx, ny32 = (int)pb.ny, ioff = (int)pb.ioff;
@@ -458,20 +474,12 @@ __device__ __forceinline__ void adj2d_body(const KProb& pb, const KStep& st, con
   const int64_t nitems = pb.n1 * pb.n2;
   const int64_t cstride = nitems * LMAX;
 
-  // derivative weights times -lamx (x) and -lamy (y) in LDS, row-major: rows
-  // for the recursion, columns for its transpose
-  for (int i = tid; i < N1 * N1 + N2 * N2; i += BLOCK)
-    g1s[i] = i < N1 * N1 ? -lamx * TB.G1[Q1][i / N1][i % N1]
-                         : -lamy * TB.G1[Q2][(i - N1 * N1) / N2][(i - N1 * N1) % N2];
-  __syncthreads();
-  const double* gx = g1s;
-  const double* gy = g1s + N1 * N1;
   const bool on_row = a2 == Q2 - 1, on_col = a1 == Q1 - 1;
 
   int buf = 0;
-  for (int64_t base = sl.lo; base < sl.hi; base += CPB) {
-    const bool valid = inblk && base + g < sl.hi;
-    const int32_t e = valid ? sl.items[base + g] : 0;
+  for (; base < end; base += CPB) {
+    const bool valid = inblk && base + g < end;
+    const int32_t e = valid ? items[base + g] : 0;
     const uint32_t eq = (uint32_t)e / n1u;
     const int i2 = (int)eq + ioff, i1 = (int)((uint32_t)e - eq * n1u) + ioff;
     const int x = bc_index32(i1 + (a1 - Q1 + 1), nx32, pb.bc);
@@ -571,14 +579,30 @@ __device__ __forceinline__ void adj2d_body(const KProb& pb, const KStep& st, con
   }
 }
 
+// One class: stages its derivative weights in g1s, then runs a share of its list.
+template <int FLUX, int NV, int Q1, int Q2, int PASSES>
+__device__ __forceinline__ void adj2d_class(const KProb& pb, const KStep& st, const Slice& sl,
+                                            const double* __restrict__ ubo, double* __restrict__ C, int LMAX,
+                                            double2* xsm, double* g1s) {
+  constexpr int N1 = 2 * Q1, N2 = 2 * Q2;
+  const double dt = step_dt(st);
+  const double lamx = dt / pb.dx, lamy = dt / pb.dy;
+  for (int i = threadIdx.x; i < N1 * N1 + N2 * N2; i += BLOCK)
+    g1s[i] = i < N1 * N1 ? -lamx * TB.G1[Q1][i / N1][i % N1]
+                         : -lamy * TB.G1[Q2][(i - N1 * N1) / N2][(i - N1 * N1) % N2];
+  __syncthreads();
+  adj2d_body<FLUX, NV, Q1, Q2, PASSES>(pb, st, (int)threadIdx.x, dt, sl.items, sl.lo, sl.hi, ubo, C, LMAX, xsm, g1s,
+                                       g1s + N1 * N1);
+}
+
 template <int FLUX, int NV, int Q1, int Q2, int PASSES = 3>
 __global__ __launch_bounds__(BLOCK) void k_adj2d(KProb pb, KStep st, const double* __restrict__ ubo,
                                                  double* __restrict__ C, int LMAX) {
   constexpr int L = (2 * Q1) * (2 * Q2);
   __shared__ double2 xsm[2 * Xch<NV>::NP * adj_stride<L>()];
   __shared__ double g1s[(2 * Q1) * (2 * Q1) + (2 * Q2) * (2 * Q2)];
-  adj2d_body<FLUX, NV, Q1, Q2, PASSES>(pb, st, Slice(st.counts, st.list, (Q1 - 1) * pb.P + (Q2 - 1)), ubo, C,
-                                       LMAX, xsm, g1s);
+  adj2d_class<FLUX, NV, Q1, Q2, PASSES>(
+      pb, st, Slice(st.counts, st.list, (Q1 - 1) * pb.P + (Q2 - 1), Groups<L>::PER_BLOCK), ubo, C, LMAX, xsm, g1s);
 }
 
 // Order class (1,1) with ONE LANE PER CORNER: the adjoint of the one-lane
@@ -589,9 +613,9 @@ __global__ __launch_bounds__(BLOCK) void k_adj2d(KProb pb, KStep st, const doubl
 // the terms that are zero for this class: the predicted-state adjoint at
 // node (1,1), which no flux reads.  Writes the four nodes' contributions.
 template <int FLUX, int NV>
-__global__ __launch_bounds__(BLOCK) void k_adj2d_q11(KProb pb, KStep st, const double* __restrict__ ubo,
-                                                     double* __restrict__ C, int LMAX) {
-  const double dt = step_dt(st);
+__device__ __forceinline__ void adj2d_q11(const KProb& pb, const KStep& st, int tid, double dt, const int32_t* items,
+                                          int64_t base, int64_t end, const double* __restrict__ ubo,
+                                          double* __restrict__ C, int LMAX) {
   const double lamx = dt / pb.dx, lamy = dt / pb.dy;
   double gx[2][2], gy[2][2];   // -lamx G1[1][a][l], -lamy G1[1][a][l]
 #pragma unroll
@@ -609,9 +633,8 @@ __global__ __launch_bounds__(BLOCK) void k_adj2d_q11(KProb pb, KStep st, const d
   const int64_t nitems = pb.n1 * pb.n2;
   const int64_t cstride = nitems * LMAX;
   const bool per = pb.bc == PERIODIC;
-  const Slice sl(st.counts, st.list, 0);
-  for (int64_t it = sl.lo + threadIdx.x; it < sl.hi; it += BLOCK) {
-    const int32_t e = sl.items[it];
+  for (int64_t it = base + tid; it < end; it += BLOCK) {
+    const int32_t e = items[it];
     const uint32_t eq = (uint32_t)e / n1u;
     const int i2 = (int)eq + ioff, i1 = (int)((uint32_t)e - eq * n1u) + ioff;
     int xs[2], ys[2];
@@ -757,6 +780,13 @@ __global__ __launch_bounds__(BLOCK) void k_adj2d_q11(KProb pb, KStep st, const d
   }
 }
 
+template <int FLUX, int NV>
+__global__ __launch_bounds__(BLOCK) void k_adj2d_q11(KProb pb, KStep st, const double* __restrict__ ubo,
+                                                     double* __restrict__ C, int LMAX) {
+  const Slice sl(st.counts, st.list, 0, BLOCK);
+  adj2d_q11<FLUX, NV>(pb, st, (int)threadIdx.x, step_dt(st), sl.items, sl.lo, sl.hi, ubo, C, LMAX);
+}
+
 // The mirror classes (QA, QB) and (QB, QA), QA < QB, in one launch (both
 // recursions in one pass): the grid is cut into two runs of whole XCD groups
 // of blocks sized by the classes' corner counts, at least one per class with
@@ -766,7 +796,7 @@ __global__ __launch_bounds__(BLOCK) void k_adj2d_q11(KProb pb, KStep st, const d
 template <int FLUX, int NV, int QA, int QB>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu((QB <= 2) ? 2 : 1))) void k_adj2d_pair(
     KProb pb, KStep st, const double* __restrict__ ubo, double* __restrict__ C, int LMAX) {
-  constexpr int L = (2 * QA) * (2 * QB);
+  constexpr int L = (2 * QA) * (2 * QB), CPB = Groups<L>::PER_BLOCK;
   __shared__ double2 xsm[2 * Xch<NV>::NP * adj_stride<L>()];
   __shared__ double g1s[(2 * QA) * (2 * QA) + (2 * QB) * (2 * QB)];
   const int ca = (QA - 1) * pb.P + (QB - 1), cb = (QB - 1) * pb.P + (QA - 1);
@@ -776,12 +806,12 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu((QB <= 2)
   const int ua = na == 0 ? 0 : (nb == 0 ? units : 1 + (int)((int64_t)(units - 2) * na / (na + nb)));
   const int unit = (int)blockIdx.x / NXCD;
   if (unit < ua)
-    adj2d_body<FLUX, NV, QA, QB, 3>(pb, st, Slice(st.counts, st.list, ca, blockIdx.x, ua * NXCD), ubo, C, LMAX,
-                                    xsm, g1s);
+    adj2d_class<FLUX, NV, QA, QB, 3>(pb, st, Slice(st.counts, st.list, ca, blockIdx.x, ua * NXCD, CPB), ubo, C, LMAX,
+                                     xsm, g1s);
   else
-    adj2d_body<FLUX, NV, QB, QA, 3>(pb, st,
-                                    Slice(st.counts, st.list, cb, blockIdx.x - ua * NXCD, (units - ua) * NXCD),
-                                    ubo, C, LMAX, xsm, g1s);
+    adj2d_class<FLUX, NV, QB, QA, 3>(pb, st,
+                                     Slice(st.counts, st.list, cb, blockIdx.x - ua * NXCD, (units - ua) * NXCD, CPB),
+                                     ubo, C, LMAX, xsm, g1s);
 }
 
 // Corners k whose node at offset j reads cell m along one direction of n
@@ -879,6 +909,126 @@ __global__ __launch_bounds__(BLOCK) void k_gather2d(KProb pb, KStep st, const do
     if (e_ != hipSuccess) return e_;         \
   } while (0)
 
+// Every class of a step of P <= 3 with orders up to 2 (HIGH false: two blocks per
+// CU) or with an order 3 (HIGH: one block), in one launch whose blocks share the
+// rounds of all its class lists.  Same arithmetic per corner as a launch per
+// class.  Bound by FP64 issue at one or two waves per SIMD, and a launch per class
+// ended each with most of the card idle: a class of a small grid has fewer rounds
+// than the card has blocks.  The blocks take the rounds in turn, the costliest
+// class first.
+// Whole adjoint step, Euler, launches per class / sets: 192^2 P = 3 276 us / 193,
+// 512^2 P = 3 1738 / 1703, 512^2 P = 2 185 / 176.  P = 4 keeps a launch per class:
+// its rectangles of order 4 run in two launches each, and the body of all
+// others beside them spills.
+template <int P, bool HIGH>
+struct AdjSet {
+  struct Cls {
+    int q1, q2, per_round, stride;
+  };
+  template <int Q1, int Q2>
+  static constexpr Cls cls() {
+    if (Q1 * Q2 == 1) return {1, 1, BLOCK, 0};
+    return {Q1, Q2, Groups<4 * Q1 * Q2>::PER_BLOCK, adj_stride<4 * Q1 * Q2>()};
+  }
+  static constexpr Cls EVERY[9] = {cls<3, 3>(), cls<2, 3>(), cls<3, 2>(), cls<1, 3>(), cls<3, 1>(),
+                                   cls<2, 2>(), cls<1, 2>(), cls<2, 1>(), cls<1, 1>()};   // costliest first
+  static constexpr int FIRST = HIGH ? 0 : (P >= 2 ? 5 : 8);
+  static constexpr int N = HIGH ? (P == 3 ? 5 : 0) : 9 - FIRST;
+  static constexpr Cls at(int k) { return EVERY[FIRST + k]; }
+  static constexpr int max_stride() {
+    int m = 1;
+    for (int k = 0; k < N; ++k) m = at(k).stride > m ? at(k).stride : m;
+    return m;
+  }
+  static constexpr int min_per_round() {
+    int m = BLOCK;
+    for (int k = 0; k < N; ++k) m = at(k).per_round < m ? at(k).per_round : m;
+    return m;
+  }
+};
+
+template <int FLUX, int NV, int P, bool HIGH>
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(HIGH ? 1 : 2))) void k_adj2d_set(
+    KProb pb, KStep st, const double* __restrict__ ubo, double* __restrict__ C, int LMAX) {
+  using Set = AdjSet<P, HIGH>;
+  __shared__ double2 xsm[2 * Xch<NV>::NP * Set::max_stride()];
+  __shared__ double gxs[EdgeWeights::first(P + 1)], gys[EdgeWeights::first(P + 1)];
+  __shared__ ChunkTable tab;
+  const double dt = step_dt(st);
+  for (int q = 1; q <= P; ++q) {
+    const double lamx = dt / pb.dx, lamy = dt / pb.dy;
+    for (int i = threadIdx.x; i < 4 * q * q; i += BLOCK) {
+      const double w = TB.G1[q][i / (2 * q)][i % (2 * q)];
+      gxs[EdgeWeights::first(q) + i] = -lamx * w;
+      gys[EdgeWeights::first(q) + i] = -lamy * w;
+    }
+  }
+  constexpr auto sets = [] {
+    struct {
+      int cls[9], per_round[9];
+    } t{};
+    for (int k = 0; k < Set::N; ++k) {
+      t.cls[k] = (Set::at(k).q1 - 1) * P + Set::at(k).q2 - 1;
+      t.per_round[k] = Set::at(k).per_round;
+    }
+    return t;
+  }();
+  Chunks<Set::N, false> ck(st, tab, 0, blockIdx.x, gridDim.x, [&](int k, int& c, int& per_round) {
+    c = sets.cls[k];
+    per_round = sets.per_round[k];
+  });
+  auto run = [&](auto kc) {
+    constexpr int k = decltype(kc)::value;
+    if constexpr (k < Set::N) {
+      constexpr auto c = Set::at(k);
+      // computed at each chunk: kept for all classes at once it would spill
+      int tid = threadIdx.x;
+      double h = dt;
+      asm volatile("" : "+v"(tid), "+v"(h));
+      if constexpr (c.q1 == 1 && c.q2 == 1)
+        adj2d_q11<FLUX, NV>(pb, st, tid, h, ck.items, ck.base, ck.end, ubo, C, LMAX);
+      else
+        adj2d_body<FLUX, NV, c.q1, c.q2, 3>(pb, st, tid, h, ck.items, ck.base, ck.end, ubo, C, LMAX, xsm,
+                                            gxs + EdgeWeights::first(c.q1), gys + EdgeWeights::first(c.q2));
+    }
+  };
+  while (ck.start(st, tab)) {
+    switch (ck.cls) {
+      case 0: run(std::integral_constant<int, 0>{}); break;
+      case 1: run(std::integral_constant<int, 1>{}); break;
+      case 2: run(std::integral_constant<int, 2>{}); break;
+      case 3: run(std::integral_constant<int, 3>{}); break;
+      default: run(std::integral_constant<int, 4>{}); break;
+    }
+    ck.advance(tab);
+  }
+}
+
+template <int FLUX, int NV, int P, bool HIGH>
+hipError_t launch_adjset(const KProb& pb, const KStep& st, const double* ubo, double* C, hipStream_t s) {
+  using Set = AdjSet<P, HIGH>;
+  if constexpr (Set::N > 0) {
+    static const std::string name = [] {
+      std::string n = "adjoint2d_";
+      for (int k = 0; k < Set::N; ++k) n += "q" + std::to_string(10 * Set::at(k).q1 + Set::at(k).q2);
+      return n;
+    }();
+    auto kern = k_adj2d_set<FLUX, NV, P, HIGH>;
+    static const int per_cu = [&] {
+      int b = 0;
+      return hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, kern, BLOCK, 0) == hipSuccess && b > 0 ? b : 1;
+    }();
+    const int64_t rounds = pb.n1 * pb.n2 / Set::min_per_round() + NXCD * Set::N;
+    const int grid = persistent_grid(kern, rounds * BLOCK, 0, BLOCK, per_cu);
+    {
+      ProfScope ps(name.c_str(), s);
+      kern<<<grid, BLOCK, 0, s>>>(pb, st, ubo, C, 4 * P * P);
+    }
+    ACAT_CHECK_LAUNCH();
+  }
+  return hipSuccess;
+}
+
 template <int FLUX, int NV, int P, int p>
 hipError_t launch_adj1d(const KProb& pb, const KStep& st, const double* ubo, double* C, hipStream_t s) {
   if constexpr (p <= P) {
@@ -971,19 +1121,24 @@ hipError_t launch_adjpair2d(const KProb& pb, const KStep& st, const double* ubo,
 template <int FLUX, int NV, int P>
 hipError_t adj2d_impl(const KProb& pb, const KStep& st, const double* ubo, double* ubi, double* C, hipStream_t s) {
   hipError_t e;
-  if ((e = launch_adj2d<FLUX, NV, P, 1, 1>(pb, st, ubo, C, s)) != hipSuccess) return e;
-  if ((e = launch_adjpair2d<FLUX, NV, P, 1, 2>(pb, st, ubo, C, s)) != hipSuccess) return e;
-  if ((e = launch_adj2d<FLUX, NV, P, 2, 2>(pb, st, ubo, C, s)) != hipSuccess) return e;
-  if ((e = launch_adjpair2d<FLUX, NV, P, 1, 3>(pb, st, ubo, C, s)) != hipSuccess) return e;
-  if ((e = launch_adjpair2d<FLUX, NV, P, 2, 3>(pb, st, ubo, C, s)) != hipSuccess) return e;
-  if ((e = launch_adj2d<FLUX, NV, P, 3, 3>(pb, st, ubo, C, s)) != hipSuccess) return e;
-  if ((e = launch_adj2d<FLUX, NV, P, 1, 4>(pb, st, ubo, C, s)) != hipSuccess) return e;
-  if ((e = launch_adj2d<FLUX, NV, P, 4, 1>(pb, st, ubo, C, s)) != hipSuccess) return e;
-  if ((e = launch_adj2d<FLUX, NV, P, 2, 4>(pb, st, ubo, C, s)) != hipSuccess) return e;
-  if ((e = launch_adj2d<FLUX, NV, P, 4, 2>(pb, st, ubo, C, s)) != hipSuccess) return e;
-  if ((e = launch_adj2d<FLUX, NV, P, 3, 4>(pb, st, ubo, C, s)) != hipSuccess) return e;
-  if ((e = launch_adj2d<FLUX, NV, P, 4, 3>(pb, st, ubo, C, s)) != hipSuccess) return e;
-  if ((e = launch_adj2d<FLUX, NV, P, 4, 4>(pb, st, ubo, C, s)) != hipSuccess) return e;
+  if constexpr (P <= 3) {
+    if ((e = launch_adjset<FLUX, NV, P, false>(pb, st, ubo, C, s)) != hipSuccess) return e;
+    if ((e = launch_adjset<FLUX, NV, P, true>(pb, st, ubo, C, s)) != hipSuccess) return e;
+  } else {
+    if ((e = launch_adj2d<FLUX, NV, P, 1, 1>(pb, st, ubo, C, s)) != hipSuccess) return e;
+    if ((e = launch_adjpair2d<FLUX, NV, P, 1, 2>(pb, st, ubo, C, s)) != hipSuccess) return e;
+    if ((e = launch_adj2d<FLUX, NV, P, 2, 2>(pb, st, ubo, C, s)) != hipSuccess) return e;
+    if ((e = launch_adjpair2d<FLUX, NV, P, 1, 3>(pb, st, ubo, C, s)) != hipSuccess) return e;
+    if ((e = launch_adjpair2d<FLUX, NV, P, 2, 3>(pb, st, ubo, C, s)) != hipSuccess) return e;
+    if ((e = launch_adj2d<FLUX, NV, P, 3, 3>(pb, st, ubo, C, s)) != hipSuccess) return e;
+    if ((e = launch_adj2d<FLUX, NV, P, 1, 4>(pb, st, ubo, C, s)) != hipSuccess) return e;
+    if ((e = launch_adj2d<FLUX, NV, P, 4, 1>(pb, st, ubo, C, s)) != hipSuccess) return e;
+    if ((e = launch_adj2d<FLUX, NV, P, 2, 4>(pb, st, ubo, C, s)) != hipSuccess) return e;
+    if ((e = launch_adj2d<FLUX, NV, P, 4, 2>(pb, st, ubo, C, s)) != hipSuccess) return e;
+    if ((e = launch_adj2d<FLUX, NV, P, 3, 4>(pb, st, ubo, C, s)) != hipSuccess) return e;
+    if ((e = launch_adj2d<FLUX, NV, P, 4, 3>(pb, st, ubo, C, s)) != hipSuccess) return e;
+    if ((e = launch_adj2d<FLUX, NV, P, 4, 4>(pb, st, ubo, C, s)) != hipSuccess) return e;
+  }
   {
     ProfScope ps("gather2d", s);
     const unsigned gb = (unsigned)((pb.nx * pb.ny + BLOCK - 1) / BLOCK);

@@ -59,7 +59,7 @@ __global__ __launch_bounds__(BS) void k_flux_b(KBatch bt, KBStep st) {
   using Cat = Cat1D<FLUX, NV, p, BS>;
   __shared__ double xs[Cat::LDS_DOUBLES];
   const Cat cat(threadIdx.x);
-  const Slice sl(st.counts, st.list, p - 1);
+  const Slice sl(st.counts, st.list, p - 1, Cat::PER_ROUND);
   for (int64_t base = sl.lo; base < sl.hi; base += Cat::PER_ROUND) {
     const bool valid = cat.in && base + cat.g < sl.hi;
     const int64_t kg = valid ? sl.items[base + cat.g] : 0;

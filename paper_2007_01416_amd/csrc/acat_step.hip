@@ -99,7 +99,7 @@ __global__ __launch_bounds__(BLOCK) void k_flux1d(KProb pb, KStep st) {
   const Cat cat(threadIdx.x);
   const double lam = step_dt(st) / pb.dx;
   const int64_t nx = pb.nx, nI = pb.nIx;
-  const Slice sl(st.counts, st.list, p - 1);
+  const Slice sl(st.counts, st.list, p - 1, Cat::PER_ROUND);
   for (int64_t base = sl.lo; base < sl.hi; base += Cat::PER_ROUND) {
     const bool valid = cat.in && base + cat.g < sl.hi;
     const int32_t k = valid ? sl.items[base + cat.g] : 0;
@@ -428,12 +428,6 @@ template <int L>
 constexpr int corner_stride() {
   return Groups<L>::TOTAL * corner_group_stride<L>();
 }
-
-// First-derivative weights of every half-width up to 4 times -lamx (rows) and
-// -lamy (columns), in LDS: node a, weight l of half-width q at first(q) + 2 q a + l.
-struct EdgeWeights {
-  static constexpr int first(int q) { return 4 * ((q - 1) * q * (2 * q - 1) / 6); }   // 4 sum_{k<q} k^2
-};
 
 // Fluxes of the corners of order class (Q1, Q2) (Sec. 4; rectangle J_Q1 x J_Q2),
 // items [base, end) of the list; every class but (1,1), which runs one lane

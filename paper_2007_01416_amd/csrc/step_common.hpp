@@ -128,27 +128,29 @@ __device__ __forceinline__ double limiter(const double (&v)[NV][2 * G]) {
 }
 
 // Balanced slice of one class list: the n items of class c (spatial order)
-// are cut into gridDim.x contiguous slices, and the slices of the blocks on
-// XCD x (blockIdx % 8) are adjacent, so neighbouring items share that XCD's L2.
+// are cut, by whole rounds of per_round items, into gridDim.x contiguous
+// slices, and the slices of the blocks on XCD x (blockIdx % 8) are adjacent, so
+// neighbouring items share that XCD's L2.
 struct Slice {
   const int32_t* items;
   int64_t lo, hi;
-  __device__ Slice(const int32_t* counts, const int32_t* list, int c) {
-    init(counts, list, c, blockIdx.x, gridDim.x);
+  __device__ Slice(const int32_t* counts, const int32_t* list, int c, int per_round) {
+    init(counts, list, c, blockIdx.x, gridDim.x, per_round);
   }
   // block `blk` of `nblk` blocks working on class c (nblk a multiple of the
   // XCD count, and blk on XCD blk % NXCD)
-  __device__ Slice(const int32_t* counts, const int32_t* list, int c, int blk, int nblk) {
-    init(counts, list, c, blk, nblk);
+  __device__ Slice(const int32_t* counts, const int32_t* list, int c, int blk, int nblk, int per_round) {
+    init(counts, list, c, blk, nblk, per_round);
   }
-  __device__ void init(const int32_t* counts, const int32_t* list, int c, int blk, int nblk) {
+  __device__ void init(const int32_t* counts, const int32_t* list, int c, int blk, int nblk, int per_round) {
     int64_t base = 0;
     for (int k = 0; k < c; ++k) base += counts[k];
-    const int64_t n = counts[c];
+    const int64_t n = counts[c], rounds = (n + per_round - 1) / per_round;
     const int nb = nblk / NXCD;
     const int r = (blk % NXCD) * nb + blk / NXCD;
-    lo = n * r / nblk;
-    hi = n * (r + 1) / nblk;
+    lo = rounds * r / nblk * per_round;
+    hi = rounds * (r + 1) / nblk * per_round;
+    if (hi > n) hi = n;
     items = list + base;
   }
 };
@@ -460,6 +462,8 @@ __device__ __forceinline__ T wave_uniform(T v) {
 // 6570; class (4, 4) of 1021 x 777 corners 3410 and 3200).  One ticket per wave
 // instead of per block made class (2, 2) of 400^2 corners 65 us instead of 40:
 // draws from one counter take about 20 ns each.
+// Without tickets (DRAW false: the reverse kernels, whose step has no launch to
+// clear them in): chunks of one round, block j takes the j-th, (j + nb)-th, ...
 struct ChunkTable {
   int32_t cum[MAX_CLASSES + 1];     // first chunk of each class in the sequence, and their number
   int32_t len[MAX_CLASSES];         // items of the class's region
@@ -468,7 +472,7 @@ struct ChunkTable {
   int32_t next[2];                  // ticket broadcast, used in turn (one barrier per chunk)
 };
 
-template <int NCLS>
+template <int NCLS, bool DRAW = true>
 struct Chunks {
   int cls, base, end;               // the current chunk: items [base, end) of class number cls
   const int32_t* items;             // of that class's region
@@ -484,7 +488,7 @@ struct Chunks {
     id = blk / NXCD;
     phase = 0;
     drawn = 0;
-    ticket = st.tickets + (row * NXCD + x) * TICKET_STRIDE;
+    ticket = DRAW ? st.tickets + (row * NXCD + x) * TICKET_STRIDE : nullptr;
     if (threadIdx.x == 0) {
       int cum = 0;
       for (int k = 0; k < NCLS; ++k) {
@@ -495,7 +499,7 @@ struct Chunks {
         const int64_t n = st.counts[c], lo = n * x / NXCD;
         const int len = (int)(n * (x + 1) / NXCD - lo);
         const int share = len / (per_round * nb * 8);
-        const int step = per_round * (share < 1 ? 1 : share > 8 ? 8 : share);
+        const int step = per_round * (!DRAW || share < 1 ? 1 : share > 8 ? 8 : share);
         tab.cum[k] = cum;
         tab.len[k] = len;
         tab.step[k] = step;
@@ -518,13 +522,18 @@ struct Chunks {
     base = (id - wave_uniform(tab.cum[cls])) * step;
     end = len - base < step ? len : base + step;
     items = st.list + tab.lo[cls];
-    if (threadIdx.x == 0 && nb < total) drawn = atomicAdd(ticket, 1);
+    if (DRAW && threadIdx.x == 0 && nb < total) drawn = atomicAdd(ticket, 1);
     return true;
   }
   // After a chunk: its successor's id, in every thread.
   __device__ __forceinline__ void advance(ChunkTable& tab) {
     if (nb >= total) {
       id = total;
+      return;
+    }
+    if constexpr (!DRAW) {
+      __syncthreads();
+      id += nb;
       return;
     }
     if (threadIdx.x == 0) tab.next[phase] = drawn;
@@ -543,6 +552,12 @@ int group_grid(K kernel, int64_t nitems, int cap) {
   constexpr int PB = Groups<L>::PER_BLOCK;
   return persistent_grid(kernel, (nitems + PB - 1) / PB * BLOCK, cap);
 }
+
+// First-derivative weights of every half-width up to 4 times -lamx (rows) and
+// -lamy (columns), in LDS: node a, weight l of half-width q at first(q) + 2 q a + l.
+struct EdgeWeights {
+  static constexpr int first(int q) { return 4 * ((q - 1) * q * (2 * q - 1) / 6); }   // 4 sum_{k<q} k^2
+};
 
 // LDS exchange of the time-derivative fluxes of a 2D corner: per node, the
 // NV components of Fh and of Gh stored as double2 pairs in component-major
