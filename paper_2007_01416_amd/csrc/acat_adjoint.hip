@@ -909,18 +909,20 @@ __global__ __launch_bounds__(BLOCK) void k_gather2d(KProb pb, KStep st, const do
     if (e_ != hipSuccess) return e_;         \
   } while (0)
 
-// Every class of a step of P <= 3 with orders up to 2 (HIGH false: two blocks per
-// CU) or with an order 3 (HIGH: one block), in one launch whose blocks share the
-// rounds of all its class lists.  Same arithmetic per corner as a launch per
-// class.  Bound by FP64 issue at one or two waves per SIMD, and a launch per class
-// ended each with most of the card idle: a class of a small grid has fewer rounds
-// than the card has blocks.  The blocks take the rounds in turn, the costliest
-// class first.
-// Whole adjoint step, Euler, launches per class / sets: 192^2 P = 3 276 us / 193,
-// 512^2 P = 3 1738 / 1703, 512^2 P = 2 185 / 176.  P = 4 keeps a launch per class:
-// its rectangles of order 4 run in two launches each, and the body of all
-// others beside them spills.
-template <int P, bool HIGH>
+// The classes of a step of P <= 3 in one launch whose blocks share the rounds of
+// all their lists: those of orders up to 2 (LOW: two blocks per CU), those with
+// an order 3 (HIGH: one block), or each of them (EACH: one).  Same arithmetic per
+// corner as a launch per class.  Bound by FP64 issue at one or two waves per SIMD,
+// and a launch per class ended each with most of the card idle: a class of a
+// small grid has fewer rounds than the card has blocks.  The blocks take the
+// rounds in turn, the costliest class first.  Whole adjoint step, Euler, launches
+// per class / one launch (P = 3 512^2: two): 192^2 P = 3 276 us / 186, 512^2 P = 3
+// 1738 / 1703, 512^2 P = 2 185 / 176.  P = 4 keeps a launch per class: its
+// rectangles of order 4 run in two launches each, and the body of all others
+// beside them spills.
+enum AdjClasses { LOW, HIGH, EACH };
+
+template <int P, AdjClasses S>
 struct AdjSet {
   struct Cls {
     int q1, q2, per_round, stride;
@@ -932,8 +934,8 @@ struct AdjSet {
   }
   static constexpr Cls EVERY[9] = {cls<3, 3>(), cls<2, 3>(), cls<3, 2>(), cls<1, 3>(), cls<3, 1>(),
                                    cls<2, 2>(), cls<1, 2>(), cls<2, 1>(), cls<1, 1>()};   // costliest first
-  static constexpr int FIRST = HIGH ? 0 : (P >= 2 ? 5 : 8);
-  static constexpr int N = HIGH ? (P == 3 ? 5 : 0) : 9 - FIRST;
+  static constexpr int FIRST = S != LOW ? 0 : (P >= 2 ? 5 : 8);
+  static constexpr int N = S == HIGH ? 5 : 9 - FIRST;
   static constexpr Cls at(int k) { return EVERY[FIRST + k]; }
   static constexpr int max_stride() {
     int m = 1;
@@ -947,10 +949,10 @@ struct AdjSet {
   }
 };
 
-template <int FLUX, int NV, int P, bool HIGH>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(HIGH ? 1 : 2))) void k_adj2d_set(
+template <int FLUX, int NV, int P, AdjClasses S>
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(S == LOW ? 2 : 1))) void k_adj2d_set(
     KProb pb, KStep st, const double* __restrict__ ubo, double* __restrict__ C, int LMAX) {
-  using Set = AdjSet<P, HIGH>;
+  using Set = AdjSet<P, S>;
   __shared__ double2 xsm[2 * Xch<NV>::NP * Set::max_stride()];
   __shared__ double gxs[EdgeWeights::first(P + 1)], gys[EdgeWeights::first(P + 1)];
   __shared__ ChunkTable tab;
@@ -998,34 +1000,36 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(HIGH ? 1 
       case 1: run(std::integral_constant<int, 1>{}); break;
       case 2: run(std::integral_constant<int, 2>{}); break;
       case 3: run(std::integral_constant<int, 3>{}); break;
-      default: run(std::integral_constant<int, 4>{}); break;
+      case 4: run(std::integral_constant<int, 4>{}); break;
+      case 5: run(std::integral_constant<int, 5>{}); break;
+      case 6: run(std::integral_constant<int, 6>{}); break;
+      case 7: run(std::integral_constant<int, 7>{}); break;
+      default: run(std::integral_constant<int, 8>{}); break;
     }
     ck.advance(tab);
   }
 }
 
-template <int FLUX, int NV, int P, bool HIGH>
-hipError_t launch_adjset(const KProb& pb, const KStep& st, const double* ubo, double* C, hipStream_t s) {
-  using Set = AdjSet<P, HIGH>;
-  if constexpr (Set::N > 0) {
-    static const std::string name = [] {
-      std::string n = "adjoint2d_";
-      for (int k = 0; k < Set::N; ++k) n += "q" + std::to_string(10 * Set::at(k).q1 + Set::at(k).q2);
-      return n;
-    }();
-    auto kern = k_adj2d_set<FLUX, NV, P, HIGH>;
-    static const int per_cu = [&] {
-      int b = 0;
-      return hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, kern, BLOCK, 0) == hipSuccess && b > 0 ? b : 1;
-    }();
-    const int64_t rounds = pb.n1 * pb.n2 / Set::min_per_round() + NXCD * Set::N;
-    const int grid = persistent_grid(kern, rounds * BLOCK, 0, BLOCK, per_cu);
-    {
-      ProfScope ps(name.c_str(), s);
-      kern<<<grid, BLOCK, 0, s>>>(pb, st, ubo, C, 4 * P * P);
-    }
-    ACAT_CHECK_LAUNCH();
+template <int FLUX, int NV, int P, AdjClasses S>
+hipError_t launch_adjset(const KProb& pb, const KStep& st, const double* ubo, double* C, hipStream_t stream) {
+  using Set = AdjSet<P, S>;
+  static const std::string name = [] {
+    std::string n = "adjoint2d_";
+    for (int k = 0; k < Set::N; ++k) n += "q" + std::to_string(10 * Set::at(k).q1 + Set::at(k).q2);
+    return n;
+  }();
+  auto kern = k_adj2d_set<FLUX, NV, P, S>;
+  static const int per_cu = [&] {
+    int b = 0;
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, kern, BLOCK, 0) == hipSuccess && b > 0 ? b : 1;
+  }();
+  const int64_t rounds = pb.n1 * pb.n2 / Set::min_per_round() + NXCD * Set::N;
+  const int grid = persistent_grid(kern, rounds * BLOCK, 0, BLOCK, per_cu);
+  {
+    ProfScope ps(name.c_str(), stream);
+    kern<<<grid, BLOCK, 0, stream>>>(pb, st, ubo, C, 4 * P * P);
   }
+  ACAT_CHECK_LAUNCH();
   return hipSuccess;
 }
 
@@ -1118,12 +1122,25 @@ hipError_t launch_adjpair2d(const KProb& pb, const KStep& st, const double* ubo,
   return hipSuccess;
 }
 
+// Corners up to which the adjoint of P = 3 takes its classes in one launch.  It saves
+// a launch and its last rounds (192^2 195 us in two, 186 in one; 384^2 933, 927;
+// 512^2 1703, 1692), but runs the low orders at one block per CU instead of two,
+// which a large grid of mostly low orders feels (512^2, noise everywhere: 97.5
+// us in two, 100.9 in one; 192^2 50.3, 46.6).
+constexpr int64_t ADJ_ONE_LAUNCH = 150000;
+
 template <int FLUX, int NV, int P>
 hipError_t adj2d_impl(const KProb& pb, const KStep& st, const double* ubo, double* ubi, double* C, hipStream_t s) {
   hipError_t e;
   if constexpr (P <= 3) {
-    if ((e = launch_adjset<FLUX, NV, P, false>(pb, st, ubo, C, s)) != hipSuccess) return e;
-    if ((e = launch_adjset<FLUX, NV, P, true>(pb, st, ubo, C, s)) != hipSuccess) return e;
+    if (P == 3 && pb.n1 * pb.n2 <= ADJ_ONE_LAUNCH) {
+      if constexpr (P == 3)
+        if ((e = launch_adjset<FLUX, NV, P, EACH>(pb, st, ubo, C, s)) != hipSuccess) return e;
+    } else {
+      if ((e = launch_adjset<FLUX, NV, P, LOW>(pb, st, ubo, C, s)) != hipSuccess) return e;
+      if constexpr (P == 3)
+        if ((e = launch_adjset<FLUX, NV, P, HIGH>(pb, st, ubo, C, s)) != hipSuccess) return e;
+    }
   } else {
     if ((e = launch_adj2d<FLUX, NV, P, 1, 1>(pb, st, ubo, C, s)) != hipSuccess) return e;
     if ((e = launch_adjpair2d<FLUX, NV, P, 1, 2>(pb, st, ubo, C, s)) != hipSuccess) return e;

@@ -1,5 +1,5 @@
-"""The 2D adjoint's set launches (P <= 3: all corner classes in one launch, or in
-two of which the second holds those with an order 3) against the launches per
+"""The 2D adjoint's set launches (P <= 3: all corner classes in one launch, or above
+150000 corners at P = 3 in two, of which the second holds those with an order 3) against the launches per
 class of P = 4, with the same forced orders of at most 3.  Every corner runs the
 same arithmetic in both, so only the gather's summation order and the compiler's
 contraction differ: at most 4 P^2 = 64 contributions of comparable size per cell
@@ -44,7 +44,7 @@ def test_sets_equal_the_launches_per_class(acat, P, kind, bc):
     # corners below, at and above one round of every class (256, 64, 28, 20, 16, 10, 7, ...)
     # and more rounds than resident blocks; "rare": one interface row and column off the
     # common order; "top" / "low": the second / first set only
-    for nx, ny in ((8, 8), (9, 8), (10, 26), (65, 130), (150, 140)):
+    for nx, ny in ((8, 8), (9, 8), (10, 26), (65, 130), (150, 140)) + ((401, 380),) * (P == 3):
         rng = np.random.default_rng(nx * ny + P)
         ext = 0 if bc == "periodic" else 1
         sx, sy = (ny, nx + ext), (ny + ext, nx)
