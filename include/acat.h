@@ -196,7 +196,7 @@ acat_status acat_step_adjoint(const acat_problem* prob, const double* u_in, doub
                               void* workspace, size_t workspace_bytes, void* stream);
 
 /* acat_step_adjoint without its classification and list passes: the
- * order-class map and per-class corner (2D) or interface (1D) lists are
+ * order-class map and, in 2D, the per-class corner lists are
  * read from `step_workspace`, the workspace of the forward step of the same
  * u_in whose decisions `dec` holds (acat_step or acat_step_cfl recording
  * into `dec`, or acat_step_replay of `dec`; Sec. 3 order selection, the

@@ -28,26 +28,29 @@ namespace {
 // contribution buffer, slot-major: C[c][slot][k] with slot = j + P - 1 for the
 // node at offset j in [-P+1, P] of interface k, so that a gather over one
 // offset reads consecutive interfaces
+// An interface of order p on the 2p lanes of its group (grp; wave-local): the
+// adjoint contributions of interface k at its nodes.  xs: the wave's LDS
+// exchange, 2 NV NS doubles.
 template <int FLUX, int NV, int p>
-__global__ __launch_bounds__(BLOCK) void k_adj1d(KProb pb, KStep st, const double* __restrict__ ubo,
-                                                 double* __restrict__ C, int LMAX) {
-  constexpr int L = 2 * p;
-  using Grp = Groups<L>;
-  constexpr int GPB = Grp::PER_BLOCK;
-  constexpr int SL = L + 1;
-  constexpr int NS = Grp::TOTAL * SL;
-  __shared__ double xs[2][NV][NS];
+struct Adj1D {
+  static constexpr int L = 2 * p, SL = L + 1;
+  using Grp = Groups<L, 64>;
+  static_assert(Grp::WAVE_LOCAL, "the exchange needs no block barrier");
+  static constexpr int NS = Grp::TOTAL * SL;
+  static constexpr int LDS_DOUBLES = 2 * NV * NS;
+};
 
-  const Grp grp(threadIdx.x);
-  const int g = grp.g;
-  const int a = grp.node;
+template <int FLUX, int NV, int p>
+__device__ __forceinline__ void adj1d_body(const KProb& pb, const KStep& st, const Groups<2 * p, 64>& grp, bool valid,
+                                           int32_t k, double dt, const double* __restrict__ ubo,
+                                           double* __restrict__ C, double* xs) {
+  constexpr int L = 2 * p, SL = Adj1D<FLUX, NV, p>::SL, NS = Adj1D<FLUX, NV, p>::NS;
+  const int g = grp.g, a = grp.node;
   const int slot = g * SL + a;
-  const bool inblk = grp.in;
-  const double lam = step_dt(st) / pb.dx;
+  const double lam = dt / pb.dx;
   const int64_t nx = pb.nx, nI = pb.nIx;
   const int nx32 = (int)nx;
-  const int64_t cstride = nI * LMAX;
-
+  const int64_t cstride = nI * 2 * pb.P;
   double g1[L], g1T[L];
 #pragma unroll
   for (int l = 0; l < L; ++l) {
@@ -55,175 +58,179 @@ __global__ __launch_bounds__(BLOCK) void k_adj1d(KProb pb, KStep st, const doubl
     g1T[l] = TB.G1[p][l][a];
   }
   const double eta = TB.ETA[p][a];
-
   int buf = 0;
-  const Slice sl(st.counts, st.list, p - 1, GPB);
-  for (int64_t base = sl.lo; base < sl.hi; base += GPB) {
-    const bool valid = inblk && base + g < sl.hi;
-    const int32_t k = valid ? sl.items[base + g] : 0;
-    const int i = k + (int)pb.ioff;
-    const int node = bc_index32(i + (a - p + 1), nx32, pb.bc);
-    double u[NV], Fb[NV];
+  const int i = k + (int)pb.ioff;
+  const int node = bc_index32(i + (a - p + 1), nx32, pb.bc);
+  double u[NV], Fb[NV];
 #pragma unroll
-    for (int c = 0; c < NV; ++c) u[c] = valid ? st.u[c * nx + node] : 1.0;
-    // Fbar = lambda (ubar_{i+1} - ubar_i); a transmissive boundary interface
-    // updates only the cell inside the grid
-    const bool hasR = valid && (pb.bc == PERIODIC || i + 1 < nx32);
-    const bool hasL = valid && i >= 0;
-    const int cr = bc_index32(i + 1, nx32, pb.bc), cl = bc_index32(i, nx32, pb.bc);
+  for (int c = 0; c < NV; ++c) u[c] = valid ? st.u[c * nx + node] : 1.0;
+  // Fbar = lambda (ubar_{i+1} - ubar_i); a transmissive boundary interface
+  // updates only the cell inside the grid
+  const bool hasR = valid && (pb.bc == PERIODIC || i + 1 < nx32);
+  const bool hasL = valid && i >= 0;
+  const int cr = bc_index32(i + 1, nx32, pb.bc), cl = bc_index32(i, nx32, pb.bc);
 #pragma unroll
-    for (int c = 0; c < NV; ++c) {
-      const double ur = hasR ? ubo[c * nx + cr] : 0.0;
-      const double ul = hasL ? ubo[c * nx + cl] : 0.0;
-      Fb[c] = lam * (ur - ul);
-    }
-    double psi = 1.0, al = 0.0;
-    if constexpr (p == 1) {
-      if (valid) {
-        psi = st.psix[k];
-        al = st.alx[k];
-      }
-    }
-    // ---- forward recomputation, keeping U^l at this node
-    double fh0[NV], cur[NV];
-    flux1d<FLUX, NV>(pb.ph, u, fh0);
-#pragma unroll
-    for (int c = 0; c < NV; ++c) cur[c] = fh0[c];
-    double U[L][NV];
-#pragma unroll
-    for (int kk = 2; kk <= 2 * p - 1; ++kk) {   // Fh^{2p-1} is not needed backwards
-#pragma unroll
-      for (int c = 0; c < NV; ++c) xs[buf][c][slot] = cur[c];
-      Grp::sync();
-#pragma unroll
-      for (int c = 0; c < NV; ++c) {
-        double sacc = 0.0;
-#pragma unroll
-        for (int l = 0; l < L; ++l) sacc = fma(g1[l], xs[buf][c][g * SL + l], sacc);
-        U[kk - 1][c] = -lam * sacc;
-      }
-      buf ^= 1;
-      double nxt[NV];
-#pragma unroll
-      for (int c = 0; c < NV; ++c) nxt[c] = 0.0;
-#pragma unroll
-      for (int ri = 0; ri < L; ++ri) {
-        const int r = ri - p + 1;
-        double ph[NV];
-        if (r == 0) {
-#pragma unroll
-          for (int c = 0; c < NV; ++c) ph[c] = fh0[c];
-        } else {
-          double w[NV];
-#pragma unroll
-          for (int c = 0; c < NV; ++c) {
-            double sacc = u[c];
-#pragma unroll
-            for (int l = 1; l <= kk - 1; ++l) sacc = fma(TB.TAYLOR[r + PMAX - 1][l], U[l][c], sacc);
-            w[c] = sacc;
-          }
-          flux1d<FLUX, NV>(pb.ph, w, ph);
-        }
-#pragma unroll
-        for (int c = 0; c < NV; ++c) nxt[c] = fma(TB.GT[p][kk - 1][ri], ph[c], nxt[c]);
-      }
-#pragma unroll
-      for (int c = 0; c < NV; ++c) cur[c] = nxt[c];
-    }
-    // U^{2p-1}
-    if (2 * p >= 2) {
-#pragma unroll
-      for (int c = 0; c < NV; ++c) xs[buf][c][slot] = cur[c];
-      Grp::sync();
-#pragma unroll
-      for (int c = 0; c < NV; ++c) {
-        double sacc = 0.0;
-#pragma unroll
-        for (int l = 0; l < L; ++l) sacc = fma(g1[l], xs[buf][c][g * SL + l], sacc);
-        U[2 * p - 1][c] = -lam * sacc;
-      }
-      buf ^= 1;
-    }
-    // ---- reverse sweep
-    // F = sum_j eta_j S_j, S_j = sum_k Fh^{k-1}_j / k!  =>  Sbar_j = eta_j psi Fbar
-    double sb[NV], ub[NV], f0b[NV], fhb[NV];
-#pragma unroll
-    for (int c = 0; c < NV; ++c) {
-      sb[c] = eta * psi * Fb[c];
-      ub[c] = 0.0;
-      f0b[c] = 0.0;
-      fhb[c] = TB.INVFACT[2 * p] * sb[c];   // Fhbar^{2p-1}
-    }
-    double Ub[L][NV];
-#pragma unroll
-    for (int l = 0; l < L; ++l)
-#pragma unroll
-      for (int c = 0; c < NV; ++c) Ub[l][c] = 0.0;
-#pragma unroll
-    for (int kk = 2 * p; kk >= 2; --kk) {
-      // Fh^{kk-1} = sum_r GT_r phi_r
-#pragma unroll
-      for (int ri = 0; ri < L; ++ri) {
-        const int r = ri - p + 1;
-        double phb[NV];
-#pragma unroll
-        for (int c = 0; c < NV; ++c) phb[c] = TB.GT[p][kk - 1][ri] * fhb[c];
-        if (r == 0) {
-#pragma unroll
-          for (int c = 0; c < NV; ++c) f0b[c] += phb[c];
-        } else {
-          double w[NV], wb[NV];
-#pragma unroll
-          for (int c = 0; c < NV; ++c) {
-            double sacc = u[c];
-#pragma unroll
-            for (int l = 1; l <= kk - 1; ++l) sacc = fma(TB.TAYLOR[r + PMAX - 1][l], U[l][c], sacc);
-            w[c] = sacc;
-            wb[c] = 0.0;
-          }
-          flux1d_vjp<FLUX, NV>(pb.ph, w, phb, wb);
-#pragma unroll
-          for (int c = 0; c < NV; ++c) {
-            ub[c] += wb[c];
-#pragma unroll
-            for (int l = 1; l <= kk - 1; ++l) Ub[l][c] += TB.TAYLOR[r + PMAX - 1][l] * wb[c];
-          }
-        }
-      }
-      // U^{kk-1}_a = -lam sum_l g1[a][l] Fh^{kk-2}_l  =>  Fhbar^{kk-2}_a += -lam sum_j g1[j][a] Ubar_j
-#pragma unroll
-      for (int c = 0; c < NV; ++c) xs[buf][c][slot] = Ub[kk - 1][c];
-      Grp::sync();
-#pragma unroll
-      for (int c = 0; c < NV; ++c) {
-        double sacc = 0.0;
-#pragma unroll
-        for (int j = 0; j < L; ++j) sacc += g1T[j] * xs[buf][c][g * SL + j];
-        fhb[c] = TB.INVFACT[kk - 1] * sb[c] - lam * sacc;   // Fhbar^{kk-2}
-      }
-      buf ^= 1;
-    }
-    // Fh^0 = f(u) also enters every r = 0 term
-#pragma unroll
-    for (int c = 0; c < NV; ++c) f0b[c] += fhb[c];
-    flux1d_vjp<FLUX, NV>(pb.ph, u, f0b, ub);
-    if constexpr (p == 1) {
-      // Rusanov part of the FL-CAT2 blend: (1 - psi) [(f_i + f_{i+1})/2 - alpha/2 (u_{i+1} - u_i)]
-      double lb[NV], zero[NV];
-#pragma unroll
-      for (int c = 0; c < NV; ++c) {
-        lb[c] = 0.5 * (1.0 - psi) * Fb[c];
-        zero[c] = 0.0;
-      }
-      flux1d_vjp<FLUX, NV>(pb.ph, u, lb, zero);
-      const double sp = (pb.flags & FLAG_FLO_LF) ? pb.dx / ((double)pb.dim * step_dt(st)) : al;
-#pragma unroll
-      for (int c = 0; c < NV; ++c) ub[c] += zero[c] + (a == 0 ? sp : -sp) * lb[c];
-    }
+  for (int c = 0; c < NV; ++c) {
+    const double ur = hasR ? ubo[c * nx + cr] : 0.0;
+    const double ul = hasL ? ubo[c * nx + cl] : 0.0;
+    Fb[c] = lam * (ur - ul);
+  }
+  double psi = 1.0, al = 0.0;
+  if constexpr (p == 1) {
     if (valid) {
-#pragma unroll
-      for (int c = 0; c < NV; ++c) C[c * cstride + (int64_t)(a - p + pb.P) * nI + k] = ub[c];
+      psi = st.psix[k];
+      al = st.alx[k];
     }
+  }
+  // ---- forward recomputation, keeping U^l at this node
+  double fh0[NV], cur[NV];
+  flux1d<FLUX, NV>(pb.ph, u, fh0);
+#pragma unroll
+  for (int c = 0; c < NV; ++c) cur[c] = fh0[c];
+  double U[L][NV];
+#pragma unroll
+  for (int kk = 2; kk <= 2 * p - 1; ++kk) {   // Fh^{2p-1} is not needed backwards
+#pragma unroll
+    for (int c = 0; c < NV; ++c) xs[(buf * NV + c) * NS + slot] = cur[c];
+    wave_sync();
+#pragma unroll
+    for (int c = 0; c < NV; ++c) {
+      double sacc = 0.0;
+#pragma unroll
+      for (int l = 0; l < L; ++l) sacc = fma(g1[l], xs[(buf * NV + c) * NS + g * SL + l], sacc);
+      U[kk - 1][c] = -lam * sacc;
+    }
+    buf ^= 1;
+    double nxt[NV];
+#pragma unroll
+    for (int c = 0; c < NV; ++c) nxt[c] = 0.0;
+#pragma unroll
+    for (int ri = 0; ri < L; ++ri) {
+      const int r = ri - p + 1;
+      double ph[NV];
+      if (r == 0) {
+#pragma unroll
+        for (int c = 0; c < NV; ++c) ph[c] = fh0[c];
+      } else {
+        double w[NV];
+#pragma unroll
+        for (int c = 0; c < NV; ++c) {
+          double sacc = u[c];
+#pragma unroll
+          for (int l = 1; l <= kk - 1; ++l) sacc = fma(TB.TAYLOR[r + PMAX - 1][l], U[l][c], sacc);
+          w[c] = sacc;
+        }
+        flux1d<FLUX, NV>(pb.ph, w, ph);
+      }
+#pragma unroll
+      for (int c = 0; c < NV; ++c) nxt[c] = fma(TB.GT[p][kk - 1][ri], ph[c], nxt[c]);
+    }
+#pragma unroll
+    for (int c = 0; c < NV; ++c) cur[c] = nxt[c];
+  }
+  // U^{2p-1}
+  if (2 * p >= 2) {
+#pragma unroll
+    for (int c = 0; c < NV; ++c) xs[(buf * NV + c) * NS + slot] = cur[c];
+    wave_sync();
+#pragma unroll
+    for (int c = 0; c < NV; ++c) {
+      double sacc = 0.0;
+#pragma unroll
+      for (int l = 0; l < L; ++l) sacc = fma(g1[l], xs[(buf * NV + c) * NS + g * SL + l], sacc);
+      U[2 * p - 1][c] = -lam * sacc;
+    }
+    buf ^= 1;
+  }
+  // ---- reverse sweep
+  // F = sum_j eta_j S_j, S_j = sum_k Fh^{k-1}_j / k!  =>  Sbar_j = eta_j psi Fbar
+  double sb[NV], ub[NV], f0b[NV], fhb[NV];
+#pragma unroll
+  for (int c = 0; c < NV; ++c) {
+    sb[c] = eta * psi * Fb[c];
+    ub[c] = 0.0;
+    f0b[c] = 0.0;
+    fhb[c] = TB.INVFACT[2 * p] * sb[c];   // Fhbar^{2p-1}
+  }
+  double Ub[L][NV];
+#pragma unroll
+  for (int l = 0; l < L; ++l)
+#pragma unroll
+    for (int c = 0; c < NV; ++c) Ub[l][c] = 0.0;
+#pragma unroll
+  for (int kk = 2 * p; kk >= 2; --kk) {
+    // as in the 2D recursion: not the forward sweep's predicted states, held from
+    // there to here (registers and scratch of p = 3, 4, 5 in a kernel of its own: 352,
+    // 512 + 472 bytes, 512 + 2180; so 270, 440, 512 + 488).  A scalar's fit up to
+    // p = 6 (Burgers 2e5 cells: P = 4 94 us, opaque 88; P = 5 159, 164; P = 6 402, 411).
+    if constexpr (p >= 2 && (NV > 1 || p <= 4)) {
+#pragma unroll
+      for (int l = 1; l <= kk - 1; ++l)
+#pragma unroll
+        for (int c = 0; c < NV; ++c) asm volatile("" : "+v"(U[l][c]));
+    }
+    // Fh^{kk-1} = sum_r GT_r phi_r
+#pragma unroll
+    for (int ri = 0; ri < L; ++ri) {
+      const int r = ri - p + 1;
+      double phb[NV];
+#pragma unroll
+      for (int c = 0; c < NV; ++c) phb[c] = TB.GT[p][kk - 1][ri] * fhb[c];
+      if (r == 0) {
+#pragma unroll
+        for (int c = 0; c < NV; ++c) f0b[c] += phb[c];
+      } else {
+        double w[NV], wb[NV];
+#pragma unroll
+        for (int c = 0; c < NV; ++c) {
+          double sacc = u[c];
+#pragma unroll
+          for (int l = 1; l <= kk - 1; ++l) sacc = fma(TB.TAYLOR[r + PMAX - 1][l], U[l][c], sacc);
+          w[c] = sacc;
+          wb[c] = 0.0;
+        }
+        flux1d_vjp<FLUX, NV>(pb.ph, w, phb, wb);
+#pragma unroll
+        for (int c = 0; c < NV; ++c) {
+          ub[c] += wb[c];
+#pragma unroll
+          for (int l = 1; l <= kk - 1; ++l) Ub[l][c] += TB.TAYLOR[r + PMAX - 1][l] * wb[c];
+        }
+      }
+    }
+    // U^{kk-1}_a = -lam sum_l g1[a][l] Fh^{kk-2}_l  =>  Fhbar^{kk-2}_a += -lam sum_j g1[j][a] Ubar_j
+#pragma unroll
+    for (int c = 0; c < NV; ++c) xs[(buf * NV + c) * NS + slot] = Ub[kk - 1][c];
+    wave_sync();
+#pragma unroll
+    for (int c = 0; c < NV; ++c) {
+      double sacc = 0.0;
+#pragma unroll
+      for (int j = 0; j < L; ++j) sacc += g1T[j] * xs[(buf * NV + c) * NS + g * SL + j];
+      fhb[c] = TB.INVFACT[kk - 1] * sb[c] - lam * sacc;   // Fhbar^{kk-2}
+    }
+    buf ^= 1;
+  }
+  // Fh^0 = f(u) also enters every r = 0 term
+#pragma unroll
+  for (int c = 0; c < NV; ++c) f0b[c] += fhb[c];
+  flux1d_vjp<FLUX, NV>(pb.ph, u, f0b, ub);
+  if constexpr (p == 1) {
+    // Rusanov part of the FL-CAT2 blend: (1 - psi) [(f_i + f_{i+1})/2 - alpha/2 (u_{i+1} - u_i)]
+    double lb[NV], zero[NV];
+#pragma unroll
+    for (int c = 0; c < NV; ++c) {
+      lb[c] = 0.5 * (1.0 - psi) * Fb[c];
+      zero[c] = 0.0;
+    }
+    flux1d_vjp<FLUX, NV>(pb.ph, u, lb, zero);
+    const double sp = (pb.flags & FLAG_FLO_LF) ? pb.dx / ((double)pb.dim * dt) : al;
+#pragma unroll
+    for (int c = 0; c < NV; ++c) ub[c] += zero[c] + (a == 0 ? sp : -sp) * lb[c];
+  }
+  if (valid) {
+#pragma unroll
+    for (int c = 0; c < NV; ++c) C[c * cstride + (int64_t)(a - p + pb.P) * nI + k] = ub[c];
   }
 }
 
@@ -234,29 +241,38 @@ __global__ __launch_bounds__(BLOCK) void k_adj1d(KProb pb, KStep st, const doubl
 // i + j = m, as nx >= 2P).  Transmissive: the same window, extended to the
 // first (last) interface for the P cells next to the left (right) edge,
 // whose clamped nodes reach them.
-template <int NV>
+template <int NV, int P>
 __global__ __launch_bounds__(BLOCK) void k_gather1d(KProb pb, KStep st, const double* __restrict__ ubo,
-                                                    const double* __restrict__ C, int LMAX, double* ubi) {
+                                                    const double* __restrict__ C, double* ubi) {
   const int m = blockIdx.x * BLOCK + threadIdx.x;
-  const int nx = (int)pb.nx, P = pb.P, ioff = (int)pb.ioff, nI = (int)pb.nIx;
+  const int nx = (int)pb.nx, ioff = (int)pb.ioff, nI = (int)pb.nIx;
   if (m >= nx) return;
-  const int64_t cstride = (int64_t)nI * LMAX;
+  const int64_t cstride = (int64_t)nI * 2 * P;
   const bool per = pb.bc == PERIODIC;
   double acc[NV];
 #pragma unroll
   for (int c = 0; c < NV; ++c) acc[c] = ubo[c * pb.nx + m];
-  const int ilo = (!per && m < P) ? ioff : m - P;
-  const int ihi = (!per && m >= nx - P) ? nx - 1 : m + P - 1;
-  for (int i0 = ilo; i0 <= ihi; ++i0) {
-    const int i = per ? (i0 < 0 ? i0 + nx : (i0 >= nx ? i0 - nx : i0)) : i0;
-    const int k = i - ioff;
-    const int q = st.cls[k] + 1;
-    for (int a = 0; a < 2 * q; ++a) {
-      const int j = a - q + 1;
-      const int node = per ? i0 + j : bc_index32(i0 + j, nx, pb.bc);
-      if (node != m) continue;
+  if (per || (m >= P && m < nx - P)) {
+    // cell m is node j = m - i of interface i alone
+#pragma unroll
+    for (int j = P; j >= -P + 1; --j) {
+      const int i = m - j, k = (per ? (i < 0 ? i + nx : (i >= nx ? i - nx : i)) : i) - ioff;
+      const int q = st.cls[k] + 1;
+      if (j > q || j <= -q) continue;
 #pragma unroll
       for (int c = 0; c < NV; ++c) acc[c] += C[c * cstride + (int64_t)(j + P - 1) * nI + k];
+    }
+  } else {
+    const int ilo = m < P ? ioff : m - P;
+    const int ihi = m >= nx - P ? nx - 1 : m + P - 1;
+    for (int i = ilo; i <= ihi; ++i) {
+      const int q = st.cls[i - ioff] + 1;
+      for (int a = 0; a < 2 * q; ++a) {
+        const int j = a - q + 1;
+        if (bc_index32(i + j, nx, pb.bc) != m) continue;
+#pragma unroll
+        for (int c = 0; c < NV; ++c) acc[c] += C[c * cstride + (int64_t)(j + P - 1) * nI + (i - ioff)];
+      }
     }
   }
 #pragma unroll
@@ -1033,34 +1049,125 @@ hipError_t launch_adjset(const KProb& pb, const KStep& st, const double* ubo, do
   return hipSuccess;
 }
 
-template <int FLUX, int NV, int P, int p>
-hipError_t launch_adj1d(const KProb& pb, const KStep& st, const double* ubo, double* C, hipStream_t s) {
-  if constexpr (p <= P) {
-    static const char* names[7] = {"", "adjoint1d_p1", "adjoint1d_p2", "adjoint1d_p3", "adjoint1d_p4",
-                                   "adjoint1d_p5", "adjoint1d_p6"};
-    auto kern = k_adj1d<FLUX, NV, p>;
-    const int grid = group_grid<2 * p>(kern, pb.nIx, 0);
-    {
-      ProfScope ps(names[p], s);
-      kern<<<grid, BLOCK, 0, s>>>(pb, st, ubo, C, 2 * P);
+// One order of a tile's interfaces: the wave's share of its rounds, the rounds of
+// all orders dealt to the waves in turn.
+template <int FLUX, int NV, int PM, int p>
+__device__ __forceinline__ void adjtile_order(const KProb& pb, const KStep& st, double dt,
+                                              const double* __restrict__ ubo, double* __restrict__ C, double* xs,
+                                              const uint8_t* list, int k0, int first, int count, int& task) {
+  if constexpr (p <= PM) {
+    using Grp = Groups<2 * p, 64>;
+    const int rounds = (count + Grp::PER_BLOCK - 1) / Grp::PER_BLOCK;
+    if (task < rounds) {
+      int lane = __lane_id();   // computed at each order: kept for all at once it would spill
+      asm volatile("" : "+v"(lane), "+v"(dt));
+      const Grp grp(lane);
+      for (; task < rounds; task += NWAVE) {
+        const int it = task * Grp::PER_BLOCK + grp.g;
+        const bool valid = grp.in && it < count;
+        const int32_t k = valid ? k0 + list[first + it] : 0;
+        adj1d_body<FLUX, NV, p>(pb, st, grp, valid, k, dt, ubo, C, xs);
+      }
     }
-    ACAT_CHECK_LAUNCH();
+    task -= rounds;
   }
-  return hipSuccess;
+}
+
+template <int FLUX, int NV, int PM>
+constexpr int adj_xs_doubles() {
+  int m = Adj1D<FLUX, NV, 1>::LDS_DOUBLES;
+  if constexpr (PM > 1) m = std::max(adj_xs_doubles<FLUX, NV, PM - 1>(), Adj1D<FLUX, NV, PM>::LDS_DOUBLES);
+  return m;
+}
+
+// The contributions of a tile of T consecutive interfaces by one block, which groups
+// them by order in LDS (mapped: by the class map, else by the recorded orders,
+// which it writes to the map).  Bound by FP64 issue at the one to three waves per
+// SIMD that the Taylor history of the order leaves (spilled to reach one more it
+// is slower: Burgers P = 6 2e5 cells 411 us in one, 541 in two); small problems by
+// launches, of which lists and a kernel per order took six more.  Recorded step and
+// adjoint, Euler, 30 % noise, by orders / by tiles: 20011 cells P = 3 (and a replayed
+// step) 98 us / 53; 1e6 cells P = 3 609 / 514, P = 4 1976 / 1620, P = 5 10452 / 4982,
+// P = 6 44772 / 10622 (there the opaque history counts most).  Slower only beyond
+// what fills the chip: Burgers P = 6 2e5 cells 389 / 402, 1e6 1303 / 1396, and
+// nothing but order 1 at P = 4, 1e6 cells 143 / 164.
+template <int FLUX, int NV, int P>
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(P <= 2 ? 3 : P == 3 || (NV == 1 && P <= 5) ? 2 : 1))) void k_adj1d(
+    KProb pb, KStep st, int T, int mapped, const double* __restrict__ ubo, double* __restrict__ C) {
+  __shared__ double xs[NWAVE][adj_xs_doubles<FLUX, NV, P>()];
+  __shared__ int wc[P][NWAVE];
+  __shared__ uint8_t list[BLOCK];
+  const int tid = threadIdx.x, lane = __lane_id(), wid = tid >> 6;
+  const int k0 = blockIdx.x * T;
+  const double dt = step_dt(st);
+  int ps = 0;
+  if (tid < T && k0 + tid < pb.nIx) {
+    if (mapped) {
+      ps = st.cls[k0 + tid] + 1;
+    } else {
+      ps = st.ordx[k0 + tid];
+      if (ps < 1 || ps > P) {   // invalid recorded order: taken as 1, flagged
+        ps = 1;
+        atomicOr(st.status, 4u);
+      }
+      st.cls[k0 + tid] = (int8_t)(ps - 1);
+    }
+  }
+  unsigned long long mine = 0ull;
+#pragma unroll
+  for (int p = 1; p <= P; ++p) {
+    const unsigned long long b = __ballot(ps == p);
+    if (ps == p) mine = b;
+    if (lane == 0) wc[p - 1][wid] = __popcll(b);
+  }
+  __syncthreads();
+  int count[P + 1], first[P + 1], run = 0;
+#pragma unroll
+  for (int p = P; p >= 1; --p) {
+    first[p] = run;
+    int pos = run;
+    count[p] = 0;
+#pragma unroll
+    for (int q = 0; q < NWAVE; ++q) {
+      const int n = __builtin_amdgcn_readfirstlane(wc[p - 1][q]);
+      if (q < wid) pos += n;
+      count[p] += n;
+    }
+    if (ps == p) list[pos + __popcll(mine & ((1ull << lane) - 1ull))] = (uint8_t)tid;
+    run += count[p];
+  }
+  __syncthreads();
+  int task = __builtin_amdgcn_readfirstlane(wid);
+  auto order = [&](auto pc) {
+    constexpr int p = decltype(pc)::value;
+    if constexpr (p <= P)
+      adjtile_order<FLUX, NV, P, p>(pb, st, dt, ubo, C, xs[wid], list, k0, first[p], count[p], task);
+  };
+  order(std::integral_constant<int, 6>{});
+  order(std::integral_constant<int, 5>{});
+  order(std::integral_constant<int, 4>{});
+  order(std::integral_constant<int, 3>{});
+  order(std::integral_constant<int, 2>{});
+  order(std::integral_constant<int, 1>{});
 }
 
 template <int FLUX, int NV, int P>
-hipError_t adj1d_impl(const KProb& pb, const KStep& st, const double* ubo, double* ubi, double* C, hipStream_t s) {
-  hipError_t e;
-  if ((e = launch_adj1d<FLUX, NV, P, 1>(pb, st, ubo, C, s)) != hipSuccess) return e;
-  if ((e = launch_adj1d<FLUX, NV, P, 2>(pb, st, ubo, C, s)) != hipSuccess) return e;
-  if ((e = launch_adj1d<FLUX, NV, P, 3>(pb, st, ubo, C, s)) != hipSuccess) return e;
-  if ((e = launch_adj1d<FLUX, NV, P, 4>(pb, st, ubo, C, s)) != hipSuccess) return e;
-  if ((e = launch_adj1d<FLUX, NV, P, 5>(pb, st, ubo, C, s)) != hipSuccess) return e;
-  if ((e = launch_adj1d<FLUX, NV, P, 6>(pb, st, ubo, C, s)) != hipSuccess) return e;
+hipError_t adj1d_impl(const KProb& pb, const KStep& st, bool mapped, const double* ubo, double* ubi, double* C,
+                      hipStream_t s) {
+  auto kern = k_adj1d<FLUX, NV, P>;
+  static const int per_cu = [&] {
+    int b = 0;
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, kern, BLOCK, 0) == hipSuccess && b > 0 ? b : 1;
+  }();
+  const int T = tile_cells<P>(pb.nIx, (int64_t)per_cu * num_cus(), 0, BLOCK);
+  {
+    ProfScope ps("adjoint1d", s);
+    kern<<<(unsigned)((pb.nIx + T - 1) / T), BLOCK, 0, s>>>(pb, st, T, mapped, ubo, C);
+  }
+  ACAT_CHECK_LAUNCH();
   {
     ProfScope ps("gather1d", s);
-    k_gather1d<NV><<<(unsigned)((pb.nx + BLOCK - 1) / BLOCK), BLOCK, 0, s>>>(pb, st, ubo, C, 2 * P, ubi);
+    k_gather1d<NV, P><<<(unsigned)((pb.nx + BLOCK - 1) / BLOCK), BLOCK, 0, s>>>(pb, st, ubo, C, ubi);
   }
   ACAT_CHECK_LAUNCH();
   return hipSuccess;
@@ -1168,35 +1275,35 @@ hipError_t adj2d_impl(const KProb& pb, const KStep& st, const double* ubo, doubl
 
 }  // namespace
 
-hipError_t launch_adjoint(const KProb& pb, const KStep& st, const double* ubo, double* ubi, double* C,
+hipError_t launch_adjoint(const KProb& pb, const KStep& st, bool mapped, const double* ubo, double* ubi, double* C,
                           hipStream_t s) {
   if (pb.dim == 1) {
     if (pb.flux == EUL) {
       switch (pb.P) {
-        case 1: return adj1d_impl<EUL, 3, 1>(pb, st, ubo, ubi, C, s);
-        case 2: return adj1d_impl<EUL, 3, 2>(pb, st, ubo, ubi, C, s);
-        case 3: return adj1d_impl<EUL, 3, 3>(pb, st, ubo, ubi, C, s);
-        case 4: return adj1d_impl<EUL, 3, 4>(pb, st, ubo, ubi, C, s);
-        case 5: return adj1d_impl<EUL, 3, 5>(pb, st, ubo, ubi, C, s);
-        case 6: return adj1d_impl<EUL, 3, 6>(pb, st, ubo, ubi, C, s);
+        case 1: return adj1d_impl<EUL, 3, 1>(pb, st, mapped, ubo, ubi, C, s);
+        case 2: return adj1d_impl<EUL, 3, 2>(pb, st, mapped, ubo, ubi, C, s);
+        case 3: return adj1d_impl<EUL, 3, 3>(pb, st, mapped, ubo, ubi, C, s);
+        case 4: return adj1d_impl<EUL, 3, 4>(pb, st, mapped, ubo, ubi, C, s);
+        case 5: return adj1d_impl<EUL, 3, 5>(pb, st, mapped, ubo, ubi, C, s);
+        case 6: return adj1d_impl<EUL, 3, 6>(pb, st, mapped, ubo, ubi, C, s);
       }
     } else if (pb.flux == BURG) {
       switch (pb.P) {
-        case 1: return adj1d_impl<BURG, 1, 1>(pb, st, ubo, ubi, C, s);
-        case 2: return adj1d_impl<BURG, 1, 2>(pb, st, ubo, ubi, C, s);
-        case 3: return adj1d_impl<BURG, 1, 3>(pb, st, ubo, ubi, C, s);
-        case 4: return adj1d_impl<BURG, 1, 4>(pb, st, ubo, ubi, C, s);
-        case 5: return adj1d_impl<BURG, 1, 5>(pb, st, ubo, ubi, C, s);
-        case 6: return adj1d_impl<BURG, 1, 6>(pb, st, ubo, ubi, C, s);
+        case 1: return adj1d_impl<BURG, 1, 1>(pb, st, mapped, ubo, ubi, C, s);
+        case 2: return adj1d_impl<BURG, 1, 2>(pb, st, mapped, ubo, ubi, C, s);
+        case 3: return adj1d_impl<BURG, 1, 3>(pb, st, mapped, ubo, ubi, C, s);
+        case 4: return adj1d_impl<BURG, 1, 4>(pb, st, mapped, ubo, ubi, C, s);
+        case 5: return adj1d_impl<BURG, 1, 5>(pb, st, mapped, ubo, ubi, C, s);
+        case 6: return adj1d_impl<BURG, 1, 6>(pb, st, mapped, ubo, ubi, C, s);
       }
     } else {
       switch (pb.P) {
-        case 1: return adj1d_impl<ADV, 1, 1>(pb, st, ubo, ubi, C, s);
-        case 2: return adj1d_impl<ADV, 1, 2>(pb, st, ubo, ubi, C, s);
-        case 3: return adj1d_impl<ADV, 1, 3>(pb, st, ubo, ubi, C, s);
-        case 4: return adj1d_impl<ADV, 1, 4>(pb, st, ubo, ubi, C, s);
-        case 5: return adj1d_impl<ADV, 1, 5>(pb, st, ubo, ubi, C, s);
-        case 6: return adj1d_impl<ADV, 1, 6>(pb, st, ubo, ubi, C, s);
+        case 1: return adj1d_impl<ADV, 1, 1>(pb, st, mapped, ubo, ubi, C, s);
+        case 2: return adj1d_impl<ADV, 1, 2>(pb, st, mapped, ubo, ubi, C, s);
+        case 3: return adj1d_impl<ADV, 1, 3>(pb, st, mapped, ubo, ubi, C, s);
+        case 4: return adj1d_impl<ADV, 1, 4>(pb, st, mapped, ubo, ubi, C, s);
+        case 5: return adj1d_impl<ADV, 1, 5>(pb, st, mapped, ubo, ubi, C, s);
+        case 6: return adj1d_impl<ADV, 1, 6>(pb, st, mapped, ubo, ubi, C, s);
       }
     }
   } else {

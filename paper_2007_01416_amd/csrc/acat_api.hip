@@ -224,11 +224,7 @@ acat_status do_step(const acat_problem* prob, const double* u_in, double* u_out,
   hipStream_t s = static_cast<hipStream_t>(stream);
   st.recorded = dec && (dec->order_x || dec->psi1_x || dec->alpha_x ||
                         (k.dim == 2 && (dec->order_y || dec->psi1_y || dec->alpha_y)));
-  // a 1D step none of whose decisions are recorded leaves nothing to read in
-  // the workspace either, and runs by tiles
-  hipError_t e = k.dim == 2               ? launch_step_2d(k, st, 0, s)
-                 : replay || st.recorded ? launch_step_1d(k, st, 0, s)
-                                          : launch_tile_1d(k, st, s);
+  hipError_t e = k.dim == 2 ? launch_step_2d(k, st, 0, s) : launch_step_1d(k, st, s);
   return e == hipSuccess ? ACAT_OK : ACAT_ERR_DEVICE;
 }
 
@@ -485,8 +481,9 @@ acat_status do_adjoint(const acat_problem* prob, const double* u_in, double dt, 
   if (!st.status) return ACAT_ERR_DEVICE;
   st.replay = 1;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  hipError_t e = lists_ws ? hipSuccess : launch_lists(k, st, s);
-  if (e == hipSuccess) e = launch_adjoint(k, st, ubar_out, ubar_in, reinterpret_cast<double*>(w + L.C), s);
+  hipError_t e = lists_ws || k.dim == 1 ? hipSuccess : launch_lists(k, st, s);
+  if (e == hipSuccess)
+    e = launch_adjoint(k, st, lists_ws != nullptr, ubar_out, ubar_in, reinterpret_cast<double*>(w + L.C), s);
   return e == hipSuccess ? ACAT_OK : ACAT_ERR_DEVICE;
 }
 

@@ -1,36 +1,32 @@
-// ACAT forward step on gfx950: classification, per-order-class flux kernels,
-// conservative update, CFL reduction.
+// ACAT 2D forward step on gfx950: classification, flux kernels over the order
+// classes, conservative update; and the CFL reductions of 1D and 2D.
 //
 // Data flow of one step (all on one stream, no host synchronisation):
-//   k_classify*    one thread per 1D interface / 2D corner: smoothness
-//                  indicators psi^p (Sec. 3.2, minimum over components,
-//                  Sec. 3.4), order p_s (Sec. 3, admissible set), and where
-//                  p_s = 1 the superbee weight psi^1 (Sec. 3.1) and the
-//                  Rusanov speed; writes the order (1D) or the corner's
-//                  order class (2D) as one byte, and a per-block histogram
+//   k_classify2d   one thread per corner: smoothness indicators psi^p
+//                  (Sec. 3.2, minimum over components, Sec. 3.4), order p_s
+//                  (Sec. 3, admissible set), and where p_s = 1 the superbee
+//                  weight psi^1 (Sec. 3.1) and the Rusanov speed; writes the
+//                  corner's order class as one byte, and a per-block histogram
 //   k_scan_hist    per-class exclusive prefix of the tile histograms (and,
 //                  in CFL mode, the time step from the classification's
 //                  per-block maxima)
 //   k_scatter      the item lists: every class's items in tile order
 //                  (wave ballots, no global atomics)
-//   k_flux1d<p>    persistent kernels, 1D: one per order class, each block a
-//   k_flux2d       contiguous slice of its class's list; 2D: one or two for
-//                  all classes, whose blocks draw chunks of the class lists.
-//                  A list is processed in rounds, one LANE PER STENCIL NODE: a
-//                  1D interface of order p occupies 2p lanes, a 2D corner of
-//                  orders (q1, q2) 2q1 x 2q2 lanes.  Each lane keeps its
-//                  node's state and Taylor predictions in registers and
-//                  evaluates the flux at its own predicted states; the
-//                  spatial derivatives of the time-derivative fluxes go
-//                  through LDS (Sec. 2.2 recursion, Sec. 4 corner recursion)
-//   k_update*      conservative flux-difference update + status bits
+//   k_flux2d       one or two persistent launches for all classes, whose blocks
+//                  draw chunks of the class lists.  A list is processed in
+//                  rounds, one LANE PER STENCIL NODE: a corner of orders
+//                  (q1, q2) 2q1 x 2q2 lanes.  Each lane keeps its node's state
+//                  and Taylor predictions in registers and evaluates the flux
+//                  at its own predicted states; the spatial derivatives of the
+//                  time-derivative fluxes go through LDS (Sec. 4 corner
+//                  recursion)
+//   k_update2d     conservative flux-difference update + status bits
 #include <hip/hip_runtime.h>
 
 #include <string>
 #include <utility>
 
 #include "acat_internal.hpp"
-#include "cat1d.hpp"
 #include "coeffs.hpp"
 #include "step_common.hpp"
 
@@ -40,115 +36,6 @@ namespace {
 __global__ void k_zero_u64(unsigned long long* p, int n) {
   const int t = threadIdx.x;
   if (t < n) p[t] = 0ull;
-}
-
-// ======================================================================= 1D
-template <int FLUX, int NV, int P>
-__global__ __launch_bounds__(BLOCK) void k_classify1d(KProb pb, KStep st) {
-  constexpr int G = P > 2 ? P : 2;
-  const int64_t k = (int64_t)blockIdx.x * BLOCK + threadIdx.x;
-  const bool valid = k < pb.nIx;
-  int ps = 1;
-  double smax = 0.0;
-  if (valid) {
-    if (st.replay) {
-      ps = st.ordx[k];
-      if (ps < 1 || ps > P) {   // invalid recorded order: fall back to 1, flag it
-        ps = 1;
-        atomicOr(st.status, 4u);
-      }
-    } else {
-      const int64_t i = k + pb.ioff;
-      double v[NV][2 * G];
-#pragma unroll
-      for (int a = 0; a < 2 * G; ++a) {
-        const int64_t node = bc_index(i - G + 1 + a, pb.nx, pb.bc);
-#pragma unroll
-        for (int c = 0; c < NV; ++c) v[c][a] = st.u[c * pb.nx + node];
-      }
-      if (st.cfl_mode) {   // the cell of node 0 (every cell is node 0 of one interface)
-        double uc[NV];
-#pragma unroll
-        for (int c = 0; c < NV; ++c) uc[c] = v[c][G - 1];
-        smax = spectral_radius<FLUX, 1, NV>(pb.ph, uc, 0);
-      }
-      ps = Select<NV, G, P>::run(v, pb.eps, pb.theta, (pb.flags & FLAG_PSI2_MODIFIED) != 0);
-      double psi1 = -1.0, al = -1.0;
-      if (ps == 1) low_order_weights<FLUX, NV, G>(pb.ph, pb.flags, v, psi1, al);
-      st.ordx[k] = (int8_t)ps;
-      st.psix[k] = psi1;
-      st.alx[k] = al;
-    }
-  }
-  if (valid) st.cls[k] = (int8_t)(ps - 1);
-  __shared__ int sh[MAX_CLASSES];
-  block_hist(sh, valid, ps - 1, st.hist);
-  if (st.cfl_mode) {
-    double dummy = 0.0;
-    block_max2(smax, dummy);
-    if (threadIdx.x == 0) st.part[blockIdx.x] = smax;
-  }
-}
-
-// CAT2p flux of the interfaces of order p (p = 1: FL-CAT2 blend).
-template <int FLUX, int NV, int p>
-__global__ __launch_bounds__(BLOCK) void k_flux1d(KProb pb, KStep st) {
-  using Cat = Cat1D<FLUX, NV, p, BLOCK>;
-  __shared__ double xs[Cat::LDS_DOUBLES];
-
-  const Cat cat(threadIdx.x);
-  const double lam = step_dt(st) / pb.dx;
-  const int64_t nx = pb.nx, nI = pb.nIx;
-  const Slice sl(st.counts, st.list, p - 1, Cat::PER_ROUND);
-  for (int64_t base = sl.lo; base < sl.hi; base += Cat::PER_ROUND) {
-    const bool valid = cat.in && base + cat.g < sl.hi;
-    const int32_t k = valid ? sl.items[base + cat.g] : 0;
-    const int i = k + (int)pb.ioff;
-    const int node = bc_index32(i + (cat.a - p + 1), (int)nx, pb.bc);
-    double u[NV];
-#pragma unroll
-    for (int c = 0; c < NV; ++c) u[c] = valid ? st.u[c * nx + node] : 1.0;
-    double Fc[2];
-    cat.flux(pb.ph, u, lam, xs, Fc[0], Fc[1]);
-    if (!valid) continue;
-#pragma unroll
-    for (int task = 0; task < (NV > Cat::L ? 2 : 1); ++task) {
-      const int c = cat.a + task * Cat::L;
-      if (c >= NV) continue;
-      double F = Fc[task];
-      if constexpr (p == 1) {
-        const int64_t nl = bc_index32(i, (int)nx, pb.bc), nr = bc_index32(i + 1, (int)nx, pb.bc);
-        double uL[NV], uR[NV];
-#pragma unroll
-        for (int cc = 0; cc < NV; ++cc) {
-          uL[cc] = st.u[cc * nx + nl];
-          uR[cc] = st.u[cc * nx + nr];
-        }
-        F = fl_cat2<FLUX, NV>(pb.ph, pb.flags, uL, uR, c, F, st.psix[k], st.alx[k],
-                              pb.dx / ((double)pb.dim * step_dt(st)));
-      }
-      st.Fx[c * nI + k] = F;
-    }
-  }
-}
-
-template <int FLUX, int NV>
-__global__ __launch_bounds__(BLOCK) void k_update1d(KProb pb, KStep st) {
-  const int64_t i = (int64_t)blockIdx.x * BLOCK + threadIdx.x;
-  if (i >= pb.nx) return;
-  const double lam = step_dt(st) / pb.dx;
-  const int64_t kr = i - pb.ioff;
-  const int64_t kl = (pb.bc == PERIODIC) ? (i == 0 ? pb.nx - 1 : i - 1) : i;
-  double w[NV];
-  bool finite = true;
-#pragma unroll
-  for (int c = 0; c < NV; ++c) {
-    w[c] = st.u[c * pb.nx + i] + lam * (st.Fx[c * pb.nIx + kl] - st.Fx[c * pb.nIx + kr]);
-    st.uout[c * pb.nx + i] = w[c];
-    finite = finite && isfinite(w[c]);
-  }
-  uint32_t bad = (finite ? 0u : 1u) | (physical<FLUX, 1, NV>(pb.ph, w) ? 0u : 2u);
-  if (bad) atomicOr(st.status, bad);
 }
 
 // ======================================================================= 2D
@@ -897,61 +784,6 @@ CflReduce cfl_reduce(const KProb& pb, const KStep& st, int nparts) {
     if (e_ != hipSuccess) return e_;         \
   } while (0)
 
-template <int FLUX, int NV, int P, int p>
-hipError_t launch_class1d(const KProb& pb, const KStep& st, int cap, hipStream_t s) {
-  if constexpr (p <= P) {
-    static const char* names[7] = {"", "flux1d_p1", "flux1d_p2", "flux1d_p3", "flux1d_p4", "flux1d_p5",
-                                   "flux1d_p6"};
-    auto kern = k_flux1d<FLUX, NV, p>;
-    const int grid = group_grid<2 * p>(kern, pb.nIx, cap);
-    {
-      ProfScope ps(names[p], s);
-      kern<<<grid, BLOCK, 0, s>>>(pb, st);
-    }
-    ACAT_CHECK_LAUNCH();
-  }
-  return hipSuccess;
-}
-
-// classification (or, in replay, the recorded orders) -> class map, then the
-// per-class item lists
-template <int FLUX, int NV, int P>
-hipError_t lists1d_impl(const KProb& pb, const KStep& st, hipStream_t s) {
-  const int64_t nI = pb.nIx;
-  const int cblocks = (int)((nI + BLOCK - 1) / BLOCK);
-  {
-    ProfScope ps("classify1d", s);
-    k_classify1d<FLUX, NV, P><<<cblocks, BLOCK, 0, s>>>(pb, st);
-  }
-  ACAT_CHECK_LAUNCH();
-  {
-    ProfScope ps("class_lists", s);
-    k_scan_hist<<<P + (st.cfl_mode ? 1 : 0), SCAN_T, 0, s>>>(st.hist, cblocks, st.offs, st.counts, P,
-                                                            cfl_reduce(pb, st, cblocks));
-    k_scatter<P, false><<<cblocks, BLOCK, 0, s>>>(st.cls, 0, nI, 1, cblocks, st.offs, st.counts, st.list);
-  }
-  ACAT_CHECK_LAUNCH();
-  return hipSuccess;
-}
-
-template <int FLUX, int NV, int P>
-hipError_t step1d_impl(const KProb& pb, const KStep& st, int cap, hipStream_t s) {
-  hipError_t e;
-  if ((e = lists1d_impl<FLUX, NV, P>(pb, st, s)) != hipSuccess) return e;
-  if ((e = launch_class1d<FLUX, NV, P, 1>(pb, st, cap, s)) != hipSuccess) return e;
-  if ((e = launch_class1d<FLUX, NV, P, 2>(pb, st, cap, s)) != hipSuccess) return e;
-  if ((e = launch_class1d<FLUX, NV, P, 3>(pb, st, cap, s)) != hipSuccess) return e;
-  if ((e = launch_class1d<FLUX, NV, P, 4>(pb, st, cap, s)) != hipSuccess) return e;
-  if ((e = launch_class1d<FLUX, NV, P, 5>(pb, st, cap, s)) != hipSuccess) return e;
-  if ((e = launch_class1d<FLUX, NV, P, 6>(pb, st, cap, s)) != hipSuccess) return e;
-  {
-    ProfScope ps("update1d", s);
-    k_update1d<FLUX, NV><<<(unsigned)((pb.nx + BLOCK - 1) / BLOCK), BLOCK, 0, s>>>(pb, st);
-  }
-  ACAT_CHECK_LAUNCH();
-  return hipSuccess;
-}
-
 // The classes of one launch (ClassSet).
 template <int FLUX, int NV, int P, Blocks B, bool SQUARE>
 hipError_t launch_flux2d(const KProb& pb, const KStep& st, int cap, hipStream_t s) {
@@ -1035,39 +867,6 @@ hipError_t step2d_impl(const KProb& pb, const KStep& st, int cap, hipStream_t s)
 
 }  // namespace
 
-hipError_t launch_step_1d(const KProb& pb, const KStep& st, int grid_blocks, hipStream_t s) {
-  const int cap = grid_blocks;
-  if (pb.flux == EUL) {
-    switch (pb.P) {
-      case 1: return step1d_impl<EUL, 3, 1>(pb, st, cap, s);
-      case 2: return step1d_impl<EUL, 3, 2>(pb, st, cap, s);
-      case 3: return step1d_impl<EUL, 3, 3>(pb, st, cap, s);
-      case 4: return step1d_impl<EUL, 3, 4>(pb, st, cap, s);
-      case 5: return step1d_impl<EUL, 3, 5>(pb, st, cap, s);
-      case 6: return step1d_impl<EUL, 3, 6>(pb, st, cap, s);
-    }
-  } else if (pb.flux == BURG) {
-    switch (pb.P) {
-      case 1: return step1d_impl<BURG, 1, 1>(pb, st, cap, s);
-      case 2: return step1d_impl<BURG, 1, 2>(pb, st, cap, s);
-      case 3: return step1d_impl<BURG, 1, 3>(pb, st, cap, s);
-      case 4: return step1d_impl<BURG, 1, 4>(pb, st, cap, s);
-      case 5: return step1d_impl<BURG, 1, 5>(pb, st, cap, s);
-      case 6: return step1d_impl<BURG, 1, 6>(pb, st, cap, s);
-    }
-  } else {
-    switch (pb.P) {
-      case 1: return step1d_impl<ADV, 1, 1>(pb, st, cap, s);
-      case 2: return step1d_impl<ADV, 1, 2>(pb, st, cap, s);
-      case 3: return step1d_impl<ADV, 1, 3>(pb, st, cap, s);
-      case 4: return step1d_impl<ADV, 1, 4>(pb, st, cap, s);
-      case 5: return step1d_impl<ADV, 1, 5>(pb, st, cap, s);
-      case 6: return step1d_impl<ADV, 1, 6>(pb, st, cap, s);
-    }
-  }
-  return hipErrorInvalidValue;
-}
-
 hipError_t launch_step_2d(const KProb& pb, const KStep& st, int grid_blocks, hipStream_t s) {
   const int cap = grid_blocks;
   if (pb.flux == EUL) {
@@ -1089,36 +888,7 @@ hipError_t launch_step_2d(const KProb& pb, const KStep& st, int grid_blocks, hip
 }
 
 hipError_t launch_lists(const KProb& pb, const KStep& st, hipStream_t s) {
-  if (pb.dim == 1) {
-    if (pb.flux == EUL) {
-      switch (pb.P) {
-        case 1: return lists1d_impl<EUL, 3, 1>(pb, st, s);
-        case 2: return lists1d_impl<EUL, 3, 2>(pb, st, s);
-        case 3: return lists1d_impl<EUL, 3, 3>(pb, st, s);
-        case 4: return lists1d_impl<EUL, 3, 4>(pb, st, s);
-        case 5: return lists1d_impl<EUL, 3, 5>(pb, st, s);
-        case 6: return lists1d_impl<EUL, 3, 6>(pb, st, s);
-      }
-    } else if (pb.flux == BURG) {
-      switch (pb.P) {
-        case 1: return lists1d_impl<BURG, 1, 1>(pb, st, s);
-        case 2: return lists1d_impl<BURG, 1, 2>(pb, st, s);
-        case 3: return lists1d_impl<BURG, 1, 3>(pb, st, s);
-        case 4: return lists1d_impl<BURG, 1, 4>(pb, st, s);
-        case 5: return lists1d_impl<BURG, 1, 5>(pb, st, s);
-        case 6: return lists1d_impl<BURG, 1, 6>(pb, st, s);
-      }
-    } else {
-      switch (pb.P) {
-        case 1: return lists1d_impl<ADV, 1, 1>(pb, st, s);
-        case 2: return lists1d_impl<ADV, 1, 2>(pb, st, s);
-        case 3: return lists1d_impl<ADV, 1, 3>(pb, st, s);
-        case 4: return lists1d_impl<ADV, 1, 4>(pb, st, s);
-        case 5: return lists1d_impl<ADV, 1, 5>(pb, st, s);
-        case 6: return lists1d_impl<ADV, 1, 6>(pb, st, s);
-      }
-    }
-  } else if (pb.flux == EUL) {
+  if (pb.flux == EUL) {
     switch (pb.P) {
       case 1: return lists2d_impl<EUL, 4, 1>(pb, st, s);
       case 2: return lists2d_impl<EUL, 4, 2>(pb, st, s);

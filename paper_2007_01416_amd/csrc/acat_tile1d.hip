@@ -1,7 +1,10 @@
 // The 1D step by tiles: one launch for a given time step, two for a CFL step
 // (the wave-speed maxima, then the tiles), instead of one launch per pass and
-// order class.  Taken when the caller records no decisions; a step whose
-// decisions or class lists are read afterwards runs pass by pass.
+// order class.  Where decisions are recorded or given, the tiles also write the
+// class map and their interfaces per order, which one more launch adds up to the
+// class counts (a single tile writes those itself): three launches where a
+// launch per pass and class took P + 4 (Euler 20011 cells P = 3, a recorded step,
+// a replayed one and the adjoint: 98 -> 53 us with the adjoint by tiles too).
 #include <hip/hip_runtime.h>
 
 #include "acat_internal.hpp"
@@ -43,7 +46,7 @@ __global__ __launch_bounds__(BLOCK) void k_speed1d(KProb pb, const double* __res
 // 0, from the one tile that holds the whole problem.
 // Four waves per SIMD up to P = 5 (bounded to 128 registers there, 137
 // unbounded: 3e5 cells 218 -> 206 us per step), three at P = 6 (159).
-template <int FLUX, int NV, int P>
+template <int FLUX, int NV, int P, bool DEC>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(P <= 5 ? 4 : 3))) void k_tile1d(
     KProb pb, KStep st, int T, int nparts) {
   __shared__ TileMem<FLUX, NV, P> m;
@@ -78,42 +81,33 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(P <= 5 ? 
     __syncthreads();
   }
   double w[NV];
-  tile_step<FLUX, NV, P, false>(m, t, pb.ph, pb.flags, pb.eps, pb.theta, dt, st.status, w);
+  const TileDec dec{st.ordx, st.psix, st.alx, st.cls, gridDim.x == 1 ? st.counts : st.list, st.replay != 0};
+  tile_step<FLUX, NV, P, false, DEC>(m, t, pb.ph, pb.flags, pb.eps, pb.theta, dt, st.status, w, dec);
 }
 
-// Cells per tile: 4 GPW r - 1, whose interfaces are r rounds for each of the
-// block's four waves (GPW interfaces of order P per round).  A tile costs its
-// r rounds and 0.55 of one for staging, classification and update; the nb
-// tiles pass over the chip (`resident` blocks at once) nb / resident times
-// and half a pass more until the last ones end.  The r of the least
-// (nb / resident + 0.5) (r + 0.55) is within 2 % of the fastest measured r
-// (1, 2, 3, 4, 6, 8, 12) at orders 4 to 12 and 4e3 to 1e6 cells; e.g. P = 4:
-// 4096 cells r = 1 (15.8 us per step; r = 2 20.9), 65536 cells r = 2 (36.7;
-// r = 1 39.1, r = 4 47.3), P = 6, 1e6 cells r = 8 (961; r = 1 1449).
-template <int P>
-int tile_cells(int64_t n, int64_t resident) {
-  constexpr int per = NWAVE * Groups<2 * P, 64>::PER_BLOCK, rmax = BLOCK / per;
-  int best = 1;
-  double cost = 1e300;
-  for (int r = 1; r <= rmax; ++r) {
-    const int64_t nb = (n + per * r - 2) / (per * r - 1);
-    const double c = ((double)nb / (double)resident + 0.5) * (r + 0.55);
-    if (c < cost) {
-      cost = c;
-      best = r;
-    }
+// counts[c] = the sum of class c over the tiles; one block per class
+__global__ __launch_bounds__(BLOCK) void k_sum_counts(const int32_t* tiles, int ntiles, int32_t* counts) {
+  __shared__ int ws[NWAVE];
+  int n = 0;
+  for (int i = threadIdx.x; i < ntiles; i += BLOCK) n += tiles[(int64_t)blockIdx.x * ntiles + i];
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) n += __shfl_xor(n, off);
+  if (__lane_id() == 0) ws[threadIdx.x >> 6] = n;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < NWAVE; ++w) n += ws[w];
+    counts[blockIdx.x] = n;
   }
-  return per * best - 1;
 }
 
-template <int FLUX, int NV, int P>
+template <int FLUX, int NV, int P, bool DEC>
 hipError_t tile1d_impl(const KProb& pb, const KStep& st, hipStream_t s) {
-  auto kern = k_tile1d<FLUX, NV, P>;
+  auto kern = k_tile1d<FLUX, NV, P, DEC>;
   static const int per_cu = [&] {
     int b = 0;
     return hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, kern, BLOCK, 0) == hipSuccess && b > 0 ? b : 1;
   }();
-  int T = tile_cells<P>(pb.nx, (int64_t)per_cu * num_cus()), nparts = 0;
+  int T = tile_cells<P>(pb.nx, (int64_t)per_cu * num_cus(), 1, BLOCK), nparts = 0;
   if (st.cfl_mode) {
     // a problem of up to four rounds per wave in one block: the block reduces
     // the wave speeds itself (one launch)
@@ -128,43 +122,58 @@ hipError_t tile1d_impl(const KProb& pb, const KStep& st, hipStream_t s) {
     }
   }
   const int64_t nb = (pb.nx + T - 1) / T;
+  // the tiles' counts, P for each, lie where a 2D step has its item lists, at least
+  // nx entries: with T >= 2 P and nx >= 2 P, P ceil(nx / T) <= nx (one tile: P <= nx;
+  // more: nx > T, and P (nx / T + 1) <= nx as (T + 1)(T - P) >= P T)
+  static_assert(NWAVE * Groups<2 * P, 64>::PER_BLOCK - 1 >= 2 * P, "the tiles' counts fit the list");
   {
     ProfScope ps("step1d", s);
     kern<<<(unsigned)nb, BLOCK, 0, s>>>(pb, st, T, nparts);
   }
   ACAT_CHECK_LAUNCH();
+  if (DEC && nb > 1) {
+    ProfScope ps("class_counts", s);
+    k_sum_counts<<<P, BLOCK, 0, s>>>(st.list, (int)nb, st.counts);
+    ACAT_CHECK_LAUNCH();
+  }
   return hipSuccess;
+}
+
+template <int FLUX, int NV, int P>
+hipError_t tile1d_mode(const KProb& pb, const KStep& st, hipStream_t s) {
+  return st.replay || st.recorded ? tile1d_impl<FLUX, NV, P, true>(pb, st, s)
+                                  : tile1d_impl<FLUX, NV, P, false>(pb, st, s);
 }
 
 }  // namespace
 
-hipError_t launch_tile_1d(const KProb& pb, const KStep& st, hipStream_t s) {
+hipError_t launch_step_1d(const KProb& pb, const KStep& st, hipStream_t s) {
   if (pb.flux == EUL) {
     switch (pb.P) {
-      case 1: return tile1d_impl<EUL, 3, 1>(pb, st, s);
-      case 2: return tile1d_impl<EUL, 3, 2>(pb, st, s);
-      case 3: return tile1d_impl<EUL, 3, 3>(pb, st, s);
-      case 4: return tile1d_impl<EUL, 3, 4>(pb, st, s);
-      case 5: return tile1d_impl<EUL, 3, 5>(pb, st, s);
-      case 6: return tile1d_impl<EUL, 3, 6>(pb, st, s);
+      case 1: return tile1d_mode<EUL, 3, 1>(pb, st, s);
+      case 2: return tile1d_mode<EUL, 3, 2>(pb, st, s);
+      case 3: return tile1d_mode<EUL, 3, 3>(pb, st, s);
+      case 4: return tile1d_mode<EUL, 3, 4>(pb, st, s);
+      case 5: return tile1d_mode<EUL, 3, 5>(pb, st, s);
+      case 6: return tile1d_mode<EUL, 3, 6>(pb, st, s);
     }
   } else if (pb.flux == BURG) {
     switch (pb.P) {
-      case 1: return tile1d_impl<BURG, 1, 1>(pb, st, s);
-      case 2: return tile1d_impl<BURG, 1, 2>(pb, st, s);
-      case 3: return tile1d_impl<BURG, 1, 3>(pb, st, s);
-      case 4: return tile1d_impl<BURG, 1, 4>(pb, st, s);
-      case 5: return tile1d_impl<BURG, 1, 5>(pb, st, s);
-      case 6: return tile1d_impl<BURG, 1, 6>(pb, st, s);
+      case 1: return tile1d_mode<BURG, 1, 1>(pb, st, s);
+      case 2: return tile1d_mode<BURG, 1, 2>(pb, st, s);
+      case 3: return tile1d_mode<BURG, 1, 3>(pb, st, s);
+      case 4: return tile1d_mode<BURG, 1, 4>(pb, st, s);
+      case 5: return tile1d_mode<BURG, 1, 5>(pb, st, s);
+      case 6: return tile1d_mode<BURG, 1, 6>(pb, st, s);
     }
   } else {
     switch (pb.P) {
-      case 1: return tile1d_impl<ADV, 1, 1>(pb, st, s);
-      case 2: return tile1d_impl<ADV, 1, 2>(pb, st, s);
-      case 3: return tile1d_impl<ADV, 1, 3>(pb, st, s);
-      case 4: return tile1d_impl<ADV, 1, 4>(pb, st, s);
-      case 5: return tile1d_impl<ADV, 1, 5>(pb, st, s);
-      case 6: return tile1d_impl<ADV, 1, 6>(pb, st, s);
+      case 1: return tile1d_mode<ADV, 1, 1>(pb, st, s);
+      case 2: return tile1d_mode<ADV, 1, 2>(pb, st, s);
+      case 3: return tile1d_mode<ADV, 1, 3>(pb, st, s);
+      case 4: return tile1d_mode<ADV, 1, 4>(pb, st, s);
+      case 5: return tile1d_mode<ADV, 1, 5>(pb, st, s);
+      case 6: return tile1d_mode<ADV, 1, 6>(pb, st, s);
     }
   }
   return hipErrorInvalidValue;

@@ -443,6 +443,36 @@ struct Groups {
   }
 };
 
+constexpr int NWAVE = BLOCK / 64;
+
+// Cells per tile: 4 GPW r - 1, whose interfaces are r rounds for each of the
+// block's four waves (GPW interfaces of order P per round).  A tile costs its
+// r rounds and 0.55 of one for staging, classification and update; the nb
+// tiles pass over the chip (`resident` blocks at once) nb / resident times
+// and half a pass more until the last ones end.  The r of the least
+// (nb / resident + 0.5) (r + 0.55) is within 2 % of the fastest measured r
+// (1, 2, 3, 4, 6, 8, 12) at orders 4 to 12 and 4e3 to 1e6 cells; e.g. P = 4:
+// 4096 cells r = 1 (15.8 us per step; r = 2 20.9), 65536 cells r = 2 (36.7;
+// r = 1 39.1, r = 4 47.3), P = 6, 1e6 cells r = 8 (961; r = 1 1449).
+// shared: interfaces of a tile that the next one computes too (the step: 1);
+// limit: most interfaces of a tile.
+template <int P>
+int tile_cells(int64_t n, int64_t resident, int shared, int limit) {
+  constexpr int per = NWAVE * Groups<2 * P, 64>::PER_BLOCK;
+  const int rmax = limit / per;
+  int best = 1;
+  double cost = 1e300;
+  for (int r = 1; r <= rmax; ++r) {
+    const int64_t nb = (n + per * r - shared - 1) / (per * r - shared);
+    const double c = ((double)nb / (double)resident + 0.5) * (r + 0.55);
+    if (c < cost) {
+      cost = c;
+      best = r;
+    }
+  }
+  return per * best - shared;
+}
+
 // v, the same in every lane of the wave, in a scalar register
 template <class T>
 __device__ __forceinline__ T wave_uniform(T v) {

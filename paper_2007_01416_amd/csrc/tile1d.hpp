@@ -22,8 +22,6 @@
 namespace acat {
 namespace {
 
-constexpr int NWAVE = BLOCK / 64;
-
 // doubles of LDS one wave's exchange takes, the largest over the orders 1..PM
 template <int FLUX, int NV, int PM>
 constexpr int wave_xs_doubles() {
@@ -57,6 +55,18 @@ struct Tile {
   int64_t stride, n, c0;
   int T, P, bc;
   double dx;
+};
+
+// The decisions of a tile's interfaces: given (replay), or chosen and written; the
+// class map and the tile's interfaces per order, counts[(p - 1) ntiles + tile],
+// written in both.
+struct TileDec {
+  int8_t* ord;
+  double* psi;
+  double* al;
+  int8_t* cls;
+  int32_t* counts;
+  bool replay;
 };
 
 // Stages cells c0 - G .. c0 + T + G - 1 through the boundary map, as far as
@@ -131,17 +141,33 @@ __device__ __forceinline__ void tile_order(TileMem<FLUX, NV, PM>& m, const Phys&
 // Classifies, computes the fluxes and updates a staged tile (after the
 // barrier that follows tile_load).  RT: the largest half-width is t.P <= PM
 // (run time), else PM.  w: the new state of cell threadIdx.x of the tile;
-// returns whether the thread has one.
-template <int FLUX, int NV, int PM, bool RT>
+// returns whether the thread has one.  DEC: with the decisions of dec.
+template <int FLUX, int NV, int PM, bool RT, bool DEC = false>
 __device__ __forceinline__ bool tile_step(TileMem<FLUX, NV, PM>& m, const Tile& t, const Phys& ph, int flags,
-                                          double eps, double theta, double dt, uint32_t* status, double (&w)[NV]) {
+                                          double eps, double theta, double dt, uint32_t* status, double (&w)[NV], const TileDec& dec = {}) {
   constexpr int G = TileMem<FLUX, NV, PM>::G;
   const int tid = threadIdx.x, lane = __lane_id(), wid = tid >> 6;
   const double lam = dt / t.dx;
   // interface k: between cells c0 - 1 + k and c0 + k
   const bool valid = tid <= t.T && t.c0 + tid <= t.n;
   int ps = 0;
-  if (valid) {
+  // the tile that holds the interface's left cell writes its decisions (the
+  // first tile also those of a boundary interface to the left of all cells)
+  [[maybe_unused]] const bool own = valid && (tid >= 1 || (t.c0 == 0 && t.bc != PERIODIC));
+  [[maybe_unused]] const int64_t x = t.bc == PERIODIC ? (t.c0 + tid == 0 ? t.n : t.c0 + tid) - 1 : t.c0 + tid;
+  if (DEC && dec.replay) {
+    if (valid) {
+      ps = dec.ord[x];
+      if (ps < 1 || ps > PM) {   // invalid recorded order: taken as 1, flagged
+        ps = 1;
+        if (own) atomicOr(status, 4u);
+      }
+      if (ps == 1) {
+        m.psi[tid] = dec.psi[x];
+        m.al[tid] = dec.al[x];
+      }
+    }
+  } else if (valid) {
     double v[NV][2 * G];
 #pragma unroll
     for (int a = 0; a < 2 * G; ++a)
@@ -149,8 +175,19 @@ __device__ __forceinline__ bool tile_step(TileMem<FLUX, NV, PM>& m, const Tile& 
       for (int c = 0; c < NV; ++c) v[c][a] = m.u[c][tid + a];
     if constexpr (RT) ps = SelectRT<NV, G, PM>::run(v, t.P, eps, theta);
     else ps = Select<NV, G, PM>::run(v, eps, theta, (flags & FLAG_PSI2_MODIFIED) != 0);
-    if (ps == 1) low_order_weights<FLUX, NV, G>(ph, flags, v, m.psi[tid], m.al[tid]);
+    double psi = -1.0, al = -1.0;
+    if (ps == 1) {
+      low_order_weights<FLUX, NV, G>(ph, flags, v, psi, al);
+      m.psi[tid] = psi;
+      m.al[tid] = al;
+    }
+    if (DEC && own) {
+      dec.ord[x] = (int8_t)ps;
+      dec.psi[x] = psi;
+      dec.al[x] = al;
+    }
   }
+  if (DEC && own) dec.cls[x] = (int8_t)(ps - 1);
   unsigned long long mine = 0ull;
 #pragma unroll
   for (int p = 1; p <= PM; ++p) {
@@ -173,6 +210,11 @@ __device__ __forceinline__ bool tile_step(TileMem<FLUX, NV, PM>& m, const Tile& 
     }
     if (ps == p) m.list[pos + __popcll(mine & ((1ull << lane) - 1ull))] = (uint8_t)tid;
     run += count[p];
+  }
+  if (DEC && tid == 0) {
+#pragma unroll
+    for (int p = 1; p <= PM; ++p)
+      dec.counts[(p - 1) * (int64_t)gridDim.x + blockIdx.x] = count[p] - (ps == p && !own ? 1 : 0);
   }
   __syncthreads();
   const double alf = t.dx / dt;
