@@ -7,9 +7,10 @@
 //                  (Sec. 3, admissible set), and where p_s = 1 the superbee
 //                  weight psi^1 (Sec. 3.1) and the Rusanov speed; writes the
 //                  corner's order class as one byte, and a per-block histogram
-//   k_scan_hist    per-class exclusive prefix of the tile histograms (and,
-//                  in CFL mode, the time step from the classification's
-//                  per-block maxima)
+//   k_scan_hist    large grids: per-class exclusive prefix of the tile
+//                  histograms (and, in CFL mode, the time step from the
+//                  classification's per-block maxima); small grids: a part
+//                  of k_scatter
 //   k_scatter      the item lists: every class's items in tile order
 //                  (wave ballots, no global atomics)
 //   k_flux2d       one or two persistent launches for all classes, whose blocks
@@ -827,6 +828,15 @@ hipError_t launch_classes2d(const KProb& pb, const KStep& st, int cap, hipStream
   return e != hipSuccess ? e : launch_flux2d<FLUX, NV, P, TWO, SQUARE>(pb, st, cap, s);
 }
 
+// Tiles up to which the list kernel sums the class histograms itself instead of
+// reading the prefix that one launch more makes.  Each block then reads the
+// histograms of all tiles (from L2), work that grows with the tiles' square.  Whole
+// step, Euler, two launches / one: 64^2 P = 3 25.3 us / 24.3, 128^2 P = 2 23.8 / 21.4,
+// 400^2 P = 2 (625 tiles) 70.5 / 68.4, P = 4 578 / 578, 512^2 P = 1 40.5 / 38.7; beyond
+// the line 640^2 P = 2 (1600) 146.5 / 145.3.  The loads go eight at a time: one by
+// one 800^2 took 222 us, against 209 in two launches.
+constexpr int LISTS_ONE_LAUNCH = 1024;
+
 template <int FLUX, int NV, int P>
 hipError_t lists2d_impl(const KProb& pb, const KStep& st, hipStream_t s) {
   const int cblocks = (int)class_tiles(pb);
@@ -837,14 +847,19 @@ hipError_t lists2d_impl(const KProb& pb, const KStep& st, hipStream_t s) {
   ACAT_CHECK_LAUNCH();
   {
     ProfScope ps("class_lists", s);
-    k_scan_hist<<<P * P + (st.cfl_mode ? 1 : 0), SCAN_T, 0, s>>>(st.hist, cblocks, st.offs, st.counts, P * P,
-                                                                cfl_reduce(pb, st, cblocks), st.tickets);
-    if (pb.flags & FLAG_SQUARE_2D)
-      k_scatter<P * P, true, true><<<cblocks, BLOCK, 0, s>>>(st.cls, 0, pb.n1, pb.n2, cblocks, st.offs, st.counts,
-                                                              st.list, P);
-    else
-      k_scatter<P * P, true><<<cblocks, BLOCK, 0, s>>>(st.cls, 0, pb.n1, pb.n2, cblocks, st.offs, st.counts,
-                                                        st.list);
+    const bool square = (pb.flags & FLAG_SQUARE_2D) != 0;
+    const CflReduce cr = cfl_reduce(pb, st, cblocks);
+    if (cblocks <= LISTS_ONE_LAUNCH) {
+      auto kern = square ? k_scatter<P * P, true, true, true> : k_scatter<P * P, true, false, true>;
+      kern<<<cblocks + (st.cfl_mode ? 1 : 0), BLOCK, 0, s>>>(st.cls, 0, pb.n1, pb.n2, cblocks, st.offs, st.counts,
+                                                             st.list, P, st.hist, st.tickets, cr);
+    } else {
+      k_scan_hist<<<P * P + (st.cfl_mode ? 1 : 0), SCAN_T, 0, s>>>(st.hist, cblocks, st.offs, st.counts, P * P, cr,
+                                                                  st.tickets);
+      auto kern = square ? k_scatter<P * P, true, true> : k_scatter<P * P, true>;
+      kern<<<cblocks, BLOCK, 0, s>>>(st.cls, 0, pb.n1, pb.n2, cblocks, st.offs, st.counts, st.list, P, nullptr,
+                                     nullptr, {});
+    }
   }
   ACAT_CHECK_LAUNCH();
   return hipSuccess;

@@ -214,6 +214,35 @@ struct CflReduce {
   double* dt_out;
 };
 
+// the time step of cr from its partial maxima, by a block of T threads
+template <int T>
+__device__ __forceinline__ void cfl_reduce_block(const CflReduce& cr) {
+  __shared__ double wmax[2][T / 64];
+  const int tid = threadIdx.x, lane = __lane_id(), wid = tid >> 6;
+  double m0 = 0.0, m1 = 0.0;
+  for (int i = tid; i < cr.nparts; i += T) {
+    m0 = fmax(m0, cr.part[cr.dim * i]);
+    if (cr.dim == 2) m1 = fmax(m1, cr.part[2 * i + 1]);
+  }
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) {
+    m0 = fmax(m0, __shfl_xor(m0, off));
+    m1 = fmax(m1, __shfl_xor(m1, off));
+  }
+  if (lane == 0) {
+    wmax[0][wid] = m0;
+    wmax[1][wid] = m1;
+  }
+  __syncthreads();
+  if (tid == 0) {
+    for (int w = 1; w < T / 64; ++w) {
+      m0 = fmax(m0, wmax[0][w]);
+      m1 = fmax(m1, wmax[1][w]);
+    }
+    cfl_rule(cr.dim, cr.dx, cr.dy, m0, m1, cr.cfl, cr.t_final, cr.t_dev, cr.dt_out);
+  }
+}
+
 constexpr int SCAN_T = 1024;   // threads of the class-list prefix kernel
 
 // offs[c][t] = items of class c in tiles < t, counts[c] = total: one block per
@@ -224,31 +253,9 @@ __global__ __launch_bounds__(SCAN_T) void k_scan_hist(const int32_t* hist, int n
                                                       int32_t* counts, int ncls, CflReduce cr,
                                                       int32_t* tickets = nullptr) {
   __shared__ int wsum[SCAN_T / 64];
-  __shared__ double wmax[2][SCAN_T / 64];
   const int c = blockIdx.x, tid = threadIdx.x, lane = __lane_id(), wid = tid >> 6;
-  if (c == ncls) {   // time step
-    double m0 = 0.0, m1 = 0.0;
-    for (int i = tid; i < cr.nparts; i += SCAN_T) {
-      m0 = fmax(m0, cr.part[cr.dim * i]);
-      if (cr.dim == 2) m1 = fmax(m1, cr.part[2 * i + 1]);
-    }
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-      m0 = fmax(m0, __shfl_xor(m0, off));
-      m1 = fmax(m1, __shfl_xor(m1, off));
-    }
-    if (lane == 0) {
-      wmax[0][wid] = m0;
-      wmax[1][wid] = m1;
-    }
-    __syncthreads();
-    if (tid == 0) {
-      for (int w = 1; w < SCAN_T / 64; ++w) {
-        m0 = fmax(m0, wmax[0][w]);
-        m1 = fmax(m1, wmax[1][w]);
-      }
-      cfl_rule(cr.dim, cr.dx, cr.dy, m0, m1, cr.cfl, cr.t_final, cr.t_dev, cr.dt_out);
-    }
+  if (c == ncls) {
+    cfl_reduce_block<SCAN_T>(cr);
     return;
   }
   if (tickets && tid < NXCD) tickets[(c * NXCD + tid) * TICKET_STRIDE] = 0;
@@ -292,11 +299,53 @@ __global__ __launch_bounds__(SCAN_T) void k_scan_hist(const int32_t* hist, int n
 // SQUARE (2D square-stencil variant, map = pair class of order square_P): a
 // corner with q1 != q2 is listed in the square classes (q1, q1), tagged F
 // only, and (q2, q2), tagged G only.  No atomics, deterministic.
-template <int NCLS, bool TILED, bool SQUARE = false>
+// SCAN: the block also sums the histograms itself, those of the tiles before its
+// own and all of them, and needs no k_scan_hist before it; block 0 writes the
+// counts and clears the tickets, and with cr.part one block more writes the time
+// step.
+template <int NCLS, bool TILED, bool SQUARE = false, bool SCAN = false>
 __global__ __launch_bounds__(BLOCK) void k_scatter(const int8_t* map, int map_bias, int64_t n1, int64_t n2,
-                                                   int ntiles, const int32_t* offs, const int32_t* counts,
-                                                   int32_t* list, int square_P = 0) {
+                                                   int ntiles, const int32_t* offs, int32_t* counts,
+                                                   int32_t* list, int square_P = 0, const int32_t* hist = nullptr,
+                                                   int32_t* tickets = nullptr, CflReduce cr = {}) {
   __shared__ int wc[NCLS][BLOCK / 64];
+  __shared__ int before[SCAN ? NCLS : 1], total[SCAN ? NCLS : 1];
+  if constexpr (SCAN) {
+    if ((int)blockIdx.x == ntiles) {
+      cfl_reduce_block<BLOCK>(cr);
+      return;
+    }
+    constexpr int NW = BLOCK / 64;
+    const int w = threadIdx.x >> 6;
+#pragma unroll
+    for (int k = 0; k < (NCLS + NW - 1) / NW; ++k) {
+      const int c = k * NW + w;
+      if (c < NCLS) {
+        int all = 0, low = 0;
+        for (int t0 = __lane_id(); t0 < ntiles; t0 += 8 * 64) {   // eight loads in flight
+#pragma unroll
+          for (int n = 0; n < 8; ++n) {
+            const int t = t0 + n * 64;
+            const int v = t < ntiles ? hist[(int64_t)c * ntiles + t] : 0;
+            all += v;
+            low += t < (int)blockIdx.x ? v : 0;
+          }
+        }
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) {
+          all += __shfl_xor(all, off);
+          low += __shfl_xor(low, off);
+        }
+        if (__lane_id() == 0) {
+          before[c] = low;
+          total[c] = all;
+          if (blockIdx.x == 0) counts[c] = all;
+        }
+      }
+    }
+    if (tickets && blockIdx.x == 0)
+      for (int i = threadIdx.x; i < NCLS * NXCD; i += BLOCK) tickets[i * TICKET_STRIDE] = 0;
+  }
   int64_t e;
   bool inside;
   if constexpr (TILED) {
@@ -337,8 +386,13 @@ __global__ __launch_bounds__(BLOCK) void k_scatter(const int8_t* map, int map_bi
     const int c = cs[s];
     if (c < 0 || c >= NCLS) continue;
     int64_t pos = 0;
-    for (int k = 0; k < c; ++k) pos += counts[k];
-    pos += offs[(int64_t)c * (ntiles + 1) + blockIdx.x];
+    if constexpr (SCAN) {
+      for (int k = 0; k < c; ++k) pos += total[k];
+      pos += before[c];
+    } else {
+      for (int k = 0; k < c; ++k) pos += counts[k];
+      pos += offs[(int64_t)c * (ntiles + 1) + blockIdx.x];
+    }
     for (int w = 0; w < wid; ++w) pos += wc[c][w];
     pos += __popcll(ms[s] & ((1ull << lane) - 1ull));
     list[pos] = (int32_t)(e | ((int64_t)ts[s] << LIST_TAG_SHIFT));

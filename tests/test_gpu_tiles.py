@@ -1,5 +1,5 @@
-"""The 1D step by tiles (no decisions recorded) against the step pass by pass
-(decisions recorded), and the batched step by tiles against the one with a
+"""The 1D step by tiles (no decisions recorded) against the step that
+records them, and the batched step by tiles against the one with a
 launch per order class: the same operations per interface, so the same bits.
 Sizes around the edges of a tile: the smallest grids, one cell more or less
 than a tile and than the block that steps a whole problem, grids of several
