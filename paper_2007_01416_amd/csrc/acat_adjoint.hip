@@ -1080,6 +1080,11 @@ constexpr int adj_xs_doubles() {
   return m;
 }
 
+template <int NV, int P>
+constexpr int adj1d_waves() {
+  return P <= 2 ? 3 : P == 3 || (NV == 1 && P <= 5) ? 2 : 1;
+}
+
 // The contributions of a tile of T consecutive interfaces by one block, which groups
 // them by order in LDS (mapped: by the class map, else by the recorded orders,
 // which it writes to the map).  Bound by FP64 issue at the one to three waves per
@@ -1092,7 +1097,7 @@ constexpr int adj_xs_doubles() {
 // what fills the chip: Burgers P = 6 2e5 cells 389 / 402, 1e6 1303 / 1396, and
 // nothing but order 1 at P = 4, 1e6 cells 143 / 164.
 template <int FLUX, int NV, int P>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(P <= 2 ? 3 : P == 3 || (NV == 1 && P <= 5) ? 2 : 1))) void k_adj1d(
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(adj1d_waves<NV, P>()))) void k_adj1d(
     KProb pb, KStep st, int T, int mapped, const double* __restrict__ ubo, double* __restrict__ C) {
   __shared__ double xs[NWAVE][adj_xs_doubles<FLUX, NV, P>()];
   __shared__ int wc[P][NWAVE];

@@ -144,7 +144,8 @@ __device__ __forceinline__ void tile_order(TileMem<FLUX, NV, PM>& m, const Phys&
 // returns whether the thread has one.  DEC: with the decisions of dec.
 template <int FLUX, int NV, int PM, bool RT, bool DEC = false>
 __device__ __forceinline__ bool tile_step(TileMem<FLUX, NV, PM>& m, const Tile& t, const Phys& ph, int flags,
-                                          double eps, double theta, double dt, uint32_t* status, double (&w)[NV], const TileDec& dec = {}) {
+                                          double eps, double theta, double dt, uint32_t* status, double (&w)[NV],
+                                          const TileDec& dec = {}) {
   constexpr int G = TileMem<FLUX, NV, PM>::G;
   const int tid = threadIdx.x, lane = __lane_id(), wid = tid >> 6;
   const double lam = dt / t.dx;
