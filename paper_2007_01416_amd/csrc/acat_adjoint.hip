@@ -60,7 +60,7 @@ __device__ __forceinline__ void adj1d_body(const KProb& pb, const KStep& st, con
   const double eta = TB.ETA[p][a];
   int buf = 0;
   const int i = k + (int)pb.ioff;
-  const int node = bc_index32(i + (a - p + 1), nx32, pb.bc);
+  const int node = bc_node32(i, a - p + 1, nx32, pb.bc);
   double u[NV], Fb[NV];
 #pragma unroll
   for (int c = 0; c < NV; ++c) u[c] = valid ? st.u[c * nx + node] : 1.0;
@@ -256,7 +256,7 @@ __global__ __launch_bounds__(BLOCK) void k_gather1d(KProb pb, KStep st, const do
     // cell m is node j = m - i of interface i alone
 #pragma unroll
     for (int j = P; j >= -P + 1; --j) {
-      const int i = m - j, k = (per ? (i < 0 ? i + nx : (i >= nx ? i - nx : i)) : i) - ioff;
+      const int k = bc_node32(m, -j, nx, PERIODIC) - ioff;   // transmissive: an interior cell, nothing wraps
       const int q = st.cls[k] + 1;
       if (j > q || j <= -q) continue;
 #pragma unroll
@@ -269,7 +269,7 @@ __global__ __launch_bounds__(BLOCK) void k_gather1d(KProb pb, KStep st, const do
       const int q = st.cls[i - ioff] + 1;
       for (int a = 0; a < 2 * q; ++a) {
         const int j = a - q + 1;
-        if (bc_index32(i + j, nx, pb.bc) != m) continue;
+        if (bc_node32(i, j, nx, pb.bc) != m) continue;
 #pragma unroll
         for (int c = 0; c < NV; ++c) acc[c] += C[c * cstride + (int64_t)(j + P - 1) * nI + (i - ioff)];
       }
@@ -1103,19 +1103,19 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(adj1d_wav
   __shared__ int wc[P][NWAVE];
   __shared__ uint8_t list[BLOCK];
   const int tid = threadIdx.x, lane = __lane_id(), wid = tid >> 6;
-  const int k0 = blockIdx.x * T;
+  const int32_t k0 = tile_item(blockIdx.x, T, 0, pb.nIx), k = tile_item(blockIdx.x, T, tid, pb.nIx);
   const double dt = step_dt(st);
   int ps = 0;
-  if (tid < T && k0 + tid < pb.nIx) {
+  if (k >= 0) {
     if (mapped) {
-      ps = st.cls[k0 + tid] + 1;
+      ps = st.cls[k] + 1;
     } else {
-      ps = st.ordx[k0 + tid];
+      ps = st.ordx[k];
       if (ps < 1 || ps > P) {   // invalid recorded order: taken as 1, flagged
         ps = 1;
         atomicOr(st.status, 4u);
       }
-      st.cls[k0 + tid] = (int8_t)(ps - 1);
+      st.cls[k] = (int8_t)(ps - 1);
     }
   }
   unsigned long long mine = 0ull;

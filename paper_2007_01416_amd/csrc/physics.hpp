@@ -240,6 +240,14 @@ __device__ __forceinline__ int bc_index32(int i, int n, int bc) {
   return i < 0 ? 0 : (i >= n ? n - 1 : i);
 }
 
+// bc_index32 of node i + off (|off| < n) without forming the sum: n may be so
+// close to 2^31 that it does not fit an int.
+__device__ __forceinline__ int bc_node32(int i, int off, int n, int bc) {
+  const bool above = off > 0 && i >= n - off;
+  if (bc == PERIODIC) return above ? i - (n - off) : (i < -off ? i + (off + n) : i + off);
+  return above ? n - 1 : (i < -off ? 0 : i + off);
+}
+
 // Variants of the method (acat_problem.flags; ACAT_FLAG_* in acat.h).
 enum { FLAG_FLO_LF = 1, FLAG_FLO_HLL = 2, FLAG_PSI2_MODIFIED = 4, FLAG_PSI1_ROE = 8, FLAG_SQUARE_2D = 16 };
 

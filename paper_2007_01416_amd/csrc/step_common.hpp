@@ -527,6 +527,13 @@ int tile_cells(int64_t n, int64_t resident, int shared, int limit) {
   return per * best - shared;
 }
 
+// The item of lane `lane` of tile `tile`, for tiles of T of n items (n < 2^31); -1
+// beyond the tile or the last item.  The last tile may end past 2^31.
+__device__ __forceinline__ int32_t tile_item(uint32_t tile, int T, int lane, int64_t n) {
+  const int64_t k = (int64_t)tile * T + lane;
+  return lane < T && k < n ? (int32_t)k : -1;
+}
+
 // v, the same in every lane of the wave, in a scalar register
 template <class T>
 __device__ __forceinline__ T wave_uniform(T v) {
