@@ -7,6 +7,7 @@
 
 #include "../../include/acat.h"
 #include "acat_internal.hpp"
+#include "batch_tiles.hpp"
 
 namespace acat {
 void copy_tables(int p, double* g1, double* gt, double* eta, double* tau);
@@ -560,22 +561,9 @@ acat_status acat_batch_init(const acat_batch* batch, void* workspace, size_t wor
     for (int64_t k = ioffs[b]; k < ioffs[b + 1]; ++k) pif[k] = b;
     for (int64_t e = coff[b]; e < coff[b + 1]; ++e) pcell[e] = b;
   }
-  // tiles, the problems of the highest P first
-  int32_t* tile = reinterpret_cast<int32_t*>(host.data() + (L.tiles - L.coff));
-  int32_t* tfirst = reinterpret_cast<int32_t*>(host.data() + (L.tfirst - L.coff));
-  int32_t* tcount = reinterpret_cast<int32_t*>(host.data() + (L.tcount - L.coff));
-  int32_t nt = 0;
-  for (int q = BATCH_PMAX; q >= 1; --q)
-    for (int b = 0; b < np; ++b) {
-      if (P[b] != q) continue;
-      tfirst[b] = nt;
-      for (int64_t c0 = 0; c0 < batch->n[b]; c0 += L.T[q], ++nt) {
-        tile[4 * (int64_t)nt] = b;
-        tile[4 * (int64_t)nt + 1] = (int32_t)c0;
-        tile[4 * (int64_t)nt + 2] = L.T[q];
-      }
-      tcount[b] = nt - tfirst[b];
-    }
+  batch_tiles(np, batch->n, batch->P, L.T, reinterpret_cast<int32_t*>(host.data() + (L.tiles - L.coff)),
+              reinterpret_cast<int32_t*>(host.data() + (L.tfirst - L.coff)),
+              reinterpret_cast<int32_t*>(host.data() + (L.tcount - L.coff)));
   char* w = static_cast<char*>(workspace);
   if (hipMemcpy(w + L.coff, host.data(), host.size(), hipMemcpyHostToDevice) != hipSuccess) return ACAT_ERR_DEVICE;
   return ACAT_OK;

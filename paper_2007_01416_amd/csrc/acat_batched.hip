@@ -150,8 +150,7 @@ __global__ __launch_bounds__(BLOCK) void k_update_b(KBatch bt, KBStep st) {
 }
 
 // The whole step of one tile of one problem per block; CFL: and the largest
-// spectral radius of its new cells (NaN and -0 count as +0).  The tiles of
-// the highest orders come first, so that the launch ends on short ones.
+// spectral radius of its new cells (NaN and -0 count as +0), in the tile's slot.
 template <int FLUX, int NV, bool CFL>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void k_tile_b(KBatch bt, KBStep st) {
   __shared__ TileMem<FLUX, NV, BATCH_PMAX> m;
@@ -166,7 +165,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void
   const bool has = tile_step<FLUX, NV, BATCH_PMAX, true>(m, t, bt.ph, 0, bt.eps, bt.theta, dt, st.status, w);
   if constexpr (CFL) {
     const double s = block_max(has ? speed_floor(spectral_radius<FLUX, 1, NV>(bt.ph, w, 0)) : 0.0, m.red);
-    if (threadIdx.x == 0) st.tmax[blockIdx.x] = s;
+    if (threadIdx.x == 0) st.tmax[tl[3]] = s;
   }
 }
 

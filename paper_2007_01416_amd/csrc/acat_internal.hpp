@@ -120,8 +120,8 @@ struct KBatch {
   int waves[BATCH_PMAX + 1];    // per order class p: waves per block of the flux kernel (1, 2 or 4)
   int per_cu[BATCH_PMAX + 1];   // per order class p: persistent blocks per CU (0: occupancy limit)
   int by_tiles;                 // the whole step in one launch over the tiles, instead of one pass after another
-  const int32_t* tiles;         // [ntiles][4] problem, first cell, cells, 0; the highest P first
-  const int32_t* tfirst;        // [nprob] first tile of each problem
+  const int32_t* tiles;         // [ntiles][4] problem, first cell, cells, slot, in launch order (batch_tiles)
+  const int32_t* tfirst;        // [nprob] slot of the first tile of each problem
   const int32_t* tcount;        // [nprob] its number of tiles
   int ntiles;
 };
@@ -146,7 +146,7 @@ struct KBStep {
   // the next time steps dt_next[b] = cfl dx[b] / max and clears smax
   unsigned long long* smax;
   double* wmax;             // [ceil(ncell / 64)]
-  double* tmax;             // [ntiles] by tiles: the maximum of each tile
+  double* tmax;             // [ntiles] by tiles: the maximum of each tile, by slot
   double* dt_next;
   double cfl;
 };
