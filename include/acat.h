@@ -227,9 +227,9 @@ acat_status acat_cfl_dt(const acat_problem* prob, const double* smax_dev, double
  * Batched step: nprob independent 1D problems with one flux, each with its
  * own cell count n[b], largest half-width P[b], boundary bc[b], spacing
  * dx[b] and time step dt[b], advanced together (one launch over tiles of all
- * problems, or, with a launch table below, one classification launch and one
- * persistent flux launch per order class).  Per problem
- * the result equals acat_step bit for bit.
+ * problems, or, with a launch table below or for thousands of problems of a
+ * few dozen cells, one classification launch and persistent flux launches by
+ * order class).  Per problem the result equals acat_step bit for bit.
  *   States: SoA over the concatenated cells, u[var][coff_b + i] with
  *   coff_b = n[0] + ... + n[b-1] (total C cells: arrays of nvar * C).
  * The descriptor is a host struct of host arrays; acat_batch_init copies
@@ -248,11 +248,13 @@ typedef struct {
   const int32_t* bc;    /* host [nprob] ACAT_BC_*                              */
   const double* dx;     /* host [nprob] > 0                                    */
   /* host [8] or NULL.  NULL: the whole step in one launch of 256-thread
-   * blocks, one per tile of a problem.  A table: one launch per order class
-   * p = 1..4 with the shape of entries 2(p-1) and 2(p-1)+1 = waves per block
-   * (1, 2 or 4; 0 = 4) and persistent blocks per CU (0 = the occupancy limit,
-   * else 1..32).  Every choice gives the same results bit for bit; the
-   * autotuner chooses by timing. */
+   * blocks, one per tile of a problem; where thousands of very small problems
+   * would leave most of those blocks idle, passes over the interfaces of all
+   * problems, the highest order's fluxes in one launch and the others' in
+   * another.  A table: passes with one launch per order class p = 1..4 with the
+   * shape of entries 2(p-1) and 2(p-1)+1 = waves per block (1, 2 or 4; 0 = 4)
+   * and persistent blocks per CU (0 = the occupancy limit, else 1..32).  Every
+   * choice gives the same results bit for bit; the autotuner chooses by timing. */
   const int32_t* launch;
 } acat_batch;
 

@@ -1,6 +1,7 @@
 """Autotuner of the batched step's launch shapes.
 
-By default the batched step is one launch over tiles of its problems.  The
+By default the batched step is one launch over tiles of its problems (passes
+over all of their interfaces where thousands of them are very small).  The
 alternative is one launch per order class p, whose flux kernel's shape is a
 number of waves per block (1, 2 or 4: 64, 128 or 256 threads, i.e. 32p ...
 128/p interfaces per block round) and a number of persistent blocks per CU

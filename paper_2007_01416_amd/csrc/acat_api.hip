@@ -290,23 +290,12 @@ acat_status check_batch(const acat_batch* bt) {
   return ACAT_OK;
 }
 
-// Cells per tile of a batched problem: 4 GPW r - 1 (r rounds of order P for
-// each of a block's four waves, as in a single problem), r as large as leaves
-// the batch some 4096 tiles, four times what the chip holds at once, so that
-// the tiles dealt out last fill its gaps.
-int batch_tile_cells(int P, int64_t ncell) {
-  const int gpw = P == 3 ? 10 : 32 / P, per = 4 * gpw;
-  const int64_t r = ncell / ((int64_t)per * 4096);
-  const int rmax = BLOCK / per;
-  return per * (int)(r < 1 ? 1 : r > rmax ? rmax : r) - 1;
-}
-
 struct BLayout {
   size_t hdr, coff, ioffs, N, P, bc, dx, pif, pcell, tiles, tfirst, tcount, smax, ord, psi, al, wmax, tmax, F, hist,
       offs, list, total;
-  int64_t ncell, nif, ntiles;
+  int64_t ncell, nif;
   int Pmax;
-  int T[BATCH_PMAX + 1];   // cells per tile of the problems of half-width P
+  BatchSplit split;
 };
 
 BLayout blayout(const acat_batch* bt) {
@@ -319,8 +308,7 @@ BLayout blayout(const acat_batch* bt) {
     if (bt->P[b] > L.Pmax) L.Pmax = bt->P[b];
   }
   const int64_t tiles = (L.nif + BLOCK - 1) / BLOCK;
-  for (int P = 1; P <= BATCH_PMAX; ++P) L.T[P] = batch_tile_cells(P, L.ncell);
-  for (int b = 0; b < np; ++b) L.ntiles += (bt->n[b] + L.T[bt->P[b]] - 1) / L.T[bt->P[b]];
+  L.split = batch_split(np, bt->n, bt->P, bt->nvar);
   size_t o = 0;
   L.hdr = o;   o += align_up(sizeof(int32_t) * MAX_CLASSES);
   L.coff = o;  o += align_up(sizeof(int64_t) * (np + 1));
@@ -331,7 +319,7 @@ BLayout blayout(const acat_batch* bt) {
   L.dx = o;    o += align_up(sizeof(double) * np);
   L.pif = o;   o += align_up(sizeof(int32_t) * L.nif);
   L.pcell = o; o += align_up(sizeof(int32_t) * L.ncell);
-  L.tiles = o; o += align_up(sizeof(int32_t) * 4 * L.ntiles);
+  L.tiles = o; o += align_up(sizeof(int32_t) * 4 * L.split.ntiles);
   L.tfirst = o; o += align_up(sizeof(int32_t) * np);
   L.tcount = o; o += align_up(sizeof(int32_t) * np);
   L.smax = o;  o += align_up(sizeof(double) * np);
@@ -339,7 +327,7 @@ BLayout blayout(const acat_batch* bt) {
   L.psi = o;   o += align_up(sizeof(double) * L.nif);
   L.al = o;    o += align_up(sizeof(double) * L.nif);
   L.wmax = o;  o += align_up(sizeof(double) * ((L.ncell + 63) / 64));
-  L.tmax = o;  o += align_up(sizeof(double) * L.ntiles);
+  L.tmax = o;  o += align_up(sizeof(double) * L.split.ntiles);
   L.F = o;     o += align_up(sizeof(double) * bt->nvar * L.nif);
   L.hist = o;  o += align_up(sizeof(int32_t) * MAX_CLASSES * tiles);
   L.offs = o;  o += align_up(sizeof(int32_t) * MAX_CLASSES * (tiles + 1));
@@ -374,11 +362,12 @@ KBatch make_kbatch(const acat_batch* bt, const BLayout& L, char* w) {
     k.waves[p] = bt->launch && bt->launch[2 * (p - 1)] > 0 ? bt->launch[2 * (p - 1)] : 4;
     k.per_cu[p] = bt->launch ? bt->launch[2 * (p - 1) + 1] : 0;
   }
-  k.by_tiles = bt->launch ? 0 : 1;
+  k.two_launches = !bt->launch;
+  k.by_tiles = !bt->launch && L.split.by_tiles;
   k.tiles = reinterpret_cast<const int32_t*>(w + L.tiles);
   k.tfirst = reinterpret_cast<const int32_t*>(w + L.tfirst);
   k.tcount = reinterpret_cast<const int32_t*>(w + L.tcount);
-  k.ntiles = (int)L.ntiles;
+  k.ntiles = (int)L.split.ntiles;
   k.waves[0] = 4;
   k.per_cu[0] = 0;
   return k;
@@ -561,7 +550,7 @@ acat_status acat_batch_init(const acat_batch* batch, void* workspace, size_t wor
     for (int64_t k = ioffs[b]; k < ioffs[b + 1]; ++k) pif[k] = b;
     for (int64_t e = coff[b]; e < coff[b + 1]; ++e) pcell[e] = b;
   }
-  batch_tiles(np, batch->n, batch->P, L.T, reinterpret_cast<int32_t*>(host.data() + (L.tiles - L.coff)),
+  batch_tiles(np, batch->n, batch->P, L.split.T, reinterpret_cast<int32_t*>(host.data() + (L.tiles - L.coff)),
               reinterpret_cast<int32_t*>(host.data() + (L.tfirst - L.coff)),
               reinterpret_cast<int32_t*>(host.data() + (L.tcount - L.coff)));
   char* w = static_cast<char*>(workspace);

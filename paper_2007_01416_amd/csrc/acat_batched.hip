@@ -4,8 +4,8 @@
 // grouped into per-order work lists shared by all problems, and each order
 // class is one persistent launch over every problem, so the small problems
 // of a batch fill the GPU together.  That is the path of a batch with a launch
-// table; without one the whole step is one launch over tiles of the problems
-// (tile1d.hpp).  Per interface the arithmetic is that of the single-problem
+// table, or of very many very small problems; else the whole step is one launch
+// over tiles of the problems (tile1d.hpp; the line: batch_split).  Per interface the arithmetic is that of the single-problem
 // kernels (same rounding), so a batched step equals the per-problem steps bit
 // for bit.
 //
@@ -53,11 +53,10 @@ __global__ __launch_bounds__(BLOCK) void k_classify_b(KBatch bt, KBStep st) {
   block_hist(sh, valid, ps - 1, st.hist);
 }
 
-// Interfaces of order p of every problem, BS threads per block.
+// Interfaces of order p of every problem, BS threads per block; xs: LDS, LDS_DOUBLES.
 template <int FLUX, int NV, int p, int BS>
-__global__ __launch_bounds__(BS) void k_flux_b(KBatch bt, KBStep st) {
+__device__ __forceinline__ void flux_b_body(const KBatch& bt, const KBStep& st, double* xs) {
   using Cat = Cat1D<FLUX, NV, p, BS>;
-  __shared__ double xs[Cat::LDS_DOUBLES];
   const Cat cat(threadIdx.x);
   const Slice sl(st.counts, st.list, p - 1, Cat::PER_ROUND);
   for (int64_t base = sl.lo; base < sl.hi; base += Cat::PER_ROUND) {
@@ -93,6 +92,30 @@ __global__ __launch_bounds__(BS) void k_flux_b(KBatch bt, KBStep st) {
       st.F[c * bt.nif + kg] = F;
     }
   }
+}
+
+template <int FLUX, int NV, int p, int BS>
+__global__ __launch_bounds__(BS) void k_flux_b(KBatch bt, KBStep st) {
+  __shared__ double xs[Cat1D<FLUX, NV, p, BS>::LDS_DOUBLES];
+  flux_b_body<FLUX, NV, p, BS>(bt, st, xs);
+}
+
+// The orders below PM in one launch (a batch without a launch table): every block
+// runs its share of each list in turn.
+template <int FLUX, int NV, int PM>
+__global__ __launch_bounds__(BLOCK) void k_flux_low_b(KBatch bt, KBStep st) {
+  constexpr int a = Cat1D<FLUX, NV, 1, BLOCK>::LDS_DOUBLES, b = Cat1D<FLUX, NV, 2, BLOCK>::LDS_DOUBLES;
+  constexpr int c = Cat1D<FLUX, NV, 3, BLOCK>::LDS_DOUBLES;
+  __shared__ double xs[a > b ? (a > c ? a : c) : (b > c ? b : c)];
+  if constexpr (PM > 3) {
+    flux_b_body<FLUX, NV, 3, BLOCK>(bt, st, xs);
+    __syncthreads();
+  }
+  if constexpr (PM > 2) {
+    flux_b_body<FLUX, NV, 2, BLOCK>(bt, st, xs);
+    __syncthreads();
+  }
+  flux_b_body<FLUX, NV, 1, BLOCK>(bt, st, xs);
 }
 
 // A wave speed as a maximum candidate: NaN and -0 become +0, so that the bit
@@ -263,6 +286,21 @@ hipError_t launch_flux_b(const KBatch& bt, const KBStep& st, hipStream_t s) {
   }
 }
 
+// the highest order, then the others
+template <int FLUX, int NV, int PM>
+hipError_t launch_flux_two_b(const KBatch& bt, const KBStep& st, hipStream_t s) {
+  const hipError_t e = launch_flux_b<FLUX, NV, PM>(bt, st, s);
+  if (PM == 1 || e != hipSuccess) return e;
+  if constexpr (PM > 1) {
+    auto kern = k_flux_low_b<FLUX, NV, PM>;
+    const int grid = persistent_grid(kern, bt.nif, 0);
+    ProfScope ps("flux_b_low", s);
+    kern<<<grid, BLOCK, 0, s>>>(bt, st);
+  }
+  ACAT_CHECK_LAUNCH();
+  return hipSuccess;
+}
+
 template <int FLUX, int NV>
 hipError_t tiles_b_impl(const KBatch& bt, const KBStep& st, hipStream_t s) {
   {
@@ -292,11 +330,21 @@ hipError_t step_b_impl(const KBatch& bt, const KBStep& st, hipStream_t s) {
   k_scatter<BATCH_PMAX, false><<<cblocks, BLOCK, 0, s>>>(st.ord, 1, bt.nif, 1, cblocks, st.offs, st.counts,
                                                          st.list);
   ACAT_CHECK_LAUNCH();
-  hipError_t e;
-  if ((e = launch_flux_b<FLUX, NV, 1>(bt, st, s)) != hipSuccess) return e;
-  if ((e = launch_flux_b<FLUX, NV, 2>(bt, st, s)) != hipSuccess) return e;
-  if ((e = launch_flux_b<FLUX, NV, 3>(bt, st, s)) != hipSuccess) return e;
-  if ((e = launch_flux_b<FLUX, NV, 4>(bt, st, s)) != hipSuccess) return e;
+  hipError_t e = hipSuccess;
+  if (bt.two_launches) {
+    switch (bt.Pmax) {
+      case 1: e = launch_flux_two_b<FLUX, NV, 1>(bt, st, s); break;
+      case 2: e = launch_flux_two_b<FLUX, NV, 2>(bt, st, s); break;
+      case 3: e = launch_flux_two_b<FLUX, NV, 3>(bt, st, s); break;
+      default: e = launch_flux_two_b<FLUX, NV, 4>(bt, st, s); break;
+    }
+    if (e != hipSuccess) return e;
+  } else {
+    if ((e = launch_flux_b<FLUX, NV, 1>(bt, st, s)) != hipSuccess) return e;
+    if ((e = launch_flux_b<FLUX, NV, 2>(bt, st, s)) != hipSuccess) return e;
+    if ((e = launch_flux_b<FLUX, NV, 3>(bt, st, s)) != hipSuccess) return e;
+    if ((e = launch_flux_b<FLUX, NV, 4>(bt, st, s)) != hipSuccess) return e;
+  }
   {
     ProfScope ps("update_b", s);
     const unsigned grid = (unsigned)((bt.ncell + BLOCK - 1) / BLOCK);

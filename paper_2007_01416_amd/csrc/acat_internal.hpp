@@ -120,6 +120,8 @@ struct KBatch {
   int waves[BATCH_PMAX + 1];    // per order class p: waves per block of the flux kernel (1, 2 or 4)
   int per_cu[BATCH_PMAX + 1];   // per order class p: persistent blocks per CU (0: occupancy limit)
   int by_tiles;                 // the whole step in one launch over the tiles, instead of one pass after another
+                                // (no launch table, and batch_split)
+  int two_launches;             // no launch table: passes take the orders below Pmax in one flux launch
   const int32_t* tiles;         // [ntiles][4] problem, first cell, cells, slot, in launch order (batch_tiles)
   const int32_t* tfirst;        // [nprob] slot of the first tile of each problem
   const int32_t* tcount;        // [nprob] its number of tiles

@@ -1,11 +1,62 @@
-// The tiles of a batch (host side): which cells each block of the tile launch steps.
+// The tiles of a batch (host side): whether a step goes by tiles, and which cells each
+// block of the tile launch steps.
 #pragma once
 
+#include <algorithm>
 #include <cstdint>
 
 #include "acat_internal.hpp"
 
 namespace acat {
+
+// How a batch is cut into tiles, and whether it is stepped by them.
+struct BatchSplit {
+  int T[BATCH_PMAX + 1];   // cells per tile of the problems of half-width P
+  int64_t ntiles;
+  bool by_tiles;
+};
+
+// T: 4 GPW r - 1 (r rounds of order P for each of a block's four waves, as in a
+// single problem), r as large as leaves the batch some 4096 tiles, four times what
+// the chip holds at once, so that the tiles dealt out last fill its gaps; and no
+// smaller than holds the mean problem of that P whole, where that fits and those
+// problems fill the chip by themselves (3000 Euler problems of 64 cells, P = 4, in
+// three tiles each 121 us per step, in one 94).
+//
+// by_tiles: not where many problems fill little of their one tile each.  A tile then
+// costs about what 100 interfaces (a scalar law: 80) cost in passes, which pack those
+// of all problems into full blocks, but take five launches more, worth some 350000
+// interfaces (480000); a full tile saves at least a tenth.  Steps of equal problems,
+// tiles / passes, P = 1 and P = 4: Euler 40000 of 8 cells 212 us / 51 and 367 / 121, of
+// 64 233 / 171 and 1010 / 928; 10000 of 64 62 / 59 and 272 / 258; 20000 of 100 126 / 140
+// and 719 / 742; 5000 of 48 33 / 37 and 117 / 119; 3000 of 8 23 / 24 and 38 / 48.
+// Burgers 40000 of 64 129 / 102 and 314 / 303, 10000 of 32 34 / 33 and 56 / 59, of 48
+// 34 / 39 and 68 / 79.
+// Never where the tiles' threads pass what a launch may hold (2^32).
+inline BatchSplit batch_split(int nprob, const int64_t* n, const int32_t* P, int nvar) {
+  BatchSplit s{};
+  int64_t count[BATCH_PMAX + 1] = {}, cells[BATCH_PMAX + 1] = {}, ncell = 0;
+  for (int b = 0; b < nprob; ++b) {
+    ++count[P[b]];
+    cells[P[b]] += n[b];
+  }
+  for (int p = 1; p <= BATCH_PMAX; ++p) ncell += cells[p];
+  for (int p = 1; p <= BATCH_PMAX; ++p) {
+    const int per = 4 * (p == 3 ? 10 : 32 / p), rmax = BLOCK / per;
+    int64_t r = ncell / ((int64_t)per * 4096);
+    if (count[p] >= 1024 && cells[p] < count[p] * BLOCK) r = std::max(r, cells[p] / count[p] / per + 1);
+    s.T[p] = per * (int)(r < 1 ? 1 : r > rmax ? rmax : r) - 1;
+  }
+  int64_t idle = 0;
+  const int64_t worth = nvar == 1 ? 80 : 100;
+  for (int b = 0; b < nprob; ++b) {
+    const int64_t t = (int64_t)((double)(n[b] + s.T[P[b]] - 1) / s.T[P[b]]);   // exact: both below 2^32
+    s.ntiles += t;
+    idle += n[b] < worth * t ? worth * t - n[b] : -(n[b] / 8);
+  }
+  s.by_tiles = idle <= (nvar == 1 ? 480000 : 350000) && s.ntiles < ((int64_t)1 << 32) / BLOCK;
+  return s;
+}
 
 // tile[4 i .. 4 i + 3]: problem, first cell, cells per tile and slot of block i's
 // tile, for tiles of T[P] cells; the slots of problem b are tfirst[b] ..

@@ -1,5 +1,7 @@
-// The tiles of a batch (batch_tiles) on the CPU: reads nprob and then n and P of every
-// problem and the tile lengths of P = 1..4; prints the tiles and the slots.
+// The tiles of a batch (batch_tiles, batch_split) on the CPU: reads nprob and then n
+// and P of every problem and the tile lengths of P = 1..4; prints the tiles and the
+// slots.  With an argument: reads nprob, n, P and nvar of batches of equal problems and
+// prints whether each goes by tiles.
 #include "hip/hip_runtime.h"
 
 #include <vector>
@@ -9,7 +11,17 @@ dim3s gridDim, blockDim;
 pthread_barrier_t g_block_barrier;
 #include "batch_tiles.hpp"
 
-int main() {
+int main(int argc, char**) {
+  if (argc > 1) {
+    int np, p, nvar;
+    long v;
+    while (std::scanf("%d %ld %d %d", &np, &v, &p, &nvar) == 4) {
+      const std::vector<int64_t> n(np, v);
+      const std::vector<int32_t> P(np, p);
+      std::printf("%d\n", (int)acat::batch_split(np, n.data(), P.data(), nvar).by_tiles);
+    }
+    return 0;
+  }
   int np = 0, T[acat::BATCH_PMAX + 1] = {};
   if (std::scanf("%d", &np) != 1) return 1;
   std::vector<int64_t> n(np);

@@ -50,3 +50,15 @@ def test_tiles_of_a_batch(exe, ns):
     assert sorted(of_slot) == list(range(len(tiles)))
     for b, (first, count) in enumerate(slots):
         assert count == -(-ns[b] // T[ps[b]]) and all(of_slot[first + k] == b for k in range(count))
+
+
+@pytest.mark.parametrize("np_, n, nvar, tiles", [
+    (1, 8, 3, True), (3000, 8, 3, True), (10000, 48, 3, False), (10000, 64, 3, False), (5000, 64, 3, True), (40000, 8, 3, False),
+    (40000, 100, 3, True), (3000, 8, 1, True), (10000, 16, 1, False), (10000, 48, 1, True), (40000, 64, 1, False), (300, 5000, 3, True),
+    (1 << 24, 8, 3, False), (1 << 24, 100, 3, False), ((1 << 24) - 1, 100, 3, True)])
+def test_many_small_problems_go_by_passes(exe, np_, n, nvar, tiles):
+    """The last three: 2^24 tiles of 256 threads are more than one launch holds."""
+    for p in (1, 2, 3, 4):
+        r = subprocess.run([exe, "rule"], input=f"{np_} {n} {p} {nvar}", capture_output=True, text=True,
+                           env=dict(os.environ, ASAN_OPTIONS="detect_leaks=0"))
+        assert r.returncode == 0 and r.stdout.split() == [str(int(tiles))], (p, r.stderr[-2000:])
