@@ -385,8 +385,9 @@ __device__ __forceinline__ void corner_adjoint(const Phys& ph, const double (&u)
     // scratch per lane, with this 472; P = 3 rectangles with an order 3 in one
     // kernel: 266 spills, then 175; Euler 192^2: 126 us, then 113; the whole P = 4
     // adjoint step of 256^2: 1998 us, then 1377).  At T = 4
-    // they fit, and recomputing them costs more: 512^2 P = 2 100.5 us, 104 so.
-    if constexpr (T > 4) {
+    // they fit, and recomputing them costs more: 512^2 P = 2 100.5 us, 104 so.  A scalar
+    // law's fit at every T (advection 600^2 q44: 1325 us, opaque 1493).
+    if constexpr (T > 4 && NV > 1) {
 #pragma unroll
       for (int l = 1; l <= kk - 1; ++l)
 #pragma unroll
@@ -925,18 +926,19 @@ __global__ __launch_bounds__(BLOCK) void k_gather2d(KProb pb, KStep st, const do
     if (e_ != hipSuccess) return e_;         \
   } while (0)
 
-// The classes of a step of P <= 3 in one launch whose blocks share the rounds of
-// all their lists: those of orders up to 2 (LOW: two blocks per CU), those with
-// an order 3 (HIGH: one block), or each of them (EACH: one).  Same arithmetic per
-// corner as a launch per class.  Bound by FP64 issue at one or two waves per SIMD,
-// and a launch per class ended each with most of the card idle: a class of a
-// small grid has fewer rounds than the card has blocks.  The blocks take the
-// rounds in turn, the costliest class first.  Whole adjoint step, Euler, launches
-// per class / one launch (P = 3 512^2: two): 192^2 P = 3 276 us / 186, 512^2 P = 3
-// 1738 / 1703, 512^2 P = 2 185 / 176.  P = 4 keeps a launch per class: its
-// rectangles of order 4 run in two launches each, and the body of all others
-// beside them spills.
-enum AdjClasses { LOW, HIGH, EACH };
+// The classes of a step of P <= 3 in launches whose blocks share the rounds of all
+// their lists, taken in turn, the costliest class first: LOW, those of orders up to 2
+// (two blocks per CU); EACH, all of P = 3 (one block); RECT2 and RECT3, the classes of
+// highest order 2 and 3 without the square one, and with (1,1) for 2.  Same arithmetic
+// per corner as a launch per class.  Bound by FP64 issue at one or two waves per SIMD,
+// and a launch per class ended each with most of the card idle: a class of a small
+// grid has fewer rounds than the card has blocks.  A large grid's square class (P, P)
+// keeps a launch of its own, in which it spills nothing and a scalar law's has twice
+// the waves (adj_square_line).  Whole adjoint step, Euler, launches per class / these:
+// 192^2 P = 3 276 us / 186, 512^2 P = 3 2547 / 2430, P = 2 413 / 385 (without noise).
+// P = 4 keeps a launch per class: its rectangles of order 4 run in two launches each,
+// and the body of all others beside them spills.
+enum AdjClasses { LOW, EACH, RECT2, RECT3 };
 
 template <int P, AdjClasses S>
 struct AdjSet {
@@ -950,8 +952,8 @@ struct AdjSet {
   }
   static constexpr Cls EVERY[9] = {cls<3, 3>(), cls<2, 3>(), cls<3, 2>(), cls<1, 3>(), cls<3, 1>(),
                                    cls<2, 2>(), cls<1, 2>(), cls<2, 1>(), cls<1, 1>()};   // costliest first
-  static constexpr int FIRST = S != LOW ? 0 : (P >= 2 ? 5 : 8);
-  static constexpr int N = S == HIGH ? 5 : 9 - FIRST;
+  static constexpr int FIRST = S == RECT2 ? 6 : S == RECT3 ? 1 : S == EACH ? 0 : (P >= 2 ? 5 : 8);
+  static constexpr int N = S == RECT3 ? 4 : 9 - FIRST;
   static constexpr Cls at(int k) { return EVERY[FIRST + k]; }
   static constexpr int max_stride() {
     int m = 1;
@@ -966,7 +968,7 @@ struct AdjSet {
 };
 
 template <int FLUX, int NV, int P, AdjClasses S>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(S == LOW ? 2 : 1))) void k_adj2d_set(
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(S == LOW || S == RECT2 ? 2 : 1))) void k_adj2d_set(
     KProb pb, KStep st, const double* __restrict__ ubo, double* __restrict__ C, int LMAX) {
   using Set = AdjSet<P, S>;
   __shared__ double2 xsm[2 * Xch<NV>::NP * Set::max_stride()];
@@ -1234,24 +1236,32 @@ hipError_t launch_adjpair2d(const KProb& pb, const KStep& st, const double* ubo,
   return hipSuccess;
 }
 
-// Corners up to which the adjoint of P = 3 takes its classes in one launch.  It saves
-// a launch and its last rounds (192^2 195 us in two, 186 in one; 384^2 933, 927;
-// 512^2 1703, 1692), but runs the low orders at one block per CU instead of two,
-// which a large grid of mostly low orders feels (512^2, noise everywhere: 97.5
-// us in two, 100.9 in one; 192^2 50.3, 46.6).
-constexpr int64_t ADJ_ONE_LAUNCH = 150000;
+// Corners up to which the classes of P = 2 and 3 go in one launch; above, the square
+// class (P, P) has its own, and the others one (P = 2) or two (P = 3).  Forward step and
+// adjoint, one launch / split, without noise, with 40 %, and noise everywhere (where a
+// split launch finds next to nothing):
+//   Euler P = 2     300^2 151 / 151, 108 / 110, 50 / 50; 400^2 262 / 250, 178 / 173, 60 / 62;
+//                   600^2 561 / 526, 380 / 361, 94 / 94
+//   Euler P = 3     300^2 802 / 811, 479 / 498, 59 / 63; 400^2 1470 / 1444, 881 / 875, 76 / 78
+//                   (there in two launches instead of one)
+//   advection P = 2 300^2 76 / 76, 63 / 64, 44 / 48; 400^2 113 / 106, 86 / 86, 51 / 57
+//   advection P = 3 200^2 129 / 122, 95 / 98, 46 / 55; 300^2 239 / 207, 164 / 155, 56 / 68
+template <int NV, int P>
+constexpr int64_t adj_square_line() {
+  return NV == 1 && P == 3 ? 60000 : 120000;
+}
 
 template <int FLUX, int NV, int P>
 hipError_t adj2d_impl(const KProb& pb, const KStep& st, const double* ubo, double* ubi, double* C, hipStream_t s) {
   hipError_t e;
   if constexpr (P <= 3) {
-    if (P == 3 && pb.n1 * pb.n2 <= ADJ_ONE_LAUNCH) {
+    if (P == 1 || pb.n1 * pb.n2 <= adj_square_line<NV, P>()) {
+      if ((e = launch_adjset<FLUX, NV, P, P == 3 ? EACH : LOW>(pb, st, ubo, C, s)) != hipSuccess) return e;
+    } else if constexpr (P > 1) {
+      if ((e = launch_adj2d<FLUX, NV, P, P, P>(pb, st, ubo, C, s)) != hipSuccess) return e;
+      if ((e = launch_adjset<FLUX, NV, P, P == 3 ? RECT3 : RECT2>(pb, st, ubo, C, s)) != hipSuccess) return e;
       if constexpr (P == 3)
-        if ((e = launch_adjset<FLUX, NV, P, EACH>(pb, st, ubo, C, s)) != hipSuccess) return e;
-    } else {
-      if ((e = launch_adjset<FLUX, NV, P, LOW>(pb, st, ubo, C, s)) != hipSuccess) return e;
-      if constexpr (P == 3)
-        if ((e = launch_adjset<FLUX, NV, P, HIGH>(pb, st, ubo, C, s)) != hipSuccess) return e;
+        if ((e = launch_adjset<FLUX, NV, P, LOW>(pb, st, ubo, C, s)) != hipSuccess) return e;
     }
   } else {
     if ((e = launch_adj2d<FLUX, NV, P, 1, 1>(pb, st, ubo, C, s)) != hipSuccess) return e;
