@@ -38,26 +38,33 @@ struct Adj1D {
   static_assert(Grp::WAVE_LOCAL, "the exchange needs no block barrier");
   static constexpr int NS = Grp::TOTAL * SL;
   static constexpr int LDS_DOUBLES = 2 * NV * NS;
+
+  Grp grp;
+  double g1[L], g1T[L];   // derivative weights at this lane's node: rows for the recursion, columns for its transpose
+  double eta;
+
+  __device__ __forceinline__ explicit Adj1D(int lane) : grp(lane) {
+#pragma unroll
+    for (int l = 0; l < L; ++l) {
+      g1[l] = TB.G1[p][grp.node][l];
+      g1T[l] = TB.G1[p][l][grp.node];
+    }
+    eta = TB.ETA[p][grp.node];
+  }
 };
 
 template <int FLUX, int NV, int p>
-__device__ __forceinline__ void adj1d_body(const KProb& pb, const KStep& st, const Groups<2 * p, 64>& grp, bool valid,
-                                           int32_t k, double dt, const double* __restrict__ ubo,
+__device__ __forceinline__ void adj1d_body(const KProb& pb, const KStep& st, const Adj1D<FLUX, NV, p>& adj,
+                                           bool valid, int32_t k, double dt, const double* __restrict__ ubo,
                                            double* __restrict__ C, double* xs) {
   constexpr int L = 2 * p, SL = Adj1D<FLUX, NV, p>::SL, NS = Adj1D<FLUX, NV, p>::NS;
-  const int g = grp.g, a = grp.node;
+  const int g = adj.grp.g, a = adj.grp.node;
   const int slot = g * SL + a;
   const double lam = dt / pb.dx;
   const int64_t nx = pb.nx, nI = pb.nIx;
   const int nx32 = (int)nx;
   const int64_t cstride = nI * 2 * pb.P;
-  double g1[L], g1T[L];
-#pragma unroll
-  for (int l = 0; l < L; ++l) {
-    g1[l] = TB.G1[p][a][l];
-    g1T[l] = TB.G1[p][l][a];
-  }
-  const double eta = TB.ETA[p][a];
+  const double(&g1)[L] = adj.g1, (&g1T)[L] = adj.g1T;
   int buf = 0;
   const int i = k + (int)pb.ioff;
   const int node = bc_node32(i, a - p + 1, nx32, pb.bc);
@@ -147,7 +154,7 @@ __device__ __forceinline__ void adj1d_body(const KProb& pb, const KStep& st, con
   double sb[NV], ub[NV], f0b[NV], fhb[NV];
 #pragma unroll
   for (int c = 0; c < NV; ++c) {
-    sb[c] = eta * psi * Fb[c];
+    sb[c] = adj.eta * psi * Fb[c];
     ub[c] = 0.0;
     f0b[c] = 0.0;
     fhb[c] = TB.INVFACT[2 * p] * sb[c];   // Fhbar^{2p-1}
@@ -1053,26 +1060,25 @@ hipError_t launch_adjset(const KProb& pb, const KStep& st, const double* ubo, do
 
 // One order of a tile's interfaces: the wave's share of its rounds, the rounds of
 // all orders dealt to the waves in turn.
-template <int FLUX, int NV, int PM, int p>
+template <int FLUX, int NV, int p>
 __device__ __forceinline__ void adjtile_order(const KProb& pb, const KStep& st, double dt,
                                               const double* __restrict__ ubo, double* __restrict__ C, double* xs,
                                               const uint8_t* list, int k0, int first, int count, int& task) {
-  if constexpr (p <= PM) {
-    using Grp = Groups<2 * p, 64>;
-    const int rounds = (count + Grp::PER_BLOCK - 1) / Grp::PER_BLOCK;
-    if (task < rounds) {
-      int lane = __lane_id();   // computed at each order: kept for all at once it would spill
-      asm volatile("" : "+v"(lane), "+v"(dt));
-      const Grp grp(lane);
-      for (; task < rounds; task += NWAVE) {
-        const int it = task * Grp::PER_BLOCK + grp.g;
-        const bool valid = grp.in && it < count;
-        const int32_t k = valid ? k0 + list[first + it] : 0;
-        adj1d_body<FLUX, NV, p>(pb, st, grp, valid, k, dt, ubo, C, xs);
-      }
+  using Adj = Adj1D<FLUX, NV, p>;
+  constexpr int PER = Adj::Grp::PER_BLOCK;
+  const int rounds = (count + PER - 1) / PER;
+  if (task < rounds) {
+    int lane = __lane_id();   // computed at each order: kept for all at once it would spill
+    asm volatile("" : "+v"(lane), "+v"(dt));
+    const Adj adj(lane);
+    for (; task < rounds; task += NWAVE) {
+      const int it = task * PER + adj.grp.g;
+      const bool valid = adj.grp.in && it < count;
+      const int32_t k = valid ? k0 + list[first + it] : 0;
+      adj1d_body<FLUX, NV, p>(pb, st, adj, valid, k, dt, ubo, C, xs);
     }
-    task -= rounds;
   }
+  task -= rounds;
 }
 
 template <int FLUX, int NV, int PM>
@@ -1087,22 +1093,26 @@ constexpr int adj1d_waves() {
   return P <= 2 ? 3 : P == 3 || (NV == 1 && P <= 5) ? 2 : 1;
 }
 
-// The contributions of a tile of T consecutive interfaces by one block, which groups
-// them by order in LDS (mapped: by the class map, else by the recorded orders,
-// which it writes to the map).  Bound by FP64 issue at the one to three waves per
-// SIMD that the Taylor history of the order leaves (spilled to reach one more it
-// is slower: Burgers P = 6 2e5 cells 411 us in one, 541 in two); small problems by
-// launches, of which lists and a kernel per order took six more.  Recorded step and
-// adjoint, Euler, 30 % noise, by orders / by tiles: 20011 cells P = 3 (and a replayed
-// step) 98 us / 53; 1e6 cells P = 3 609 / 514, P = 4 1976 / 1620, P = 5 10452 / 4982,
-// P = 6 44772 / 10622 (there the opaque history counts most).  Slower only beyond
-// what fills the chip: Burgers P = 6 2e5 cells 389 / 402, 1e6 1303 / 1396, and
-// nothing but order 1 at P = 4, 1e6 cells 143 / 164.
-template <int FLUX, int NV, int P>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(adj1d_waves<NV, P>()))) void k_adj1d(
-    KProb pb, KStep st, int T, int mapped, const double* __restrict__ ubo, double* __restrict__ C) {
-  __shared__ double xs[NWAVE][adj_xs_doubles<FLUX, NV, P>()];
-  __shared__ int wc[P][NWAVE];
+// The contributions of the interfaces of orders LO .. HI of a tile of T consecutive ones
+// by one block, which groups them by order in LDS (mapped: by the class map, else by
+// the recorded orders, which it writes to the map; counted: with the class counts).  Bound by FP64 issue at the one to
+// three waves per SIMD that the Taylor history of the order leaves (spilled to reach
+// one more it is slower: Burgers P = 6 2e5 cells 411 us in one, 541 in two); small
+// problems by launches, of which lists and a kernel per order took six more.  Recorded
+// step and adjoint, Euler, 30 % noise, by orders / by tiles: 20011 cells P = 3 (and a
+// replayed step) 98 us / 53; 1e6 cells P = 3 627 / 516, P = 4 2274 / 1610, 4e5 cells P = 5
+// 4418 / 2246, P = 6 20103 / 4795 (there the opaque history counts most); Burgers 1e6
+// cells P = 5 824 / 595, P = 6 1306 / 1236, and nothing but order 1 129 / 117.
+template <int FLUX, int NV, int P, int LO, int HI, bool TOP>
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(adj1d_waves<NV, HI>()))) void k_adj1d(
+    KProb pb, KStep st, int T, int mapped, int counted, const double* __restrict__ ubo, double* __restrict__ C) {
+  if (LO > 1 && counted) {   // the step's class counts: nothing to do
+    int any = 0;
+    for (int p = LO; p <= HI; ++p) any |= st.counts[p - 1];
+    if (any == 0) return;
+  }
+  __shared__ double xs[NWAVE][adj_xs_doubles<FLUX, NV, HI>()];
+  __shared__ int wc[HI + 1][NWAVE];
   __shared__ uint8_t list[BLOCK];
   const int tid = threadIdx.x, lane = __lane_id(), wid = tid >> 6;
   const int32_t k0 = tile_item(blockIdx.x, T, 0, pb.nIx), k = tile_item(blockIdx.x, T, tid, pb.nIx);
@@ -1122,21 +1132,30 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(adj1d_wav
   }
   unsigned long long mine = 0ull;
 #pragma unroll
-  for (int p = 1; p <= P; ++p) {
+  for (int p = LO; p <= HI; ++p) {
     const unsigned long long b = __ballot(ps == p);
     if (ps == p) mine = b;
-    if (lane == 0) wc[p - 1][wid] = __popcll(b);
+    if (lane == 0) wc[p][wid] = __popcll(b);
+  }
+  if constexpr (TOP) {
+    const unsigned long long b = __ballot(ps == P);
+    if (lane == 0) wc[0][wid] = __popcll(b);
   }
   __syncthreads();
-  int count[P + 1], first[P + 1], run = 0;
+  if (TOP && tid == 0) {
+    int n = 0;
+    for (int q = 0; q < NWAVE; ++q) n += wc[0][q];
+    st.hist[blockIdx.x] = n;
+  }
+  int count[HI + 1], first[HI + 1], run = 0;
 #pragma unroll
-  for (int p = P; p >= 1; --p) {
+  for (int p = HI; p >= LO; --p) {
     first[p] = run;
     int pos = run;
     count[p] = 0;
 #pragma unroll
     for (int q = 0; q < NWAVE; ++q) {
-      const int n = __builtin_amdgcn_readfirstlane(wc[p - 1][q]);
+      const int n = __builtin_amdgcn_readfirstlane(wc[p][q]);
       if (q < wid) pos += n;
       count[p] += n;
     }
@@ -1147,8 +1166,8 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(adj1d_wav
   int task = __builtin_amdgcn_readfirstlane(wid);
   auto order = [&](auto pc) {
     constexpr int p = decltype(pc)::value;
-    if constexpr (p <= P)
-      adjtile_order<FLUX, NV, P, p>(pb, st, dt, ubo, C, xs[wid], list, k0, first[p], count[p], task);
+    if constexpr (p >= LO && p <= HI)
+      adjtile_order<FLUX, NV, p>(pb, st, dt, ubo, C, xs[wid], list, k0, first[p], count[p], task);
   };
   order(std::integral_constant<int, 6>{});
   order(std::integral_constant<int, 5>{});
@@ -1158,20 +1177,169 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(adj1d_wav
   order(std::integral_constant<int, 1>{});
 }
 
+// The interfaces of order P (by the class map) alone, in equal shares, one contiguous
+// stretch of them per wave; counts: their number in each of ntiles tiles of T
+// interfaces.  For the scalar laws' P = 6, at one wave per SIMD: of a tile's few
+// rounds of order 6 the last left waves idle, and the last tiles the chip (1e6
+// cells, 30 % noise, the orders from 3 on by tiles 1410 us, so 1236; advection 1135 and
+// 1030).  Held to one wave the advection's round is 2 % faster, Burgers' 1 % slower.
 template <int FLUX, int NV, int P>
-hipError_t adj1d_impl(const KProb& pb, const KStep& st, bool mapped, const double* ubo, double* ubi, double* C,
-                      hipStream_t s) {
-  auto kern = k_adj1d<FLUX, NV, P>;
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_adj1d_top(KProb pb, KStep st, const int32_t* counts, int ntiles, int T,
+                                                     const double* __restrict__ ubo, double* __restrict__ C) {
+  using Adj = Adj1D<FLUX, NV, P>;
+  constexpr int PER = Adj::Grp::PER_BLOCK;
+  __shared__ double xs[NWAVE][Adj::LDS_DOUBLES];
+  __shared__ int32_t queue[NWAVE][64 + PER];
+  __shared__ int wsum[NWAVE], tile0[NWAVE], skip0[NWAVE];
+  const int tid = threadIdx.x, lane = __lane_id(), wid = wave_uniform(tid >> 6);
+  // the prefix over the tiles, a stretch of them per thread, and in it each wave's first item
+  const int per = (ntiles + BLOCK - 1) / BLOCK, t0 = min(tid * per, ntiles), t1 = min(t0 + per, ntiles);
+  int mine = 0;
+  for (int t = t0; t < t1; ++t) mine += counts[t];
+  int before = mine;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const int v = __shfl_up(before, off);
+    if (lane >= off) before += v;
+  }
+  if (lane == 63) wsum[wid] = before;
+  __syncthreads();
+  before -= mine;
+  int total = 0;
+  for (int w = 0; w < NWAVE; ++w) {
+    if (w < wid) before += wsum[w];
+    total += wsum[w];
+  }
+  const int64_t waves = (int64_t)gridDim.x * NWAVE;
+  const int64_t first = ((int64_t)(blockIdx.x % NXCD) * (gridDim.x / NXCD) + blockIdx.x / NXCD) * NWAVE;
+  for (int w = 0; w < NWAVE; ++w) {
+    int s = (int)((first + w) * total / waves) - before;
+    if (s >= 0 && s < mine) {
+      int t = t0;
+      for (; s >= counts[t]; ++t) s -= counts[t];
+      tile0[w] = t;
+      skip0[w] = s;
+    }
+  }
+  __syncthreads();
+  int left = wave_uniform((int)((first + wid + 1) * total / waves - (first + wid) * total / waves));
+  if (left == 0) return;
+  int skip = wave_uniform(skip0[wid]);
+  const Adj adj(lane);
+  const double dt = step_dt(st);
+  int32_t* q = queue[wid];
+  int queued = 0;
+  // 64 interfaces of a tile at a time, the next ones read ahead, tiles without any left out
+  int t = wave_uniform(tile0[wid]), j = 0, window = t;
+  auto filled = [&] { return __ballot(window + lane < ntiles && counts[window + lane] != 0); };
+  auto has = [&](int t, int j) {
+    const int64_t k = (int64_t)t * T + j + lane;
+    return t < ntiles && j + lane < T && k < pb.nIx && st.cls[k] == P - 1;
+  };
+  unsigned long long some = filled();
+  bool take = has(t, j);
+  while (left > 0 && t < ntiles) {
+    int tn = t, jn = j + 64;
+    if (jn >= T) {
+      jn = 0;
+      for (++tn; tn < ntiles; tn = window + 64) {
+        if (tn >= window + 64) {
+          window = tn;
+          some = filled();
+        }
+        const unsigned long long m = some >> (tn - window);
+        if (m) {
+          tn += __builtin_ctzll(m);
+          break;
+        }
+      }
+    }
+    const bool next = has(tn, jn);
+    const unsigned long long b = __ballot(take);
+    const int rank = __popcll(b & ((1ull << lane) - 1ull)) - skip, n = __popcll(b);
+    const int add = min(max(n - skip, 0), left);
+    if (take && rank >= 0 && rank < add) q[queued + rank] = (int32_t)((int64_t)t * T + j + lane);
+    skip = max(skip - n, 0);
+    queued += add;
+    left -= add;
+    wave_sync();
+    int done = 0;
+    for (; queued - done >= PER || (left == 0 && done < queued); done += PER) {
+      const bool valid = adj.grp.in && done + adj.grp.g < queued;
+      adj1d_body<FLUX, NV, P>(pb, st, adj, valid, valid ? q[done + adj.grp.g] : 0, dt, ubo, C, xs[wid]);
+    }
+    if (left == 0) break;
+    queued -= done;   // what is left, less than a round, to the front
+    const int32_t rest = lane < queued ? q[done + lane] : 0;
+    wave_sync();
+    if (lane < queued) q[lane] = rest;
+    t = tn;
+    j = jn;
+    take = next;
+  }
+}
+
+// Interfaces up to which the adjoint takes all orders in one launch.  Above, the
+// orders 1 and 2 have one of their own, at three waves per SIMD (a scalar law: eight),
+// and the scalar laws' order 6 another; a launch more costs 3 to 5 us.  Recorded step
+// and adjoint, one launch / split, without noise, with 30 %, and noise everywhere (all
+// interfaces of order 1):
+//   Euler P = 4    120000 cells 312 / 315, 249 / 253, 46 / 44; 200000 483 / 484, 397 / 396,
+//                  62 / 52; 1e6 2305 / 2268, 1632 / 1604, 165 / 124
+//   Euler P = 5    20000 206 / 207, 196 / 196, 31 / 33; 60000 544 / 536, 419 / 414, 48 / 42;
+//                  200000 1602 / 1557, 1130 / 1101, 86 / 68
+//   Euler P = 6    60000 819 / 805, 1103 / 1083, 48 / 46; 400000 3707 / 3620, 4896 / 4795, 112 / 87
+//   Burgers P = 5  120000 132 / 132, 111 / 112, 44 / 43; 200000 202 / 202, 158 / 155, 52 / 51;
+//                  1e6 811 / 797, 614 / 595, 122 / 106
+//   Burgers P = 6  100000 264 / 278, 215 / 222, 46 / 42; 200000 492 / 477, 404 / 370, 64 / 58;
+//                  1e6 1890 / 1670, 1411 / 1236, 171 / 117
+// At P <= 3 and a scalar law's P = 4 the one kernel has two waves or more for all
+// orders (Burgers P = 4 1e6 365 / 366, 289 / 290, 91 / 88).
+template <int NV, int P>
+constexpr int64_t adj1d_line() {
+  return P < 4 || (NV == 1 && P == 4) ? INT64_MAX : NV == 1 ? 125000 : P == 4 ? 150000 : 50000;
+}
+
+// Tiles of the interfaces of orders LO .. HI, T interfaces each.  TOP: writes the number
+// of those of order P > HI in each tile to st.hist.
+template <int FLUX, int NV, int P, int LO, int HI, bool TOP = false>
+hipError_t launch_adj1d(const KProb& pb, const KStep& st, bool mapped, bool counted, const double* ubo, double* C,
+                        hipStream_t s, int* tile = nullptr) {
+  auto kern = k_adj1d<FLUX, NV, P, LO, HI, TOP>;
   static const int per_cu = [&] {
     int b = 0;
     return hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, kern, BLOCK, 0) == hipSuccess && b > 0 ? b : 1;
   }();
-  const int T = tile_cells<P>(pb.nIx, (int64_t)per_cu * num_cus(), 0, BLOCK);
-  {
-    ProfScope ps("adjoint1d", s);
-    kern<<<(unsigned)((pb.nIx + T - 1) / T), BLOCK, 0, s>>>(pb, st, T, mapped, ubo, C);
+  const int T = tile_cells<HI>(pb.nIx, (int64_t)per_cu * num_cus(), 0, BLOCK);
+  if (tile) *tile = T;
+  static const char* const names[3] = {"adjoint1d", "adjoint1d_low", "adjoint1d_high"};
+  ProfScope ps(names[LO == 1 && HI == P ? 0 : LO == 1 ? 1 : 2], s);
+  kern<<<(unsigned)((pb.nIx + T - 1) / T), BLOCK, 0, s>>>(pb, st, T, mapped, counted, ubo, C);
+  return hipGetLastError();
+}
+
+template <int FLUX, int NV, int P>
+hipError_t adj1d_impl(const KProb& pb, const KStep& st, bool mapped, const double* ubo, double* ubi, double* C,
+                      hipStream_t s) {
+  hipError_t e;
+  if (pb.nIx <= adj1d_line<NV, P>()) {
+    if ((e = launch_adj1d<FLUX, NV, P, 1, P>(pb, st, mapped, mapped, ubo, C, s)) != hipSuccess) return e;
+  } else if constexpr (P >= 4) {
+    constexpr bool TOP = NV == 1 && P == 6;
+    int T = 0;
+    if ((e = launch_adj1d<FLUX, NV, P, 1, 2, TOP>(pb, st, mapped, mapped, ubo, C, s, &T)) != hipSuccess)
+      return e;
+    if ((e = launch_adj1d<FLUX, NV, P, 3, TOP ? P - 1 : P>(pb, st, true, mapped, ubo, C, s)) != hipSuccess) return e;
+    if constexpr (TOP) {
+      // the tiles' counts lie where a 2D step has its histograms, MAX_CLASSES for each 256 interfaces
+      static_assert(NWAVE * Groups<4, 64>::PER_BLOCK * MAX_CLASSES >= 256, "the tiles' counts fit the histograms");
+      auto kern = k_adj1d_top<FLUX, NV, P>;
+      const int grid = persistent_grid(kern, pb.nIx, 0);
+      ProfScope ps("adjoint1d_top", s);
+      kern<<<grid, BLOCK, 0, s>>>(pb, st, st.hist, (int)((pb.nIx + T - 1) / T), T, ubo, C);
+      if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
   }
-  ACAT_CHECK_LAUNCH();
   {
     ProfScope ps("gather1d", s);
     k_gather1d<NV, P><<<(unsigned)((pb.nx + BLOCK - 1) / BLOCK), BLOCK, 0, s>>>(pb, st, ubo, C, ubi);
