@@ -633,9 +633,16 @@ struct ClassSet {
   }
 };
 
-template <int FLUX, int NV, int P, Blocks B, bool SQUARE>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(B == THREE ? 3 : 2))) void k_flux2d(KProb pb,
-                                                                                                         KStep st) {
+// waves per SIMD the kernel is held to: a scalar law's P = 2 six (99 registers
+// otherwise, four; 800^2 to 2000^2 4 to 5 % faster)
+template <int NV, int P, Blocks B>
+constexpr int flux2d_waves() {
+  return NV == 1 && P == 2 ? 6 : B == THREE ? 3 : 2;
+}
+
+template <int FLUX, int NV, int P, Blocks B, bool SQUARE, bool DRAW>
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(flux2d_waves<NV, P, B>()))) void k_flux2d(
+    KProb pb, KStep st) {
   using Set = ClassSet<P, B, SQUARE>;
   static_assert(Set::N <= 9, "one case of the switch per class");
   __shared__ double2 xsm[2 * Xch<NV>::NP * Set::max_stride()];
@@ -660,7 +667,8 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(B == THRE
     }
     return t;
   }();
-  Chunks<Set::N> ck(st, tab, B == TWO ? 1 : 0, blockIdx.x, gridDim.x, [&](int k, int& c, int& per_round) {
+  constexpr int MIN = NV == 1 && P == 2 ? 2 : 1;
+  Chunks<Set::N, DRAW, MIN> ck(st, tab, B == TWO ? 1 : 0, blockIdx.x, gridDim.x, [&](int k, int& c, int& per_round) {
     c = sets.cls[k];
     per_round = sets.per_round[k];
   });
@@ -786,7 +794,7 @@ CflReduce cfl_reduce(const KProb& pb, const KStep& st, int nparts) {
   } while (0)
 
 // The classes of one launch (ClassSet).
-template <int FLUX, int NV, int P, Blocks B, bool SQUARE>
+template <int FLUX, int NV, int P, Blocks B, bool SQUARE, bool DRAW = true>
 hipError_t launch_flux2d(const KProb& pb, const KStep& st, int cap, hipStream_t s) {
   using Set = ClassSet<P, B, SQUARE>;
   if constexpr (Set::N > 0) {
@@ -795,7 +803,7 @@ hipError_t launch_flux2d(const KProb& pb, const KStep& st, int cap, hipStream_t 
       for (int k = 0; k < Set::N; ++k) n += "q" + std::to_string(10 * Set::at(k).q1 + Set::at(k).q2);
       return n;
     }();
-    auto kern = k_flux2d<FLUX, NV, P, B, SQUARE>;
+    auto kern = k_flux2d<FLUX, NV, P, B, SQUARE, DRAW>;
     static const int per_cu = [&] {
       int b = 0;
       return hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, kern, BLOCK, 0) == hipSuccess && b > 0 ? b : 1;
@@ -819,13 +827,26 @@ hipError_t launch_flux2d(const KProb& pb, const KStep& st, int cap, hipStream_t 
 // 149 and 149, 512^2 358 and 343.  (At P = 4 two are as fast or faster: 100^2
 // 37.2 and 34.9, 300^2 193.8 and 195.6, 1021 x 777 3391 and 3397.)
 constexpr int64_t ONE_LAUNCH = 90000;
+// A scalar law's rounds of P <= 2 take about as long as a ticket: drawn one by one
+// they made advection 500^2 P = 2 67 us without noise, where a launch per class took
+// 61, and 1200^2 P = 1 64 (63).  P = 1 takes fixed shares (55; one class, whose rounds
+// are alike), P = 2 up to this many corners: 300^2 fixed / tickets of two rounds and
+// more 29 / 34 us, 400^2 41 / 44, 500^2 58 / 57, 600^2 78 / 75, 900^2 155 / 133.
+constexpr int64_t SCALAR_FIXED = 250000;
 template <int FLUX, int NV, int P, bool SQUARE>
 hipError_t launch_classes2d(const KProb& pb, const KStep& st, int cap, hipStream_t s) {
-  if constexpr (P == 3) {
-    if (pb.n1 * pb.n2 <= ONE_LAUNCH) return launch_flux2d<FLUX, NV, P, ALL, SQUARE>(pb, st, cap, s);
+  if constexpr (NV == 1 && P == 1) {
+    return launch_flux2d<FLUX, NV, P, THREE, SQUARE, false>(pb, st, cap, s);
+  } else {
+    if constexpr (NV == 1 && P == 2) {
+      if (pb.n1 * pb.n2 <= SCALAR_FIXED) return launch_flux2d<FLUX, NV, P, THREE, SQUARE, false>(pb, st, cap, s);
+    }
+    if constexpr (P == 3) {
+      if (pb.n1 * pb.n2 <= ONE_LAUNCH) return launch_flux2d<FLUX, NV, P, ALL, SQUARE>(pb, st, cap, s);
+    }
+    const hipError_t e = launch_flux2d<FLUX, NV, P, THREE, SQUARE>(pb, st, cap, s);
+    return e != hipSuccess ? e : launch_flux2d<FLUX, NV, P, TWO, SQUARE>(pb, st, cap, s);
   }
-  const hipError_t e = launch_flux2d<FLUX, NV, P, THREE, SQUARE>(pb, st, cap, s);
-  return e != hipSuccess ? e : launch_flux2d<FLUX, NV, P, TWO, SQUARE>(pb, st, cap, s);
 }
 
 // Tiles up to which the list kernel sums the class histograms itself instead of

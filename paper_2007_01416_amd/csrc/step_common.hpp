@@ -554,7 +554,8 @@ __device__ __forceinline__ T wave_uniform(T v) {
 // instead of per block made class (2, 2) of 400^2 corners 65 us instead of 40:
 // draws from one counter take about 20 ns each.
 // Without tickets (DRAW false: the reverse kernels, whose step has no launch to
-// clear them in): chunks of one round, block j takes the j-th, (j + nb)-th, ...
+// clear them in, and where rounds are short): chunks of one round, block j takes the
+// j-th, (j + nb)-th, ...  MIN: least rounds per chunk.
 struct ChunkTable {
   int32_t cum[MAX_CLASSES + 1];     // first chunk of each class in the sequence, and their number
   int32_t len[MAX_CLASSES];         // items of the class's region
@@ -563,7 +564,7 @@ struct ChunkTable {
   int32_t next[2];                  // ticket broadcast, used in turn (one barrier per chunk)
 };
 
-template <int NCLS, bool DRAW = true>
+template <int NCLS, bool DRAW = true, int MIN = 1>
 struct Chunks {
   int cls, base, end;               // the current chunk: items [base, end) of class number cls
   const int32_t* items;             // of that class's region
@@ -590,7 +591,7 @@ struct Chunks {
         const int64_t n = st.counts[c], lo = n * x / NXCD;
         const int len = (int)(n * (x + 1) / NXCD - lo);
         const int share = len / (per_round * nb * 8);
-        const int step = per_round * (!DRAW || share < 1 ? 1 : share > 8 ? 8 : share);
+        const int step = per_round * (!DRAW ? 1 : share < MIN ? MIN : share > 8 ? 8 : share);
         tab.cum[k] = cum;
         tab.len[k] = len;
         tab.step[k] = step;
