@@ -14,7 +14,6 @@
 // fixed order (deterministic, no atomics).
 #include <hip/hip_runtime.h>
 
-#include <string>
 #include <utility>
 
 #include "acat_internal.hpp"
@@ -1038,11 +1037,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(S == LOW 
 template <int FLUX, int NV, int P, AdjClasses S>
 hipError_t launch_adjset(const KProb& pb, const KStep& st, const double* ubo, double* C, hipStream_t stream) {
   using Set = AdjSet<P, S>;
-  static const std::string name = [] {
-    std::string n = "adjoint2d_";
-    for (int k = 0; k < Set::N; ++k) n += "q" + std::to_string(10 * Set::at(k).q1 + Set::at(k).q2);
-    return n;
-  }();
+  static constexpr LaunchName name = class_launch_name<Set>("adjoint2d_");
   auto kern = k_adj2d_set<FLUX, NV, P, S>;
   static const int per_cu = [&] {
     int b = 0;
@@ -1051,7 +1046,7 @@ hipError_t launch_adjset(const KProb& pb, const KStep& st, const double* ubo, do
   const int64_t rounds = pb.n1 * pb.n2 / Set::min_per_round() + NXCD * Set::N;
   const int grid = persistent_grid(kern, rounds * BLOCK, 0, BLOCK, per_cu);
   {
-    ProfScope ps(name.c_str(), stream);
+    ProfScope ps(name.s, stream);
     kern<<<grid, BLOCK, 0, stream>>>(pb, st, ubo, C, 4 * P * P);
   }
   ACAT_CHECK_LAUNCH();

@@ -24,7 +24,6 @@
 //   k_update2d     conservative flux-difference update + status bits
 #include <hip/hip_runtime.h>
 
-#include <string>
 #include <utility>
 
 #include "acat_internal.hpp"
@@ -798,11 +797,7 @@ template <int FLUX, int NV, int P, Blocks B, bool SQUARE, bool DRAW = true>
 hipError_t launch_flux2d(const KProb& pb, const KStep& st, int cap, hipStream_t s) {
   using Set = ClassSet<P, B, SQUARE>;
   if constexpr (Set::N > 0) {
-    static const std::string name = [] {
-      std::string n = "flux2d_";
-      for (int k = 0; k < Set::N; ++k) n += "q" + std::to_string(10 * Set::at(k).q1 + Set::at(k).q2);
-      return n;
-    }();
+    static constexpr LaunchName name = class_launch_name<Set>("flux2d_");
     auto kern = k_flux2d<FLUX, NV, P, B, SQUARE, DRAW>;
     static const int per_cu = [&] {
       int b = 0;
@@ -812,7 +807,7 @@ hipError_t launch_flux2d(const KProb& pb, const KStep& st, int cap, hipStream_t 
     const int64_t rounds = pb.n1 * pb.n2 / Set::min_per_round() + NXCD * Set::N;
     const int grid = persistent_grid(kern, rounds * BLOCK, cap, BLOCK, per_cu);
     {
-      ProfScope ps(name.c_str(), s);
+      ProfScope ps(name.s, s);
       kern<<<grid, BLOCK, 0, s>>>(pb, st);
     }
     ACAT_CHECK_LAUNCH();

@@ -635,6 +635,25 @@ struct Chunks {
   }
 };
 
+// The kernel timer's name of a launch of several 2D classes: the prefix and "q<q1><q2>"
+// for each class of the set.
+struct LaunchName {
+  char s[64];
+};
+
+template <class Set>
+constexpr LaunchName class_launch_name(const char* prefix) {
+  LaunchName n{};
+  int i = 0;
+  for (; prefix[i]; ++i) n.s[i] = prefix[i];
+  for (int k = 0; k < Set::N; ++k) {
+    n.s[i++] = 'q';
+    n.s[i++] = (char)('0' + Set::at(k).q1);
+    n.s[i++] = (char)('0' + Set::at(k).q2);
+  }
+  return n;
+}
+
 // Persistent grid of a lane-per-node kernel whose blocks take PER_BLOCK
 // items (groups of L lanes) per round: at most one block per PER_BLOCK of
 // the nitems items the kernel's lists can hold (a round's worth each), and
