@@ -272,7 +272,7 @@ __global__ __launch_bounds__(BLOCK) void k_gather1d(KProb pb, KStep st, const do
     const int ilo = m < P ? ioff : m - P;
     const int ihi = m >= nx - P ? nx - 1 : m + P - 1;
     for (int i = ilo; i <= ihi; ++i) {
-      const int q = st.cls[i - ioff] + 1;
+      const int q = min(st.cls[i - ioff] + 1, P);   // no order beyond P, whatever the map holds
       for (int a = 0; a < 2 * q; ++a) {
         const int j = a - q + 1;
         if (bc_node32(i, j, nx, pb.bc) != m) continue;
