@@ -286,6 +286,16 @@ class AdjointRun:
         # (entries (q1 - 1) P + (q2 - 1); the later entries of a row are not defined)
         self.class_log = None
 
+    @property
+    def seg_cls(self) -> torch.Tensor:
+        """Class counts, int32 [k, 16], of the steps the first buffer set holds, as
+        their workspaces have them (a row's entries as in class_log)."""
+        return self._counts(self.segs[0], len(self.seg_ws))
+
+    @staticmethod
+    def _counts(seg, m):
+        return torch.stack([w[:64].view(torch.int32) for w in seg.ws[:m]])
+
     # ------------------------------------------------------------ segments
     def _fwd_body(self, m, decs):
         a, b = self.fa, self.fb
@@ -371,7 +381,7 @@ class AdjointRun:
         sg = self.segs[b]
         dts[n0:n0 + m].copy_(sg.dt[:m])
         if self.class_log is not None:
-            self.class_log[n0:n0 + m].copy_(torch.stack([w[:64].view(torch.int32) for w in sg.ws[:m]]))
+            self.class_log[n0:n0 + m].copy_(self._counts(sg, m))
         if self.verify:
             _order_hashes(sg.dec[:m], self._hash_w, hashes[n0:n0 + m])
 
