@@ -133,9 +133,11 @@ acat_status acat_step(const acat_problem* prob, const double* u_in, double* u_ou
 
 /* One step with its own CFL time step: dt_dev[0] = the time step that
  * acat_max_wave_speed + acat_cfl_dt(cfl, t_final, t_dev) would give for u_in
- * (bit for bit), computed inside the step (the classification pass reduces
- * the wave speeds; no atomics, no extra pass over u_in), then u_out = the
- * step of u_in with it.  t_dev (nullable) is advanced as in acat_cfl_dt.
+ * (bit for bit), computed inside the step, then u_out = the step of u_in with
+ * it.  No atomics.  2D: the classification pass reduces the wave speeds, no
+ * extra pass over u_in; 1D: a problem of one tile (up to four rounds of a
+ * block) reduces its own, a larger one takes a launch over u_in before the
+ * tiles.  t_dev (nullable) is advanced as in acat_cfl_dt.
  * dt_dev (device scalar) is required; cfl > 0. */
 acat_status acat_step_cfl(const acat_problem* prob, const double* u_in, double* u_out, double cfl, double t_final,
                           double* t_dev, double* dt_dev, void* workspace, size_t workspace_bytes,
@@ -204,7 +206,8 @@ acat_status acat_step_adjoint(const acat_problem* prob, const double* u_in, doub
  * written step_workspace since that step.  Results equal acat_step_adjoint's
  * bit for bit.  The pairing is the caller's: only the sizes are checked
  * (ACAT_ERR_WORKSPACE when step_workspace_bytes < acat_workspace_size(prob));
- * a workspace of another step gives wrong results, not an error.  The
+ * a workspace of another step gives wrong results, not an error (in 1D a step
+ * that recorded nothing leaves no class map).  The
  * library reads step_workspace and does not modify it; `workspace` is the
  * adjoint workspace as in acat_step_adjoint.  For a reverse sweep over many
  * steps this keeps one step workspace per recomputed step. */
@@ -264,11 +267,12 @@ acat_status acat_batch_init(const acat_batch* batch, void* workspace, size_t wor
 acat_status acat_step_batched(const acat_batch* batch, const double* u_in, double* u_out, const double* dt_dev,
                               void* workspace, size_t workspace_bytes, void* stream);
 /* The same step, and then dt_dev[b] = the time step that acat_batched_cfl_dt
- * (cfl) gives for u_out, bit for bit: the update pass reduces the new
- * state's wave speeds (one partial maximum per wavefront that lies inside
- * one problem, atomic maxima on the bit patterns for wavefronts that
- * straddle problems; max is exact in any order) and a last small launch
- * folds them per problem, so no extra pass over u_out is made.  dt_dev is
+ * (cfl) gives for u_out, bit for bit: the step reduces the new state's wave
+ * speeds where it writes them (by tiles one partial maximum per tile; by
+ * passes one per wavefront that lies inside one problem and atomic maxima on
+ * the bit patterns for wavefronts that straddle problems; max is exact in any
+ * order) and a last small launch folds them per problem, so no extra pass
+ * over u_out is made.  dt_dev is
  * read as this step's time steps before it is overwritten; cfl > 0.  The
  * first dt_dev comes from acat_batched_cfl_dt.  Errors as acat_step_batched,
  * and ACAT_ERR_ARG for cfl <= 0 or NaN. */

@@ -386,8 +386,9 @@ class Batch:
 
     def set_launch(self, table=None):
         """Launch shapes of the per-order flux kernels: {p: (waves_per_block,
-        blocks_per_cu)} (missing p and None: the defaults 4 waves, occupancy
-        limit).  Results do not depend on it."""
+        blocks_per_cu)}, a missing p with the defaults (4 waves, occupancy
+        limit); None: the default launch, by tiles of the problems or, for very
+        many very small ones, by passes.  Results do not depend on it."""
         import numpy as np
         if table is None:
             self._launch = None

@@ -10,7 +10,7 @@ so each is tuned on its own: every candidate shape runs the whole batched
 step on a fixed state a few times with the library's kernel timer on, and
 the class's own kernel time decides; the per-class picks are then kept only
 if the whole graph-replayed step runs faster with them than with the
-default single launch.  Launches never change results (tested bit for
+default launch.  Launches never change results (tested bit for
 bit), only time.
 """
 from __future__ import annotations
@@ -38,7 +38,7 @@ def _time_classes(batch, u, dt, out, reps):
 def tune(batch, u: torch.Tensor, dt: torch.Tensor, reps: int = 5, waves=WAVES, per_cu=PER_CU,
          cache: str | None = None, verbose: bool = False) -> dict:
     """Choose and set the fastest launch: one launch per order class with the
-    fastest shape of each, or the default single launch over tiles.
+    fastest shape of each, or the default launch (by tiles, or by passes).
     Returns {p: (waves, blocks_per_cu, ms)}: ms the class kernel's time, or
     (0, 0, ms per step) for every p when the default launch is kept.  With
     `cache` (a JSON file) a choice stored for the same batch signature is
@@ -64,7 +64,7 @@ def tune(batch, u: torch.Tensor, dt: torch.Tensor, reps: int = 5, waves=WAVES, p
                 if p not in best or ms < best[p][2]:
                     best[p] = (wv, pc, ms)
     # the per-class optimum is kept only if the whole graph-replayed step is
-    # at least 2 % faster with it than with the default single launch (the
+    # at least 2 % faster with it than with the default launch (the
     # launches interact through the caches and the scheduler; the default is
     # never replaced by a slower pick)
     tuned = {p: (v[0], v[1]) for p, v in best.items()}
@@ -74,7 +74,7 @@ def tune(batch, u: torch.Tensor, dt: torch.Tensor, reps: int = 5, waves=WAVES, p
         print(f"[tune] graph-replayed step: tuned {t_tuned * 1e3:.1f} us, default {t_default * 1e3:.1f} us",
               flush=True)
     if not t_tuned < 0.98 * t_default:      # within 2 %: timing noise, keep the default
-        best = {p: (0, 0, t_default) for p in best}   # waves 0: the default single launch over tiles
+        best = {p: (0, 0, t_default) for p in best}   # waves 0: the default launch
         tuned = None
     batch.set_launch(tuned)
     if cache:

@@ -168,7 +168,8 @@ __device__ __forceinline__ void adj1d_body(const KProb& pb, const KStep& st, con
     // as in the 2D recursion: not the forward sweep's predicted states, held from
     // there to here (registers and scratch of p = 3, 4, 5 in a kernel of its own: 352,
     // 512 + 472 bytes, 512 + 2180; so 270, 440, 512 + 488).  A scalar's fit up to
-    // p = 6 (Burgers 2e5 cells: P = 4 94 us, opaque 88; P = 5 159, 164; P = 6 402, 411).
+    // p = 6 (Burgers 2e5 cells, all orders by tiles: P = 4 94 us, opaque 88; P = 5 159,
+    // 164; P = 6 402, 411).
     if constexpr (p >= 2 && (NV > 1 || p <= 4)) {
 #pragma unroll
       for (int l = 1; l <= kk - 1; ++l)

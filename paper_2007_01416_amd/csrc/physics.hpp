@@ -24,7 +24,7 @@ struct Phys {
 // result lies within (1/2 + 2^-18) ulp of 1/x, from which the residual
 // correction of recip() and div_rn() rounds correctly, as from two Newton
 // steps (2^-97 before their last rounding), with one fused multiply-add less
-// on a shorter chain.
+// on a shorter chain.  (One significand is left out, see recip().)
 __device__ __forceinline__ double rcp_refined(double x) {
   const double r = __builtin_amdgcn_rcp(x);
   const double e = fma(-x, r, 1.0);
@@ -63,9 +63,11 @@ __device__ __forceinline__ void flux1d(const Phys& ph, const double (&u)[NV], do
   }
 }
 
-// 1/x, correctly rounded, for |x| in [2^-700, 2^700]: refined reciprocal and
-// residual correction, without exponent scaling and special-case fix-up, which
-// are identities in that range.  (Outside it, e.g. x = 0, the result is not
+// 1/x, correctly rounded, for |x| in [2^-700, 2^700] except where all bits of the
+// significand are ones (x = 2^k (2 - 2^-52): the estimate 2^-k-1 is its own
+// correction's fixed point, one ulp below): refined reciprocal and residual
+// correction, without exponent scaling and special-case fix-up, which are
+// identities in that range.  (Outside it, e.g. x = 0, the result is not
 // the IEEE one; such densities are non-physical.)
 __device__ __forceinline__ double recip(double x) {
   const double r = rcp_refined(x);

@@ -1,10 +1,11 @@
 """Time loop around the ACAT step: device-side CFL time step, ping-pong state
 buffers, and HIP-graph capture of several steps.
 
-Each step is: acat_max_wave_speed -> acat_cfl_dt (dt and t stay on the
-device) -> acat_step.  Nothing synchronises with the host, so a block of
-steps can be captured once into a HIP graph (torch.cuda.CUDAGraph drives
-hipStreamBeginCapture on its capture stream) and replayed.
+Each step is acat_step_cfl (a replayed one acat_max_wave_speed, acat_cfl_dt and
+acat_step_replay); dt and t stay on the device.  Nothing synchronises with the
+host, so a block of steps can be captured once into a HIP graph
+(torch.cuda.CUDAGraph drives hipStreamBeginCapture on its capture stream) and
+replayed.
 
 AdjointRun / ACATRun: gradients of a function of the final state of an
 n-step run with respect to the initial state, through acat_step_adjoint,
