@@ -936,16 +936,17 @@ __global__ __launch_bounds__(BLOCK) void k_gather2d(KProb pb, KStep st, const do
 // The classes of a step of P <= 3 in launches whose blocks share the rounds of all
 // their lists, taken in turn, the costliest class first: LOW, those of orders up to 2
 // (two blocks per CU); EACH, all of P = 3 (one block); RECT2 and RECT3, the classes of
-// highest order 2 and 3 without the square one, and with (1,1) for 2.  Same arithmetic
-// per corner as a launch per class.  Bound by FP64 issue at one or two waves per SIMD,
+// highest order 2 and 3 without the square one, and with (1,1) for 2; REST, all of
+// P = 3 without the square one (a scalar law's, two blocks).  Same arithmetic per
+// corner as a launch per class.  Bound by FP64 issue at one or two waves per SIMD,
 // and a launch per class ended each with most of the card idle: a class of a small
 // grid has fewer rounds than the card has blocks.  A large grid's square class (P, P)
 // keeps a launch of its own, in which it spills nothing and a scalar law's has twice
 // the waves (adj_square_line).  Whole adjoint step, Euler, launches per class / these:
-// 192^2 P = 3 276 us / 186, 512^2 P = 3 2547 / 2430, P = 2 413 / 385 (without noise).
-// P = 4 keeps a launch per class: its rectangles of order 4 run in two launches each,
-// and the body of all others beside them spills.
-enum AdjClasses { LOW, EACH, RECT2, RECT3 };
+// 192^2 P = 3 276 us / 186, 512^2 P = 3 2547 / 2430, 600^2 P = 2 550 / 526 (without
+// noise).  P = 4 keeps a launch per class: its rectangles of order 4 run in two
+// launches each, and the body of all others beside them spills.
+enum AdjClasses { LOW, EACH, RECT2, RECT3, REST };
 
 template <int P, AdjClasses S>
 struct AdjSet {
@@ -959,7 +960,7 @@ struct AdjSet {
   }
   static constexpr Cls EVERY[9] = {cls<3, 3>(), cls<2, 3>(), cls<3, 2>(), cls<1, 3>(), cls<3, 1>(),
                                    cls<2, 2>(), cls<1, 2>(), cls<2, 1>(), cls<1, 1>()};   // costliest first
-  static constexpr int FIRST = S == RECT2 ? 6 : S == RECT3 ? 1 : S == EACH ? 0 : (P >= 2 ? 5 : 8);
+  static constexpr int FIRST = S == RECT2 ? 6 : S == RECT3 || S == REST ? 1 : S == EACH ? 0 : (P >= 2 ? 5 : 8);
   static constexpr int N = S == RECT3 ? 4 : 9 - FIRST;
   static constexpr Cls at(int k) { return EVERY[FIRST + k]; }
   static constexpr int max_stride() {
@@ -1401,18 +1402,22 @@ hipError_t launch_adjpair2d(const KProb& pb, const KStep& st, const double* ubo,
 }
 
 // Corners up to which the classes of P = 2 and 3 go in one launch; above, the square
-// class (P, P) has its own, and the others one (P = 2) or two (P = 3).  Forward step and
-// adjoint, one launch / split, without noise, with 40 %, and noise everywhere (where a
-// split launch finds next to nothing):
-//   Euler P = 2     300^2 151 / 151, 108 / 110, 50 / 50; 400^2 262 / 250, 178 / 173, 60 / 62;
-//                   600^2 561 / 526, 380 / 361, 94 / 94
-//   Euler P = 3     300^2 802 / 811, 479 / 498, 59 / 63; 400^2 1470 / 1444, 881 / 875, 76 / 78
-//                   (there in two launches instead of one)
-//   advection P = 2 300^2 76 / 76, 63 / 64, 44 / 48; 400^2 113 / 106, 86 / 86, 51 / 57
-//   advection P = 3 200^2 129 / 122, 95 / 98, 46 / 55; 300^2 239 / 207, 164 / 155, 56 / 68
+// class (P, P) has its own, and the others one (Euler P = 3 two).  The line lies where
+// the launch more is also small against a step in which next to nothing is smooth.
+// Forward step and adjoint in us, one launch / split, without noise, with 30 % and
+// 60 % of it, and noise everywhere:
+//   Euler P = 2     350^2 200 / 197, 153 / 153, 111 / 114, 50 / 52; 512^2 408 / 384,
+//                   306 / 291, 208 / 204, 78 / 80 (200 steps of a run with 84 % of the
+//                   corners of class (1, 1): reverse pass 15.6 ms / 16.2); 600^2
+//                   562 / 526, 418 / 400, 281 / 273, 94 / 95
+//   Euler P = 3     350^2 1121 / 1101, 784 / 787, 479 / 487, 64 / 69
+//   advection P = 2 300^2 76 / 76, without and 44 / 48 with noise everywhere; 350^2
+//                   96 / 81, 80 / 72, 67 / 60, 48 / 47
+//   advection P = 3 250^2 180 / 157, 142 / 126, 106 / 99, 49 / 57; 350^2 312 / 257,
+//                   241 / 207, 167 / 150, 69 / 73
 template <int NV, int P>
 constexpr int64_t adj_square_line() {
-  return NV == 1 && P == 3 ? 60000 : 120000;
+  return NV == 1 ? (P == 3 ? 100000 : 120000) : P == 3 ? 150000 : 300000;
 }
 
 template <int FLUX, int NV, int P>
@@ -1423,8 +1428,9 @@ hipError_t adj2d_impl(const KProb& pb, const KStep& st, const double* ubo, doubl
       if ((e = launch_adjset<FLUX, NV, P, P == 3 ? EACH : LOW>(pb, st, ubo, C, s)) != hipSuccess) return e;
     } else if constexpr (P > 1) {
       if ((e = launch_adj2d<FLUX, NV, P, P, P>(pb, st, ubo, C, s)) != hipSuccess) return e;
-      if ((e = launch_adjset<FLUX, NV, P, P == 3 ? RECT3 : RECT2>(pb, st, ubo, C, s)) != hipSuccess) return e;
-      if constexpr (P == 3)
+      constexpr AdjClasses others = P == 2 ? RECT2 : NV == 1 ? REST : RECT3;
+      if ((e = launch_adjset<FLUX, NV, P, others>(pb, st, ubo, C, s)) != hipSuccess) return e;
+      if constexpr (others == RECT3)
         if ((e = launch_adjset<FLUX, NV, P, LOW>(pb, st, ubo, C, s)) != hipSuccess) return e;
     }
   } else {
