@@ -1411,7 +1411,7 @@ hipError_t launch_adjpair2d(const KProb& pb, const KStep& st, const double* ubo,
 //                   corners of class (1, 1): reverse pass 15.6 ms / 16.2); 600^2
 //                   562 / 526, 418 / 400, 281 / 273, 94 / 95
 //   Euler P = 3     350^2 1121 / 1101, 784 / 787, 479 / 487, 64 / 69
-//   advection P = 2 300^2 76 / 76, without and 44 / 48 with noise everywhere; 350^2
+//   advection P = 2 300^2 76 / 76 without, 44 / 48 with noise everywhere; 350^2
 //                   96 / 81, 80 / 72, 67 / 60, 48 / 47
 //   advection P = 3 250^2 180 / 157, 142 / 126, 106 / 99, 49 / 57; 350^2 312 / 257,
 //                   241 / 207, 167 / 150, 69 / 73

@@ -10,7 +10,7 @@
 // of the class maps, lists, weights and interface fluxes.  What remains is
 // bound by the fluxes' FP64 issue and dependency latency.  Measured per step,
 // pass by pass -> by tiles: 200 cells P = 2 25.5 -> 8.9 us (eager), 4096
-// cells P = 4 30.1 -> 14.7 us (graph), 4.2 M cells P = 6 4157 -> 3890 us, a
+// cells P = 4 30.1 -> 14.7 us (graph), 4.2 M cells P = 6 3929 -> 3608 us, a
 // batch of 256 problems of 1.2 M cells, P = 2..4, 325 -> 209 us.
 #pragma once
 
